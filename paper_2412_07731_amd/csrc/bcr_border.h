@@ -1,5 +1,5 @@
 // Border step of the Schur solve by cyclic reduction, shared by the one-tile
-// and the two-tile pair kernels: after the forward reduction every pair j has
+// and the wider pairs' kernels: after the forward reduction every pair j has
 // left its border partial Z_j'w_j (16 t0 values) in pb.
 #pragma once
 

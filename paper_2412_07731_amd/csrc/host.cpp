@@ -259,6 +259,8 @@ struct ahlp_problem_s {
   // workspace of a refined solve (allocated at create; ahlp_kkt_solve_noalloc
   // points it into the library's static device array for one call)
   SolveWs ws{};
+  double *wide_r = nullptr, *wide_w = nullptr, *wide_up = nullptr, *wide_pb = nullptr,
+         *wide_u0p = nullptr;   // pair vectors of the Schur solve for pairs of over 32 rows
   double *aty = nullptr, *gdir = nullptr;
   double *ones = nullptr, *zerosn = nullptr;
   // predictor/corrector right-hand sides by linearity (padded v-space) and scaled vectors
@@ -362,10 +364,14 @@ size_t solve_ws_layout(const ahlp_problem_s* p, double* base, SolveWs* ws) {
   take(&w.ex, n); take(&w.ey, m); take(&w.ez, n);
   take(&w.cx, n); take(&w.cy, m); take(&w.cz, n); take(&w.gc, n);
   take(&w.red_part, (long long)MAXRED * RED_PARTIALS); take(&w.scal, NSCAL);
-  if (p->fast) {
+  if (p->fast && p->tp <= 2) {
     const long long Pt = std::max(p->P, 1), T0 = std::max(p->t0, 1), tp = p->tp;
     take(&w.br, Pt * tp * 16); take(&w.bw, Pt * tp * 16); take(&w.bup, Pt * tp * 16);
     take(&w.bpb, Pt * T0 * 16); take(&w.bu0p, T0 * 16);
+  } else if (p->fast) {
+    // pairs of over 32 rows: the handle's own pair vectors, so that the solve
+    // needs no more of the static workspace than with the segmented chain
+    w.br = p->wide_r; w.bw = p->wide_w; w.bup = p->wide_up; w.bpb = p->wide_pb; w.bu0p = p->wide_u0p;
   }
   return off;
 }
@@ -1387,6 +1393,11 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
     CHK(M.alloc(&p->FLbi, (long long)std::max(p->t0 * p->t0, 1) * 256));
     set_bcr_smem_limits();
     CHK(M.alloc(&p->segout, 1));
+    if (p->tp > 2) {
+      for (double** v : {&p->wide_r, &p->wide_w, &p->wide_up}) CHK(M.alloc(v, Pt * tp * 16));
+      CHK(M.alloc(&p->wide_pb, Pt * T0 * 16));
+      CHK(M.alloc(&p->wide_u0p, T0 * 16));
+    }
   } else {
     CHK(M.alloc(&p->segout, (long long)std::max(p->G, 1) * SEG_STRIDE));
   }

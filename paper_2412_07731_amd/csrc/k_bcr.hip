@@ -1,6 +1,6 @@
 // Block cyclic reduction of the Schur complement (a6) for link pairs of at
-// most 16 rows and at most 64 linking variables (pairs of up to 32 rows:
-// k_bcr2.hip, which shares the border kernels below).
+// most 16 rows and at most 64 linking variables (wider pairs: k_bcrn.hip,
+// which shares the border kernels below).
 //
 // The assembled Schur complement is S = [T E; E' S00] with T block
 // tridiagonal over the P link pairs (App. A) and E, S00 the x_0 border.  T is
@@ -623,12 +623,12 @@ int tail_level(int P, int waves, int* n_out) {
 
 int bcr_tiles(int lmax, int n0) {
   if (n0 > 16 * BT_MAXT0) return 0;
-  return lmax <= 16 ? 1 : lmax <= 32 ? 2 : 0;
+  return lmax <= 16 ? 1 : (lmax + 15) / 16;
 }
 
 void launch_bcr_factor(hipStream_t st, const BcrArgs& c, int nparts, int chunk) {
-  if (c.tp == 2) {
-    launch_bcr2_reduce(st, c);
+  if (c.tp >= 2) {
+    launch_bcrn_reduce(st, c);
   } else if (c.P > 0) {
     const long long tiles = (long long)c.P * (2 + c.t0);
     hipLaunchKernelGGL(k_bcr_init, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st, c);
@@ -649,8 +649,8 @@ void launch_bcr_factor(hipStream_t st, const BcrArgs& c, int nparts, int chunk) 
 }
 
 void launch_bcr_solve(hipStream_t st, const BcrSolveArgs& a) {
-  if (a.c.tp == 2) {
-    launch_bcr2_solve(st, a);
+  if (a.c.tp >= 2) {
+    launch_bcrn_solve(st, a);
     return;
   }
   const int P = a.c.P;
@@ -671,7 +671,6 @@ void launch_bcr_solve(hipStream_t st, const BcrSolveArgs& a) {
 void set_bcr_smem_limits() {
   hipFuncSetAttribute((const void*)k_bcr_border, hipFuncAttributeMaxDynamicSharedMemorySize,
                       (int)border_smem(BT_MAXT0));
-  set_bcr2_smem_limits();
 }
 
 }  // namespace ahlp

@@ -101,7 +101,7 @@ constexpr int SEGRHS_STRIDE = 2 * LMAX + N0MAX;
 // n0 <= 64.  Tiles are 16x16 column-major, padded.
 struct BcrArgs {
   int P, n0, t0, ng;                              // n0: border width, ng of it global rows
-  int tp;                                         // tiles per pair side (1 or 2)
+  int tp;                                         // tiles per pair side (1 to 4)
   const int* l;
   const long long* tdoff;
   const long long* tooff;
@@ -123,7 +123,7 @@ struct BcrSolveArgs {
   double* pb;            // border partials Z_j' w_j, 16*t0 per pair
   double* u0p;           // border solution, 16*t0
 };
-// tiles per pair side of the cyclic-reduction path for these sizes (1 or 2),
+// tiles per pair side of the cyclic-reduction path for these sizes (1 to 4),
 // 0 if it does not apply
 int bcr_tiles(int lmax, int n0);
 void launch_bcr_factor(hipStream_t st, const BcrArgs& c, int nparts, int chunk);
@@ -134,11 +134,10 @@ void launch_ceiling_mfma(hipStream_t st, bool fp32, int grid, int iters, double*
 void launch_ceiling_read(hipStream_t st, const double* buf, long long n, int grid, double* out);
 // grid workgroups of one factoring wave (and four MFMA-streaming waves if beside)
 void launch_ceiling_chol(hipStream_t st, bool beside, int grid, int iters, double* out);
-// two-tile pairs (k_bcr2.hip): the reduction of T down to the final pair, and
+// pairs of two to four tiles (k_bcrn.hip): the reduction of T down to the final pair, and
 // the whole solve
-void launch_bcr2_reduce(hipStream_t st, const BcrArgs& c);
-void launch_bcr2_solve(hipStream_t st, const BcrSolveArgs& a);
-void set_bcr2_smem_limits();
+void launch_bcrn_reduce(hipStream_t st, const BcrArgs& c);
+void launch_bcrn_solve(hipStream_t st, const BcrSolveArgs& a);
 
 size_t chain_factor_smem(int lmax, int n0);
 void launch_chain_factor(hipStream_t st, const ChainArgs& c);
