@@ -323,8 +323,8 @@ ahlp_status_t ahlp_problem_set_launch(ahlp_problem_t p, int32_t mode);
  * tile-row count rt that the problem's blocks have and at least two kernels
  * can hold (rt <= 40): the panel kernel with four waves per block (panel
  * accumulators in registers, rt <= 24, two workgroups per CU), the panel
- * kernel with eight waves (rt <= 40, one per CU) or the column kernel (one
- * tile column at a time through LDS, any rt).  Without tuning, the first of
+ * kernel with eight waves (rt <= 40, one per CU) or the tall kernels, named
+ * "column" in the cache (a launch per four tile columns, any rt).  Without tuning, the first of
  * these that fits is used.  Entries for this GPU architecture found in the
  * text file cache_path (HOST string, may be NULL) are used as they are; every
  * other rt is measured on the problem's own blocks of that rt at x = z = 1

@@ -143,7 +143,7 @@ struct StageTimer {
 }  // namespace
 
 // Block-factor kernels (bf_kernel entries): the four-wave panel kernel, the
-// column-at-a-time kernel, the eight-wave panel kernel.
+// tall kernels (a launch per panel, any height), the eight-wave panel kernel.
 enum { BFK_PANEL = 0, BFK_COLUMN = 1, BFK_PANEL8 = 2 };
 
 // Segments of an interior-point iteration between host synchronizations:
@@ -206,9 +206,11 @@ struct ahlp_problem_s {
   int nsyrk = 0;
   // block-factor buckets: bf_order[0, n_panel) for the four-wave panel
   // kernel, then n_panel8 blocks for the eight-wave one, then n_col blocks
-  // for the column kernel, each largest first
+  // for the tall kernels, each largest first
   int* bf_order = nullptr;
-  int n_panel = 0, n_panel8 = 0, n_col = 0, rt_panel = 0, rt_panel8 = 0, rt_col = 0;
+  int n_panel = 0, n_panel8 = 0, n_col = 0, rt_panel = 0, rt_panel8 = 0, rt_col = 0, mt_col = 0;
+  double *tall_thr = nullptr, *tall_scratch = nullptr;   // of the tall kernels (tall_cap blocks)
+  int tall_cap = 0;
   // per-block launch mode (the reference the batched launches are compared
   // with): block i's SYRK items, link items, and its index in an identity list
   int launch_mode = AHLP_LAUNCH_BATCHED;
@@ -379,7 +381,7 @@ size_t solve_ws_layout(const ahlp_problem_s* p, double* base, SolveWs* ws) {
 // ------------------------------------------------------------- factor
 // Block-factor kernel for bordered tile-row count rt: the autotuned choice
 // (bf_kernel) or the default rule, the four-wave panel kernel where it fits,
-// else the eight-wave one, else the column kernel.
+// else the eight-wave one, else the tall kernels.
 int bf_choice(const ahlp_problem_s* p, int rt) {
   const int k = rt < (int)p->bf_kernel.size() ? p->bf_kernel[rt] : -1;
   if (k == BFK_PANEL && block_factor_panel_fits(rt)) return BFK_PANEL;
@@ -406,6 +408,7 @@ std::vector<int> bf_buckets(ahlp_problem_t p) {
   std::vector<int> out;
   int* cnt[3] = {&p->n_panel, &p->n_col, &p->n_panel8};
   int* rtm[3] = {&p->rt_panel, &p->rt_col, &p->rt_panel8};
+  p->mt_col = 0;
   for (int k : {BFK_PANEL, BFK_PANEL8, BFK_COLUMN}) {
     *cnt[k] = 0;
     *rtm[k] = 0;
@@ -414,9 +417,19 @@ std::vector<int> bf_buckets(ahlp_problem_t p) {
         out.push_back(i);
         ++*cnt[k];
         *rtm[k] = std::max(*rtm[k], p->hb[i].rt);
+        if (k == BFK_COLUMN) p->mt_col = std::max(p->mt_col, p->hb[i].mt);
       }
   }
   return out;
+}
+
+// Scratch of the tall kernels for n blocks.  An outgrown one stays until
+// destroy: a captured graph may hold it.
+ahlp_status_t ensure_tall(ahlp_problem_t p, int n) {
+  if (n <= p->tall_cap) return AHLP_OK;
+  CHK(p->mem.alloc(&p->tall_scratch, (long long)tall_scratch_doubles(n)));
+  p->tall_cap = n;
+  return AHLP_OK;
 }
 
 // Block-factor buckets into p->h_bf and bf_order, and the column bucket's
@@ -424,6 +437,7 @@ std::vector<int> bf_buckets(ahlp_problem_t p) {
 // captured graph holds the old ones, so the launch generation moves on.
 ahlp_status_t set_buckets(ahlp_problem_t p, hipStream_t st) {
   p->h_bf = bf_buckets(p);
+  CHK(ensure_tall(p, p->n_col));
   std::vector<int4> cs;
   std::vector<int2> cl;
   for (int k = p->n_panel; k < p->N; ++k) {
@@ -448,6 +462,14 @@ ahlp_status_t set_buckets(ahlp_problem_t p, hipStream_t st) {
   return AHLP_OK;
 }
 
+// The tall kernels for n blocks (their scratch is there: set_buckets, ahlp_autotune).
+template <typename T>
+void factor_tall(ahlp_problem_t p, hipStream_t st, const int* order, int n, int mt, int rt, T* LB,
+                 T* LINV) {
+  launch_block_factor_tall<T>(st, p->blk, order, n, mt, rt, p->max_kt, LB, LINV, p->PQ, p->tall_thr,
+                              p->tall_scratch, p->info, p->num_cu);
+}
+
 // The same kernels, one launch per block and stage, in block order on st:
 // the reference for the batched launches (identical arithmetic per block).
 template <typename T>
@@ -465,7 +487,7 @@ ahlp_status_t factor_blocks_per_block(ahlp_problem_t p, hipStream_t st, T* LB, T
   for (int i = 0; i < p->N; ++i) {
     const int rt = p->hb[i].rt, k = bf_choice(p, rt);
     if (k == BFK_COLUMN)
-      launch_block_factor_col<T>(st, p->blk, p->ident + i, 1, rt, LB, LINV, p->PQ, p->info);
+      factor_tall<T>(p, st, p->ident + i, 1, p->hb[i].mt, rt, LB, LINV);
     else
       launch_block_factor_panel<T>(st, p->blk, p->ident + i, 1, rt, LB, LINV, p->PQ, p->info,
                                    k == BFK_PANEL8 ? 8 : 4, p->max_kt);
@@ -491,8 +513,8 @@ ahlp_status_t factor_blocks_fused(ahlp_problem_t p, hipStream_t st, T* LB, T* LI
     launch_syrk<T>(p->side, p->blk, p->col_syrk_items, p->ncol_syrk, A, p->Dp, LB, p->delta);
     launch_block_factor_panel<T>(p->side, p->blk, p->bf_order + p->n_panel, p->n_panel8,
                                  p->rt_panel8, LB, LINV, p->PQ, p->info, 8, p->max_kt);
-    launch_block_factor_col<T>(p->side, p->blk, p->bf_order + p->n_panel + p->n_panel8, p->n_col,
-                               p->rt_col, LB, LINV, p->PQ, p->info);
+    factor_tall<T>(p, p->side, p->bf_order + p->n_panel + p->n_panel8, p->n_col, p->mt_col,
+                   p->rt_col, LB, LINV);
     HIPCHK(hipEventRecord(p->ev_join, p->side));
   }
   launch_factor_fused<T>(st, p->blk, p->bf_order, p->n_panel, p->rt_panel, p->fused_queue, p->nb,
@@ -529,7 +551,7 @@ ahlp_status_t factor_blocks(ahlp_problem_t p, hipStream_t st, T* LB, T* LINV, co
     HIPCHK(hipStreamWaitEvent(p->side, p->ev_fork, 0));
     launch_block_factor_panel<T>(p->side, p->blk, o8, nb8, p->rt_panel8, LB, LINV, p->PQ, p->info, 8,
                                  p->max_kt);
-    launch_block_factor_col<T>(p->side, p->blk, oc, nbc, p->rt_col, LB, LINV, p->PQ, p->info);
+    factor_tall<T>(p, p->side, oc, nbc, p->mt_col, p->rt_col, LB, LINV);
     HIPCHK(hipEventRecord(p->ev_join, p->side));
     launch_block_factor_panel<T>(st, p->blk, p->bf_order, p->n_panel, p->rt_panel, LB, LINV, p->PQ,
                                  p->info, 4, p->max_kt);
@@ -539,7 +561,7 @@ ahlp_status_t factor_blocks(ahlp_problem_t p, hipStream_t st, T* LB, T* LINV, co
                                  p->info, 4, p->max_kt);
     launch_block_factor_panel<T>(st, p->blk, o8, nb8, p->rt_panel8, LB, LINV, p->PQ, p->info, 8,
                                  p->max_kt);
-    launch_block_factor_col<T>(st, p->blk, oc, nbc, p->rt_col, LB, LINV, p->PQ, p->info);
+    factor_tall<T>(p, st, oc, nbc, p->mt_col, p->rt_col, LB, LINV);
   }
   p->timer.end();
   HIPCHK(hipGetLastError());
@@ -1044,8 +1066,8 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
     p->max_rt = std::max(p->max_rt, b.rt);
     p->max_kt = std::max(p->max_kt, b.kt);
   }
-  // the column-at-a-time block factor keeps a bordered block's whole tile
-  // column in LDS: (rt + 1) padded 16 x 17 tiles
+  // bordered blocks are bounded by what a tile column of (rt + 1) padded 16 x
+  // 17 tiles takes of the LDS
   {
     const size_t col_sh = (size_t)(p->max_rt + 1) * 16 * 17 * sizeof(double);
     if (col_sh > (size_t)dev_lds)
@@ -1232,7 +1254,7 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   // Uneven blocks: SYRK work goes largest block first, dealt round-robin into
   // eight chunks (the SYRK kernel gives each XCD a contiguous stretch of the
   // list, so every XCD gets a similar mix); the block factor runs two buckets
-  // (panel kernel where the bordered block fits, column kernel otherwise),
+  // (panel kernel where the bordered block fits, tall kernels otherwise),
   // each largest first.
   std::vector<int> bysize(N);
   for (int i = 0; i < N; ++i) bysize[i] = i;
@@ -1335,6 +1357,7 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   CHK(M.alloc(&p->col_link_items, std::max(p->nlink, 1)));
   CHK(M.alloc(&p->fused_queue, 1));
   CHK(M.alloc(&p->bf_order, N));
+  CHK(M.alloc(&p->tall_thr, N));
   CHK(M.alloc(&p->ident, N));
   CHK(M.alloc(&p->link_items, std::max(p->nlink, 1)));
   CHK(M.alloc(&p->rowtiles, p->nrt));
@@ -1689,6 +1712,7 @@ ahlp_status_t ahlp_autotune(ahlp_problem_t p, const char* cache_path, int32_t* m
       hblk.clear();
       for (int i = 0; i < p->N; ++i)
         if (p->hb[i].rt == rt) hblk.push_back(i);
+      CHK(ensure_tall(p, (int)hblk.size()));
       HIPCHK(hipMemcpyAsync(p->bf_order, hblk.data(), sizeof(int) * hblk.size(), hipMemcpyHostToDevice, st));
       double best[3] = {1e30, 1e30, 1e30};
       const bool can[3] = {block_factor_panel_fits(rt), true, block_factor_panel8_fits(rt)};
@@ -1700,8 +1724,7 @@ ahlp_status_t ahlp_autotune(ahlp_problem_t p, const char* cache_path, int32_t* m
           launch_syrk<double>(st, p->blk, p->syrk_items, p->nsyrk, p->A, p->Dp, p->LB, delta);
           HIPCHK(hipEventRecord(e0, st));
           if (k == BFK_COLUMN)
-            launch_block_factor_col<double>(st, p->blk, p->bf_order, (int)hblk.size(), rt, p->LB,
-                                            p->LINV, p->PQ, p->info);
+            factor_tall<double>(p, st, p->bf_order, (int)hblk.size(), rt, rt, p->LB, p->LINV);
           else
             launch_block_factor_panel<double>(st, p->blk, p->bf_order, (int)hblk.size(), rt, p->LB,
                                               p->LINV, p->PQ, p->info, k == BFK_PANEL8 ? 8 : 4,

@@ -304,75 +304,270 @@ __global__ __launch_bounds__(256) void k_link(const BlockInfo* __restrict__ blk,
 }
 
 // ---------------------------------------------------------------- a3 + a4
-// One workgroup per block: left-looking blocked Cholesky over the mt tile
-// columns of the bordered matrix.  Column panel p is first updated with the
-// finished columns (MFMA, A operand = L(r,q), B operand = L(p,q)'), its
-// diagonal tile is factored and inverted by one wave, and the tiles below are
-// multiplied by the inverse's transpose (MFMA).  The inverted diagonal tiles
-// are kept for the solve phase.
+// Tall bordered blocks (more tile rows than the panel kernels hold): left-
+// looking over panels of TALL_W tile columns, one launch per panel, several
+// workgroups per block.  Every workgroup of a block updates and factors the
+// panel's diagonal block for itself (the same arithmetic, so the same values)
+// and takes eight of the tile rows below, one per wave, through the update by
+// the earlier columns and the solve with the diagonal block.  A tile column of
+// the panel (TALL_W tiles) is shared by the eight waves through LDS, staged two
+// columns ahead by direct-to-LDS loads; a row's own tile comes straight to
+// registers.  Rows are kept transposed in the accumulators, where a tile of X'
+// is laid out as the next product's B operand, so the solve stays in
+// registers.  With few tall blocks the chain of a block is what bounds a
+// factorization; one workgroup per block and one tile column at a time (the
+// form this replaces) left 208 of 256 CUs idle: 48 blocks of 600-900 rows took
+// 4.67 ms, now 1.10 ms in 16 launches, which the MFMA work of the CUs with two
+// workgroups bounds (three times the balanced 0.35 ms).
+//
+// The diagonal block's factor must not overwrite its input while other
+// workgroups of the launch may still read it: it goes to a scratch slot of the
+// block (two slots, alternating) and the next launch's first workgroup copies
+// it into place.  Columns < c0 of the factor's diagonal tiles are read by
+// nobody until then.
+constexpr int TALL_W = 4, TALL_NW = 8, TALL_ND = TALL_W * (TALL_W + 1) / 2;
+constexpr int TALL_KS = 2;   // tile columns per stage (c0 is a multiple of it)
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_block_factor(const BlockInfo* __restrict__ blk,
-                                                      const int* __restrict__ order,
-                                                      T* __restrict__ LB, T* __restrict__ LINV,
-                                                      DevInfo* info) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const BlockInfo b = blk[order[blockIdx.x]];
-  // LDS tiles with leading dimension 17 (see the panel kernel)
+__global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
+    const BlockInfo* __restrict__ blk, const int* __restrict__ order, T* LB,
+    T* __restrict__ LINV, double* __restrict__ bthr, T* __restrict__ scratch, DevInfo* info,
+    int c0) {
   constexpr int LD = TS + 1, TEP = TS * LD, AST = sizeof(T) == 8 ? 4 : 1;
-  T* panel = reinterpret_cast<T*>(smem_raw);
-  T* linv = panel + (size_t)b.rt * TEP;
-  __shared__ double s_max[4];
-  __shared__ T xbuf[48];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   typedef typename Acc<T>::type AT;
-  const int wb = (lane & 15) * LD + (sizeof(T) == 8 ? (lane >> 4) : 4 * (lane >> 4));
-  const int rb = lane + (lane >> 4), tb = tid + (tid >> 4);
+  __shared__ __align__(16) T stg0[TALL_KS * TALL_W * TE], stg1[TALL_KS * TALL_W * TE];
+  __shared__ T Bd[TALL_ND * TEP];    // diagonal block: lower tiles (r, c) at r (r + 1) / 2 + c
+  __shared__ T Ld[TALL_W * TEP];     // inverted diagonal tiles
+  __shared__ double s_max[TALL_NW];
+  const BlockInfo b = blk[order[blockIdx.y]];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  T* slot = scratch + (long long)blockIdx.y * 2 * TALL_ND * TE;
+  auto tl = [](int r, int c) { return r * (r + 1) / 2 + c; };
+  // the previous panel's diagonal factor into place
+  if (c0 > 0 && blockIdx.x == 0 && c0 - TALL_W < b.mt) {
+    const int p0 = c0 - TALL_W, pw0 = min(TALL_W, b.mt - p0);
+    const T* src = slot + (((c0 / TALL_W) - 1) & 1) * TALL_ND * TE;
+    int r = 0, c = 0;
+    for (int u = 0; u < TALL_ND && r < pw0; ++u) {
+      if (u % TALL_NW == w) tile_copy_t(LB + lb_tile(b, p0 + r, p0 + c), src + (long long)u * TE);
+      if (++c > r) { ++r; c = 0; }
+    }
+  }
+  if (c0 >= b.mt) return;
+  const int pw = min(TALL_W, b.mt - c0), r0 = c0 + pw, nrow = b.rt - r0;
+  if (blockIdx.x > 0 && (int)blockIdx.x * TALL_NW >= nrow) return;
 
   // pivot threshold from the largest real diagonal entry of M_i
-  double md = 0.0;
-  for (int idx = tid; idx < b.m; idx += blockDim.x) {
-    const int p = idx >> 4, i = idx & 15;
-    md = fmax(md, (double)LB[lb_tile(b, p, p) + i * 17]);
+  double thr;
+  if (c0 == 0) {
+    double md = 0.0;
+    for (int idx = tid; idx < b.m; idx += 64 * TALL_NW) {
+      const int p = idx >> 4, i = idx & 15;
+      md = fmax(md, (double)LB[lb_tile(b, p, p) + i * 17]);
+    }
+    for (int off = 32; off > 0; off >>= 1) md = fmax(md, __shfl_xor(md, off));
+    if (lane == 0) s_max[w] = md;
+    __syncthreads();
+    md = 0.0;
+    for (int k = 0; k < TALL_NW; ++k) md = fmax(md, s_max[k]);
+    thr = PIVOT_REL * md;
+    if (tid == 0 && blockIdx.x == 0) bthr[order[blockIdx.y]] = thr;
+  } else {
+    thr = bthr[order[blockIdx.y]];
   }
-  for (int off = 32; off > 0; off >>= 1) md = fmax(md, __shfl_xor(md, off));
-  if (lane == 0) s_max[wave] = md;
-  __syncthreads();
-  const double thr = PIVOT_REL * fmax(fmax(fmax(s_max[0], s_max[1]), fmax(s_max[2], s_max[3])), 0.0);
-  int cnt = 0;
 
-  for (int p = 0; p < b.mt; ++p) {
-    for (int r = p + wave; r < b.rt; r += 4) {
-      AT acc;
-      const T* src = LB + lb_tile(b, r, p);
+  // stage tile columns k .. k + TALL_KS - 1 of the panel rows c0 + i: 16 bytes
+  // per thread and load, tile t = kk * TALL_W + i (rows past the block's last
+  // tile column read the last one again)
+  constexpr int E = 16 / sizeof(T), PER = 64 * TALL_NW * E, NL = TALL_KS * TALL_W * TE / PER;
+  static_assert(NL * PER == TALL_KS * TALL_W * TE, "a stage is whole loads");
+  auto stage = [&](T* dst, int k) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] = src[acc_index<T>(lane, k)];
-      for (int q = 0; q < p; ++q) {
-        const T* X = LB + lb_tile(b, r, q);
-        const T* Y = LB + lb_tile(b, p, q);
+    for (int j = 0; j < NL; ++j) {
+      const int f = (tid + 64 * TALL_NW * j) * E, f0 = (64 * w + 64 * TALL_NW * j) * E;
+      const int t = f / TE, i = min(c0 + t % TALL_W, b.mt - 1);
+      __builtin_amdgcn_global_load_lds((const void*)(LB + lb_tile(b, i, k + t / TALL_W) + f % TE),
+                                       (__attribute__((address_space(3))) void*)(dst + f0), 16, 0, 0);
+    }
+  };
+  // element s of this lane's slice of a stored tile as an operand: plain
+  // (inner index 4 s + lane / 16) and, for products with accumulator
+  // registers, with the inner index in accumulator order
+  const int wb = (lane & 15) * LD + (sizeof(T) == 8 ? (lane >> 4) : 4 * (lane >> 4));
+  int cnt = 0;
+  bool first = true;
+  for (int rb = (int)blockIdx.x * TALL_NW; first || rb < nrow; rb += (int)gridDim.x * TALL_NW) {
+    const int r = r0 + rb + w;
+    const bool row = rb + w < nrow;
+    const int rc = min(r, b.rt - 1);
+    // this wave's row of the panel, transposed, and its diagonal tiles
+    AT acc[TALL_W], da[2];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) acc = mfma(-X[64 * s + lane], Y[64 * s + lane], acc);
+    for (int j = 0; j < TALL_W; ++j) {
+      acc[j] = AT{0, 0, 0, 0};
+      if (row && j < pw)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          acc[j][k] = LB[lb_tile(b, r, c0 + j) + acc_row<T>(lane, k) * TS + (lane & 15)];
+    }
+    int dr[2], dc[2];
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const int u = w + TALL_NW * d;
+      dr[d] = 0;
+      while ((dr[d] + 1) * (dr[d] + 2) / 2 <= u) ++dr[d];
+      dc[d] = u - dr[d] * (dr[d] + 1) / 2;
+      da[d] = AT{0, 0, 0, 0};
+      if (first && dr[d] < pw) {
+        const T* src = LB + lb_tile(b, c0 + dr[d], c0 + dc[d]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) da[d][k] = src[acc_index<T>(lane, k)];
       }
-      T* dst = panel + (size_t)(r - p) * TEP;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) dst[wb + AST * k] = acc[k];
     }
-    __syncthreads();
-    if (wave == 0) cnt += wave_chol_tile<T, LD>(panel, panel, linv, thr, xbuf);
-    __syncthreads();
-    LB[lb_tile(b, p, p) + tid] = panel[tb];
-    LINV[b.linvoff + (long long)p * TE + tid] = linv[tb];
-    for (int r = p + 1 + wave; r < b.rt; r += 4) {
-      AT acc = AT{0, 0, 0, 0};
-      const T* X = panel + (size_t)(r - p) * TEP;
+    T own[TALL_KS][4], nxt[TALL_KS][4];
+    auto load_own = [&](T (*o)[4], int k) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) acc = mfma(X[rb + 68 * s], linv[rb + 68 * s], acc);
-      T* dst = LB + lb_tile(b, r, p);
+      for (int kk = 0; kk < TALL_KS; ++kk) {
+        const T* t = LB + lb_tile(b, rc, k + kk);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) dst[acc_index<T>(lane, k)] = acc[k];
+        for (int s = 0; s < 4; ++s) o[kk][s] = t[64 * s + lane];
+      }
+    };
+    auto step = [&](const T* cur, T* next, int k) {
+      // this wave's direct-to-LDS loads of the stage are in LDS before the
+      // barrier, and so every wave's after it
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+      __syncthreads();
+      const int kn = min(k + TALL_KS, c0 - TALL_KS);   // the last step requests its own tiles again
+      stage(next, kn);
+      load_own(nxt, kn);
+#pragma unroll
+      for (int kk = 0; kk < TALL_KS; ++kk) {
+        const T* P = cur + kk * TALL_W * TE;
+        if (row) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int j = 0; j < TALL_W; ++j)
+              acc[j] = mfma(-P[j * TE + 64 * s + lane], own[kk][s], acc[j]);
+        }
+        if (first) {
+#pragma unroll
+          for (int d = 0; d < 2; ++d)
+            if (dr[d] < pw) {
+              const T* X = P + dr[d] * TE;
+              const T* Y = P + dc[d] * TE;
+#pragma unroll
+              for (int s = 0; s < 4; ++s) da[d] = mfma(-X[64 * s + lane], Y[64 * s + lane], da[d]);
+            }
+        }
+      }
+#pragma unroll
+      for (int kk = 0; kk < TALL_KS; ++kk)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) own[kk][s] = nxt[kk][s];
+    };
+    if (c0 > 0) {
+      stage(stg0, 0);
+      load_own(own, 0);
+      for (int k = 0; k < c0; k += 2 * TALL_KS) {   // c0 is a multiple of TALL_W = 2 TALL_KS
+        step(stg0, stg1, k);
+        step(stg1, stg0, k + TALL_KS);
+      }
+      // the extra stage requested by the last step has landed before the
+      // buffers are used again or the workgroup ends
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
     }
-    __syncthreads();
+    if (first) {
+      // factor the diagonal block: wave 0 the diagonal tiles, the others the
+      // tile column below and the trailing tiles
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+        if (dr[d] < pw) {
+          T* t = Bd + tl(dr[d], dc[d]) * TEP;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) t[wb + AST * k] = da[d][k];
+        }
+      __syncthreads();
+      const int rbp = lane + (lane >> 4);   // operand element s of a padded tile at rbp + 68 s
+      for (int p = 0; p < pw; ++p) {
+        T* D = Bd + tl(p, p) * TEP;
+        if (w == 0) cnt += wave_chol_tile<T, LD>(D, D, Ld + p * TEP, thr, nullptr);
+        __syncthreads();
+        if (p + 1 == pw) break;
+        if (w >= 1 && w < pw - p) {
+          T* X = Bd + tl(p + w, p) * TEP;
+          AT a = AT{0, 0, 0, 0};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) a = mfma(X[rbp + 68 * s], Ld[p * TEP + rbp + 68 * s], a);
+          wave_order();
+#pragma unroll
+          for (int k = 0; k < 4; ++k) X[wb + AST * k] = a[k];
+        }
+        __syncthreads();
+        // trailing tiles, the next diagonal tile by wave 0
+        int u = 0;
+        for (int rr = p + 1; rr < pw; ++rr)
+          for (int cc = p + 1; cc <= rr; ++cc, ++u)
+            if (u % TALL_NW == w) {
+              T* t = Bd + tl(rr, cc) * TEP;
+              const T* X = Bd + tl(rr, p) * TEP;
+              const T* Y = Bd + tl(cc, p) * TEP;
+              AT a;
+#pragma unroll
+              for (int k = 0; k < 4; ++k) a[k] = t[wb + AST * k];
+#pragma unroll
+              for (int s = 0; s < 4; ++s) a = mfma(-X[rbp + 68 * s], Y[rbp + 68 * s], a);
+              wave_order();
+#pragma unroll
+              for (int k = 0; k < 4; ++k) t[wb + AST * k] = a[k];
+            }
+        wave_order();
+      }
+      if (blockIdx.x == 0) {
+        // L_pp to the scratch slot (see above), the inverted tiles in place
+        T* dst = slot + ((c0 / TALL_W) & 1) * TALL_ND * TE;
+        int rr = 0, cc = 0;
+        for (int u = 0; u < TALL_ND && rr < pw; ++u) {
+          if (u % TALL_NW == w)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) dst[(long long)u * TE + 64 * s + lane] = Bd[u * TEP + rbp + 68 * s];
+          if (++cc > rr) { ++rr; cc = 0; }
+        }
+        if (w < pw)
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            LINV[b.linvoff + (long long)(c0 + w) * TE + 64 * s + lane] = Ld[w * TEP + rbp + 68 * s];
+      }
+    }
+    // X_j' = L_jj^-1 (acc_j' - sum_q L_jq X_q'), the inner index in
+    // accumulator order
+    if (row) {
+#pragma unroll
+      for (int j = 0; j < TALL_W; ++j) {
+        if (j >= pw) break;
+#pragma unroll
+        for (int q = 0; q < j; ++q) {
+          const T* X = Bd + tl(j, q) * TEP;
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            acc[j] = mfma(-X[acc_row<T>(lane, s) * LD + (lane & 15)], acc[q][s], acc[j]);
+        }
+        AT x = AT{0, 0, 0, 0};
+        const T* I = Ld + j * TEP;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x = mfma(I[acc_row<T>(lane, s) * LD + (lane & 15)], acc[j][s], x);
+        acc[j] = x;
+        T* dst = LB + lb_tile(b, r, c0 + j);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dst[acc_row<T>(lane, k) * TS + (lane & 15)] = x[k];
+      }
+    }
+    first = false;
   }
-  if (tid == 0 && cnt) atomicAdd(&info->pivots, cnt);
+  if (tid == 0 && blockIdx.x == 0 && cnt) atomicAdd(&info->pivots, cnt);
 }
 
 // Schur contribution of block i: PQ = F D F' - X X' with X = W_i' (the
@@ -1180,15 +1375,35 @@ __global__ __launch_bounds__(512, 1) void k_factor_fused(
 }
 
 // ---------------------------------------------------------------- a5
-// Schur contribution of block i: PQ = F D F' - X X' with X = W_i' (the
-// bordered rows of the factor), in FP64 whatever the factor precision.
+// Schur contribution of the tall blocks: one wave per tile (rr, cc), the same
+// products in the same order as schur_rows (with one workgroup per block it
+// took 99 us on 48 tall blocks).
 template <typename T>
 __global__ __launch_bounds__(256) void k_schur_contrib(const BlockInfo* __restrict__ blk,
                                                        const int* __restrict__ order,
                                                        const T* __restrict__ LB,
                                                        double* __restrict__ PQ) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  schur_rows<T>(blk[order[blockIdx.x]], LB, PQ, __builtin_amdgcn_readfirstlane(tid >> 6), lane);
+  const BlockInfo b = blk[order[blockIdx.y]];
+  const int lane = threadIdx.x & 63;
+  const int u = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  int rr = 0;
+  while ((rr + 1) * (rr + 2) / 2 <= u) ++rr;
+  const int cc = u - rr * (rr + 1) / 2;
+  if (rr >= b.kt) return;
+  double* dst = PQ + pq_tile(b, rr, cc);
+  d4 acc;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) acc[k] = dst[acc_index<double>(lane, k)];
+#pragma unroll 4
+  for (int q = 0; q < b.mt; ++q) {
+    const T* X = LB + lb_tile(b, b.mt + rr, q);
+    const T* Y = LB + lb_tile(b, b.mt + cc, q);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      acc = mfma(-(double)X[64 * s + lane], (double)Y[64 * s + lane], acc);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) dst[acc_index<double>(lane, k)] = acc[k];
 }
 
 // Element (q, q2) of block i's symmetric contribution (lower tiles stored).
@@ -1398,25 +1613,40 @@ template void launch_factor_fused<float>(hipStream_t, const BlockInfo*, const in
                                          float*, float*, double*, double, DevInfo*, int);
 bool factor_fused_fits(int rt, int mt) { return rt <= 4 * BF_RMAX_MAX && mt <= 2 * FUSED_MTP; }
 
-// Column-at-a-time kernel (any height), then the Schur contributions.
+// Tall blocks (any height): one launch per panel, the last panel's diagonal
+// factors copied into place by one more, then the Schur contributions.  A
+// block gets enough workgroups for one tile row per wave as long as the launch
+// stays within the two workgroups that fit a CU.
 template <typename T>
-void launch_block_factor_col(hipStream_t st, const BlockInfo* blk, const int* order, int n,
-                             int max_rt, T* LB, T* LINV, double* PQ, DevInfo* info) {
+void launch_block_factor_tall(hipStream_t st, const BlockInfo* blk, const int* order, int n,
+                              int max_mt, int max_rt, int max_kt, T* LB, T* LINV, double* PQ,
+                              double* bthr, double* scratch, DevInfo* info, int num_cu) {
   if (n == 0) return;
-  const size_t shmem = (size_t)(max_rt + 1) * TS * (TS + 1) * sizeof(T);   // padded tiles
-  hipLaunchKernelGGL(k_block_factor<T>, dim3(n), dim3(256), shmem, st, blk, order, LB, LINV, info);
-  hipLaunchKernelGGL(k_schur_contrib<T>, dim3(n), dim3(256), 0, st, blk, order, LB, PQ);
+  for (int c0 = 0;; c0 += TALL_W) {
+    const int rows = max_rt - std::min(c0 + TALL_W, max_mt);
+    const int g = c0 >= max_mt ? 1 : std::max(1, std::min((rows + TALL_NW - 1) / TALL_NW,
+                                                           std::max(1, 2 * num_cu / n)));
+    hipLaunchKernelGGL(k_tall_panel<T>, dim3(g, n), dim3(64 * TALL_NW), 0, st, blk, order, LB, LINV,
+                       bthr, reinterpret_cast<T*>(scratch), info, c0);
+    if (c0 >= max_mt) break;
+  }
+  if (max_kt > 0)
+    hipLaunchKernelGGL(k_schur_contrib<T>, dim3((max_kt * (max_kt + 1) / 2 + 3) / 4, n), dim3(256), 0,
+                       st, blk, order, LB, PQ);
 }
+size_t tall_scratch_doubles(int n) { return (size_t)n * 2 * TALL_ND * TE; }
 bool block_factor_panel_fits(int rt) { return rt <= 4 * BF_RMAX_MAX; }
 bool block_factor_panel8_fits(int rt) { return rt <= 8 * 5; }
 template void launch_block_factor_panel<double>(hipStream_t, const BlockInfo*, const int*, int, int,
                                                 double*, double*, double*, DevInfo*, int, int);
 template void launch_block_factor_panel<float>(hipStream_t, const BlockInfo*, const int*, int, int,
                                                float*, float*, double*, DevInfo*, int, int);
-template void launch_block_factor_col<double>(hipStream_t, const BlockInfo*, const int*, int, int,
-                                              double*, double*, double*, DevInfo*);
-template void launch_block_factor_col<float>(hipStream_t, const BlockInfo*, const int*, int, int,
-                                             float*, float*, double*, DevInfo*);
+template void launch_block_factor_tall<double>(hipStream_t, const BlockInfo*, const int*, int, int,
+                                               int, int, double*, double*, double*, double*,
+                                               double*, DevInfo*, int);
+template void launch_block_factor_tall<float>(hipStream_t, const BlockInfo*, const int*, int, int,
+                                              int, int, float*, float*, double*, double*, double*,
+                                              DevInfo*, int);
 
 void launch_assemble(hipStream_t st, const BlockInfo* blk, int N, int nb, int n0, long long nl,
                      const int* lsz, const long long* tdoff, const long long* tooff,

@@ -21,7 +21,7 @@ void launch_link(hipStream_t st, const BlockInfo* blk, const int2* items, int ni
 // Block factorization of the blocks order[0..n) (bordered Cholesky giving L_i
 // and W_i', then the FP64 Schur contributions PQ): the panel kernel for
 // blocks whose bordered tile rows fit (block_factor_panel_fits), the
-// column-at-a-time kernel plus a product pass for any height.  max_rt: the
+// tall kernels plus a product pass for any height.  max_rt: the
 // largest bordered tile-row count among the n blocks; max_kt (if >= 0) an
 // upper bound on their link-column tile counts, which sizes the LDS for the
 // Schur contribution.
@@ -29,9 +29,13 @@ template <typename T>
 void launch_block_factor_panel(hipStream_t st, const BlockInfo* blk, const int* order, int n,
                                int max_rt, T* LB, T* LINV, double* PQ, DevInfo* info,
                                int waves = 4, int max_kt = -1);
+// bthr: one double per block of the problem; scratch: tall_scratch_doubles(n);
+// max_mt, max_rt, max_kt: the largest tile counts among the n blocks
 template <typename T>
-void launch_block_factor_col(hipStream_t st, const BlockInfo* blk, const int* order, int n,
-                             int max_rt, T* LB, T* LINV, double* PQ, DevInfo* info);
+void launch_block_factor_tall(hipStream_t st, const BlockInfo* blk, const int* order, int n,
+                              int max_mt, int max_rt, int max_kt, T* LB, T* LINV, double* PQ,
+                              double* bthr, double* scratch, DevInfo* info, int num_cu);
+size_t tall_scratch_doubles(int n);
 bool block_factor_panel_fits(int rt);    // the four-wave form
 bool block_factor_panel8_fits(int rt);   // the eight-wave form
 // a1-a5 for the panel bucket in one persistent launch (link columns, SYRK,
