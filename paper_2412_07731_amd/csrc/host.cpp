@@ -232,6 +232,9 @@ struct ahlp_problem_s {
   int* ident = nullptr;
   int2* link_items = nullptr;
   int nlink = 0;
+  // compressed copy of the blocks for the row and column passes (when it pays)
+  bool sparse = false;
+  SpMat sp{};
   int2 *rowtiles = nullptr, *coltiles = nullptr, *c0tiles = nullptr;
   int nrt = 0, nct = 0, nc0 = 0;
   int* d_l = nullptr;
@@ -707,7 +710,8 @@ void link_global_rows(ahlp_problem_t p, const double* xp, const double* x0, cons
 // each output written (real sizes, not the tile padding).
 void rows_pass(ahlp_problem_t p, const RowsArgs& ra, hipStream_t st) {
   p->timer.begin(AHLP_ST_AROWS);
-  launch_rows_multi(st, p->blk, p->rowtiles, p->nrt, p->A, p->C, p->d0off, ra);
+  if (p->sparse) launch_sp_rows(st, p->blk, p->sp, p->d0off, ra);
+  else launch_rows_multi(st, p->blk, p->rowtiles, p->nrt, p->A, p->C, p->d0off, ra);
   p->timer.end();
   if (p->timer.records(AHLP_ST_AROWS)) {
     bool anyC = false;
@@ -728,6 +732,22 @@ void rows_pass1(ahlp_problem_t p, const double* v, const double* base, double al
   ra.v[0] = v; ra.base[0] = base; ra.alpha[0] = alpha; ra.out[0] = out;
   ra.with_C[0] = with_C; ra.padded[0] = padded;
   rows_pass(p, ra, st);
+}
+
+// The column pass g = A_i' yp + F_i' yL and the per-block partials C_i' yp
+// (k_cols' modes and outputs).
+void cols_pass(ahlp_problem_t p, const double* yp, const double* yL, int mode, const double* cvec,
+               const double* zvec, double* gout, double* out, hipStream_t st,
+               const DzArgs& dzv = DzArgs{}) {
+  if (p->sparse) {
+    launch_sp_cols(st, p->blk, p->sp, yp,
+                   ColsArgs{yL, p->cptr, p->crow, p->cval, mode, p->n0, cvec, zvec, p->Dp, gout, out,
+                            p->ws.part, dzv});
+    return;
+  }
+  launch_cols(st, p->blk, p->coltiles, p->nct, p->A, yp, yL, p->cptr, p->crow, p->cval, mode, cvec,
+              zvec, p->Dp, gout, out, dzv);
+  launch_ccols(st, p->blk, p->c0tiles, p->nc0, p->n0, p->C, yp, p->ws.part);
 }
 
 // tpre: precomputed t = r_y + A D rhx (padded v-space) or null; gout receives
@@ -765,9 +785,7 @@ ahlp_status_t solve_once(ahlp_problem_t p, const double* rx, const double* ry, c
   else solve_blocks_bwd<double>(p, st, p->LB, p->LINV, dy);
   // dx_i = D_i (A_i' dy_i + F_i' dy_L - rhx_i), dz = (rz - Z dx) / X;  g = A' dy
   const DzArgs dzv{rz, p->zs, p->xs, dz};
-  launch_cols(st, p->blk, p->coltiles, p->nct, p->A, p->ws.dyp, p->ws.u, p->cptr, p->crow, p->cval, 2,
-              p->ws.rhx, nullptr, p->Dp, gout, dx, dzv);
-  launch_ccols(st, p->blk, p->c0tiles, p->nc0, p->n0, p->C, p->ws.dyp, p->ws.part);
+  cols_pass(p, p->ws.dyp, p->ws.u, 2, p->ws.rhx, nullptr, gout, dx, st, dzv);
   launch_solve_tail(st, p->N, p->n0, p->nle, p->f0first, p->ws.part, p->F0, p->ws.u, p->x0off, p->mblk, gout, dx, dzv,
                     dy);
   p->timer.end();
@@ -779,10 +797,8 @@ ahlp_status_t solve_once(ahlp_problem_t p, const double* rx, const double* ry, c
 void apply_At(ahlp_problem_t p, const double* y, int mode, const double* cvec,
               const double* zvec, double* out, hipStream_t st) {
   launch_pad_y(st, p->blk, p->N, y, p->ws.dyp);
-  launch_cols(st, p->blk, p->coltiles, p->nct, p->A, p->ws.dyp, y + p->mblk, p->cptr, p->crow,
-              p->cval, mode, cvec, zvec, p->Dp, mode == 0 ? out : nullptr,
-              mode == 0 ? nullptr : out);
-  launch_ccols(st, p->blk, p->c0tiles, p->nc0, p->n0, p->C, p->ws.dyp, p->ws.part);
+  cols_pass(p, p->ws.dyp, y + p->mblk, mode, cvec, zvec, mode == 0 ? out : nullptr,
+            mode == 0 ? nullptr : out, st);
   launch_x0_sum(st, p->N, p->n0, p->nle, p->f0first, p->ws.part, p->F0, y + p->mblk, mode, cvec, zvec, p->x0off,
                 mode == 0 ? out : nullptr, mode == 0 ? nullptr : out);
 }
@@ -791,9 +807,7 @@ void apply_At(ahlp_problem_t p, const double* y, int mode, const double* cvec,
 void apply_At_both(ahlp_problem_t p, const double* y, const double* cvec, const double* zvec,
                    double* rd, double* gout, hipStream_t st) {
   launch_pad_y(st, p->blk, p->N, y, p->ws.dyp);
-  launch_cols(st, p->blk, p->coltiles, p->nct, p->A, p->ws.dyp, y + p->mblk, p->cptr, p->crow,
-              p->cval, 1, cvec, zvec, p->Dp, gout, rd);
-  launch_ccols(st, p->blk, p->c0tiles, p->nc0, p->n0, p->C, p->ws.dyp, p->ws.part);
+  cols_pass(p, p->ws.dyp, y + p->mblk, 1, cvec, zvec, gout, rd, st);
   launch_x0_sum(st, p->N, p->n0, p->nle, p->f0first, p->ws.part, p->F0, y + p->mblk, 1, cvec, zvec, p->x0off,
                 gout, rd);
 }
@@ -988,6 +1002,104 @@ ahlp_status_t ahlp_problem_destroy(ahlp_problem_t p) {
   return AHLP_OK;
 }
 
+namespace {
+// The compressed copy of the blocks, where the passes are shorter with it: a
+// pass moves 10 bytes per padded nonzero against the dense tiles' 8 bytes per
+// element.  Measured on three refined solves with 256 blocks of 256 x 512, at
+// 10, 40, 60 and 80% nonzeros (0.15, 0.55, 0.82 and 1.05 of the dense bytes):
+// 1.63, 1.97, 2.22 and 2.18 ms against 2.42, 2.38, 2.38 and 2.15 ms; so it is
+// used up to SPARSE_SHARE of them.  It takes at most an eighth of the free
+// memory; without that the dense passes stay.
+constexpr double SPARSE_SHARE = 0.9;
+ahlp_status_t sparse_setup(ahlp_problem_t p, const std::vector<int>& rownz,
+                           const std::vector<int>& colnz, const std::vector<int>& ccolnz,
+                           hipStream_t st) {
+  const int N = p->N, n0 = p->n0;
+  std::vector<long long> roff{0}, coff{0};
+  std::vector<int4> ritems, citems;
+  std::vector<int2> ctiles;
+  int max_cols = 0, max_rows = 0;
+  // tiles per work item: two per wave, so that a block's vector is staged less
+  // often, where that still leaves four workgroups per CU; else one
+  auto per_item = [&](long long tiles) { return tiles >= 8LL * 4 * p->num_cu ? 8 : 4; };
+  const int pr = per_item(p->nrt), pc = per_item(p->nct + p->nc0);
+  for (int i = 0; i < N; ++i) {
+    const BlockInfo& b = p->hb[i];
+    const int nct = b.nt + b.kc0;
+    max_cols = std::max(max_cols, TS * nct);
+    max_rows = std::max(max_rows, TS * b.mt);
+    for (int t = 0; t < b.mt; t += pr)
+      ritems.push_back(int4{i, t, std::min(t + pr, b.mt), (int)roff.size() - 1 + t});
+    for (int t = 0; t < nct; t += pc)
+      citems.push_back(int4{i, t, std::min(t + pc, nct), (int)coff.size() - 1 + t});
+    for (int t = 0; t < b.mt; ++t) {
+      int most = 0;
+      for (int r = TS * t; r < std::min(TS * (t + 1), b.m); ++r) most = std::max(most, rownz[b.yoff + r]);
+      roff.push_back(roff.back() + (most + 3) / 4);
+    }
+    for (int t = 0; t < nct; ++t) {
+      int most = 0;
+      if (t < b.nt)
+        for (int c = TS * t; c < std::min(TS * (t + 1), b.n); ++c) most = std::max(most, colnz[b.xoff + c]);
+      else
+        for (int c = TS * (t - b.nt); c < std::min(TS * (t - b.nt + 1), n0); ++c)
+          most = std::max(most, ccolnz[(size_t)i * n0 + c]);
+      coff.push_back(coff.back() + (most + 3) / 4);
+      ctiles.push_back(int2{i, t});
+    }
+  }
+  // 16-bit indices, three staged vectors in 64 KiB of LDS
+  if (max_cols > 2560 || max_rows > 2560) return AHLP_OK;
+  const double dense = 8.0 * (double)(p->a_total + p->c_total);
+  if (10.0 * 64.0 * (double)std::max(roff.back(), coff.back()) > SPARSE_SHARE * dense) return AHLP_OK;
+  size_t mem_free = 0, mem_all = 0;
+  HIPCHK(hipMemGetInfo(&mem_free, &mem_all));
+  if (8.0 * 640.0 * (double)(roff.back() + coff.back()) > (double)mem_free) return AHLP_OK;
+  DevMem& M = p->mem;
+  SpMat& s = p->sp;
+  // one allocation, the parts at 256-byte steps
+  unsigned char* base = nullptr;
+  size_t bytes = 0;
+  auto place = [&](size_t n) { const size_t o = bytes; bytes += (n + 255) / 256 * 256; return o; };
+  const size_t o_rv = place(64 * 8 * (size_t)roff.back()), o_cv = place(64 * 8 * (size_t)coff.back()),
+               o_ri = place(64 * 2 * (size_t)roff.back()), o_ci = place(64 * 2 * (size_t)coff.back()),
+               o_ro = place(8 * roff.size()), o_co = place(8 * coff.size()),
+               o_rt = place(16 * ritems.size()), o_ct = place(16 * citems.size()),
+               o_tl = place(8 * ctiles.size());
+  if (M.alloc(&base, (long long)bytes) != AHLP_OK) {
+    (void)hipGetLastError();
+    g_err.clear();
+    return AHLP_OK;
+  }
+  HIPCHK(hipMemcpyAsync(base + o_ro, roff.data(), 8 * roff.size(), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(base + o_co, coff.data(), 8 * coff.size(), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(base + o_rt, ritems.data(), 16 * ritems.size(), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(base + o_ct, citems.data(), 16 * citems.size(), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(base + o_tl, ctiles.data(), 8 * ctiles.size(), hipMemcpyHostToDevice, st));
+  s.rval = reinterpret_cast<double*>(base + o_rv);
+  s.cval = reinterpret_cast<double*>(base + o_cv);
+  s.ridx = reinterpret_cast<unsigned short*>(base + o_ri);
+  s.cidx = reinterpret_cast<unsigned short*>(base + o_ci);
+  s.roff = reinterpret_cast<const long long*>(base + o_ro);
+  s.coff = reinterpret_cast<const long long*>(base + o_co);
+  s.row_items = reinterpret_cast<const int4*>(base + o_rt);
+  s.col_items = reinterpret_cast<const int4*>(base + o_ct);
+  const int2* ct = reinterpret_cast<const int2*>(base + o_tl);
+  s.nrow_items = (int)ritems.size(); s.ncol_items = (int)citems.size();
+  s.max_cols = max_cols; s.max_rows = max_rows;
+  launch_sp_fill(st, p->blk, p->rowtiles, p->nrt, ct, (int)ctiles.size(), p->A, p->C, s);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(st));   // the host vectors are temporaries
+  p->sparse = true;
+  // the row passes' algorithmic bytes: value and index of every nonzero, C's included
+  double nz = 0.0;
+  for (int v : rownz) nz += v;
+  p->a_bytes = 10.0 * nz;
+  p->c_bytes = 0.0;
+  return AHLP_OK;
+}
+}  // namespace
+
 ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
                                   ahlp_problem_t* out) {
   g_err.clear();
@@ -1085,6 +1197,8 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   // ---- host packing: A and C into tile-major, link rows into CSR/CSC
   std::vector<double> hA((size_t)ao, 0.0), hC((size_t)std::max(co, 1LL), 0.0);
   std::vector<double> rowabs((size_t)p->m_tot, 0.0), colabs((size_t)p->n_tot, 0.0);
+  // nonzeros per block row of [A | C], per column of A and per block and column of C
+  std::vector<int> rownz((size_t)yo, 0), colnz((size_t)xo, 0), ccolnz((size_t)N * n0, 0);
   {
     long long aoffs = 0, coffs = 0;
     for (int i = 0; i < N; ++i) {
@@ -1094,6 +1208,9 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
         for (int c = 0; c < b.n; ++c) {
           const double v = Ai[(long long)r * b.n + c];
           if (!std::isfinite(v)) return fail(AHLP_ENUMERIC, "non-finite A in block %d", i);
+          const int nz = v != 0.0;   // counted without a branch: the pattern is irregular
+          rownz[b.yoff + r] += nz;
+          colnz[b.xoff + c] += nz;
           hA[b.aoff + ((long long)(r / 16) * b.nt + c / 16) * 256 + (c % 16) * 16 + r % 16] = v;
           rowabs[b.yoff + r] += std::fabs(v);
           colabs[b.xoff + c] += std::fabs(v);
@@ -1105,6 +1222,9 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
           for (int c = 0; c < n0; ++c) {
             const double v = Ci[(long long)r * n0 + c];
             if (!std::isfinite(v)) return fail(AHLP_ENUMERIC, "non-finite C in block %d", i);
+            const int nz = v != 0.0;
+            rownz[b.yoff + r] += nz;
+            ccolnz[(size_t)i * n0 + c] += nz;
             hC[b.coff + ((long long)(r / 16) * kc0 + c / 16) * 256 + (c % 16) * 16 + r % 16] = v;
             rowabs[b.yoff + r] += std::fabs(v);
             colabs[p->x0off + c] += std::fabs(v);
@@ -1394,7 +1514,7 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   CHK(M.alloc(&p->S00w, std::max(nbw * nbw, 1)));
   p->tp = bcr_tiles(p->lmax, nbw);
   p->fast = p->tp > 0;
-  for (int i = 0; i < N; ++i) {
+  for (int i = 0; i < N; ++i) {   // (a_bytes, c_bytes: of the compressed copy if there is one)
     p->a_bytes += 8.0 * p->m[i] * p->n[i];
     p->c_bytes += 8.0 * p->m[i] * n0;
     p->xv_bytes += 8.0 * p->n[i];
@@ -1511,6 +1631,7 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   if (chain_sh > 64 * 1024) set_chain_smem_limits(chain_sh);
   HIPCHK(hipGetLastError());
   CHK(set_buckets(p, st));
+  CHK(sparse_setup(p, rownz, colnz, ccolnz, st));
   HIPCHK(hipStreamSynchronize(st));
   p->timer.st = st;
   *out = up.release();

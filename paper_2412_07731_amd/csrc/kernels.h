@@ -237,6 +237,35 @@ void launch_cols(hipStream_t st, const BlockInfo* blk, const int2* coltiles, int
                  const int* crow, const double* cval, int mode, const double* cvec,
                  const double* zvec, const double* Dp, double* gout, double* out,
                  const DzArgs& dzv = DzArgs{});
+// The compressed copy of the blocks (k_sparse.hip): slices of 16 rows of
+// [A_i | C_i] (a block's mt, blocks in order) and of 16 columns (its nt, then
+// its kc0), slice t's groups of 64 at off[t] .. off[t + 1].  Row entries index
+// the block's padded columns, then (from 16 nt on) those of x_0; column
+// entries its padded rows.
+struct SpMat {
+  const long long* roff; const long long* coff;
+  double* rval; double* cval;
+  unsigned short* ridx; unsigned short* cidx;
+  const int4* row_items; const int4* col_items;   // block, first tile, end, slice of the first
+  int nrow_items, ncol_items;
+  int max_cols, max_rows;                          // largest 16 (nt + kc0), 16 mt: the LDS of a pass
+};
+// the column pass's arguments (k_cols, k_ccols)
+struct ColsArgs {
+  const double* yL;
+  const int* cptr; const int* crow; const double* cval;
+  int mode, n0;
+  const double* cvec; const double* zvec; const double* Dp;
+  double* gout; double* out; double* part;
+  DzArgs dzv;
+};
+void launch_sp_fill(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
+                    const int2* coltiles, int nct, const double* A, const double* C,
+                    const SpMat& sp);
+void launch_sp_rows(hipStream_t st, const BlockInfo* blk, const SpMat& sp, long long d0off,
+                    const RowsArgs& ra);
+void launch_sp_cols(hipStream_t st, const BlockInfo* blk, const SpMat& sp, const double* yp,
+                    const ColsArgs& ca);
 void launch_ccols(hipStream_t st, const BlockInfo* blk, const int2* ctiles, int nctile, int n0,
                   const double* C, const double* yp, double* part);
 // F0 rows below f0first are zero (skipped)
