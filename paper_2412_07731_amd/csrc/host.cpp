@@ -51,9 +51,14 @@ ahlp_status_t fail(ahlp_status_t st, const char* fmt, ...) {
 
 inline long long r16(long long v) { return (v + 15) / 16 * 16; }
 
-// Device allocation registry: everything is freed by destroy.
+// Device allocation registry: everything is freed by destroy.  Requests of up
+// to SLAB / 4 bytes share slabs (256-byte aligned pieces): a problem takes over
+// a hundred, and a hipMalloc each was half of a small problem's create.
 struct DevMem {
+  static constexpr size_t SLAB = size_t(1) << 20;
   std::vector<void*> ptrs;
+  char* slab = nullptr;
+  size_t used = SLAB;
   ~DevMem() {
     for (void* p : ptrs) (void)hipFree(p);
   }
@@ -62,11 +67,22 @@ struct DevMem {
     *out = nullptr;
     if (count <= 0) count = 1;
     void* p = nullptr;
-    hipError_t e = hipMalloc(&p, (size_t)count * sizeof(T));
+    const size_t need = ((size_t)count * sizeof(T) + 255) / 256 * 256;
+    const bool small = need <= SLAB / 4;
+    if (small && used + need <= SLAB) {
+      *out = reinterpret_cast<T*>(slab + used);
+      used += need;
+      return AHLP_OK;
+    }
+    hipError_t e = hipMalloc(&p, small ? SLAB : (size_t)count * sizeof(T));
     if (e != hipSuccess)
       return fail(AHLP_ENOMEM, "hipMalloc of %lld bytes failed: %s", (long long)(count * sizeof(T)),
                   hipGetErrorString(e));
     ptrs.push_back(p);
+    if (small) {
+      slab = static_cast<char*>(p);
+      used = need;
+    }
     *out = static_cast<T*>(p);
     return AHLP_OK;
   }
@@ -235,6 +251,19 @@ struct ahlp_problem_s {
   // compressed copy of the blocks for the row and column passes (when it pays)
   bool sparse = false;
   SpMat sp{};
+  // the block SYRK's work per precision (FP64, FP32): items over the dense tiles
+  // and over the nonzero lists (some block of either plan), by block from ss_off
+  struct SyrkPlan {
+    std::vector<char> sparse;
+    int4 *dense = nullptr, *sp = nullptr;
+    int nd = 0, nsp = 0;
+  } syrk_plan[2];
+  SyrkSp ssp{};
+  double* sval = nullptr;
+  float* sval32 = nullptr;
+  int4* ss_items = nullptr;
+  long long ss_entries = 0;
+  std::vector<int> ss_off;
   int2 *rowtiles = nullptr, *coltiles = nullptr, *c0tiles = nullptr;
   int nrt = 0, nct = 0, nc0 = 0;
   int* d_l = nullptr;
@@ -465,6 +494,26 @@ ahlp_status_t set_buckets(ahlp_problem_t p, hipStream_t st) {
   return AHLP_OK;
 }
 
+// The block SYRK of all blocks, or of block i (i >= 0): over the nonzeros where
+// the plan of this precision says so, else over the dense tiles.
+template <typename T>
+void run_syrk(ahlp_problem_t p, hipStream_t st, const T* A, T* LB, int i = -1) {
+  const auto& plan = p->syrk_plan[sizeof(T) == 4];
+  const T* val;
+  if constexpr (sizeof(T) == 4) val = p->sval32;
+  else val = p->sval;
+  if (i >= 0) {
+    if (plan.sparse[i])
+      launch_syrk_sp<T>(st, p->blk, p->ss_items + p->ss_off[i], p->ss_off[i + 1] - p->ss_off[i], p->ssp,
+                        val, p->Dp, LB, p->delta);
+    else
+      launch_syrk<T>(st, p->blk, p->syrk_items + p->syrk_off[i], p->syrk_cnt[i], A, p->Dp, LB, p->delta);
+    return;
+  }
+  launch_syrk_sp<T>(st, p->blk, plan.sp, plan.nsp, p->ssp, val, p->Dp, LB, p->delta);
+  if (plan.nd > 0) launch_syrk<T>(st, p->blk, plan.dense, plan.nd, A, p->Dp, LB, p->delta);
+}
+
 // The tall kernels for n blocks (their scratch is there: set_buckets, ahlp_autotune).
 template <typename T>
 void factor_tall(ahlp_problem_t p, hipStream_t st, const int* order, int n, int mt, int rt, T* LB,
@@ -482,8 +531,7 @@ ahlp_status_t factor_blocks_per_block(ahlp_problem_t p, hipStream_t st, T* LB, T
   for (int i = 0; i < p->N; ++i) {
     launch_link<T>(st, p->blk, p->link_items + p->link_off[i], p->link_cnt[i], p->nb, p->A, p->C,
                    p->lptr, p->lcol, p->lval, p->Dp, LB, p->PQ);
-    launch_syrk<T>(st, p->blk, p->syrk_items + p->syrk_off[i], p->syrk_cnt[i], A, p->Dp, LB,
-                   p->delta);
+    run_syrk<T>(p, st, A, LB, i);
   }
   p->timer.end();
   p->timer.begin(AHLP_ST_FACTOR);
@@ -541,7 +589,7 @@ ahlp_status_t factor_blocks(ahlp_problem_t p, hipStream_t st, T* LB, T* LINV, co
                  p->lval, p->Dp, LB, p->PQ);
   HIPCHK(hipEventRecord(p->ev_join, p->side));
   p->timer.begin(AHLP_ST_SYRK);
-  launch_syrk<T>(st, p->blk, p->syrk_items, p->nsyrk, A, p->Dp, LB, p->delta);
+  run_syrk<T>(p, st, A, LB);
   p->timer.end();
   p->timer.begin(AHLP_ST_FACTOR);
   HIPCHK(hipStreamWaitEvent(st, p->ev_join, 0));
@@ -597,7 +645,15 @@ BcrArgs bcr_args(ahlp_problem_t p) {
 }
 
 ahlp_status_t ensure_fp32(ahlp_problem_t p, hipStream_t st) {
-  if (!p->A32) {
+  const auto& plan = p->syrk_plan[1];
+  if (plan.nsp > 0 && !p->sval32) {
+    float* v = nullptr;
+    CHK(p->mem.alloc(&v, p->ss_entries));
+    launch_convert_f32(st, p->ss_entries, p->sval, v);
+    p->sval32 = v;
+  }
+  // (the fused launch multiplies every block's dense tiles)
+  if (!p->A32 && (plan.nd > 0 || p->launch_mode == AHLP_LAUNCH_FUSED)) {
     CHK(p->mem.alloc(&p->A32, p->a_total));
     launch_convert_f32(st, p->a_total, p->A, p->A32);
   }
@@ -1003,6 +1059,57 @@ ahlp_status_t ahlp_problem_destroy(ahlp_problem_t p) {
 }
 
 namespace {
+// Packs block b's A_i (row-major) into its tiles, with the sums of absolute
+// values and the nonzero counts of its rows, columns and rows by stage of SS_K
+// columns (all added to, in ascending order).  false: a non-finite entry.
+// Tile by tile, each with a pass along its rows and one along its columns, so
+// that stores and sums run over consecutive elements.
+bool pack_block(const double* __restrict__ A, const BlockInfo& b, double* __restrict__ tiles,
+                double* __restrict__ rowabs, double* __restrict__ colabs, int* __restrict__ rownz,
+                int* __restrict__ colnz, unsigned char* __restrict__ stnz) {
+  const int nst = (b.n + SS_K - 1) / SS_K;
+  double chk = 0.0;   // v * 0 summed: zero unless some v is not finite
+  for (int I = 0; I < b.mt; ++I)
+    for (int K = 0; K < b.nt; ++K) {
+      const int rows = std::min(TS, b.m - TS * I), cols = std::min(TS, b.n - TS * K);
+      double buf[TS][TS] = {};
+      int nz[TS] = {};
+      double ca[TS] = {};
+      int cz[TS] = {};
+      for (int c = 0; c < cols; ++c) ca[c] = colabs[TS * K + c];
+      for (int r = 0; r < rows; ++r) {
+        const double* src = A + (long long)(TS * I + r) * b.n + TS * K;
+        if (cols == TS) std::memcpy(buf[r], src, sizeof buf[r]);
+        else std::copy(src, src + cols, buf[r]);
+        for (int c = 0; c < TS; ++c) {
+          ca[c] += std::fabs(buf[r][c]);
+          cz[c] += buf[r][c] != 0.0;
+        }
+        for (int c = 0; c < TS; ++c) chk += buf[r][c] * 0.0;
+      }
+      for (int c = 0; c < cols; ++c) {
+        colabs[TS * K + c] = ca[c];
+        colnz[TS * K + c] += cz[c];
+      }
+      double* t = tiles + 256LL * ((long long)I * b.nt + K);
+      double ra[TS] = {};
+      for (int r = 0; r < rows; ++r) ra[r] = rowabs[TS * I + r];
+      for (int c = 0; c < TS; ++c)
+        for (int r = 0; r < TS; ++r) {
+          const double v = buf[r][c];
+          t[c * TS + r] = v;
+          ra[r] += std::fabs(v);
+          nz[r] += v != 0.0;
+        }
+      for (int r = 0; r < rows; ++r) {
+        rowabs[TS * I + r] = ra[r];
+        rownz[TS * I + r] += nz[r];
+        stnz[(size_t)(TS * I + r) * nst + TS * K / SS_K] += (unsigned char)nz[r];
+      }
+    }
+  return chk == 0.0;
+}
+
 // The compressed copy of the blocks, where the passes are shorter with it: a
 // pass moves 10 bytes per padded nonzero against the dense tiles' 8 bytes per
 // element.  Measured on three refined solves with 256 blocks of 256 x 512, at
@@ -1096,6 +1203,144 @@ ahlp_status_t sparse_setup(ahlp_problem_t p, const std::vector<int>& rownz,
   for (int v : rownz) nz += v;
   p->a_bytes = 10.0 * nz;
   p->c_bytes = 0.0;
+  return AHLP_OK;
+}
+
+// Chooses per block and precision between the block SYRK over the dense tiles
+// and over the nonzero lists (the values are the same to the bit), and builds
+// the lists.  The rule compares what the two cost a CU, in microseconds,
+// fitted to kernel times at 3-30% nonzeros and 40-600 rows: the dense kernel 2
+// per 64 x 64 item and 0.043 (FP32 0.025) per 16 x 16 x 16 tile product, the
+// other 1.5 per item, 1.75 (0.95) per item and stage and 0.003 (0.0023) per
+// nonzero walked, more than twice that past 16 in a row and stage.  256 blocks of 256 x 512, FP64: 198 us dense; lists 76, 114,
+// 176 and 282 us at 3, 10, 20 and 30% nonzeros.  With fewer items than two per
+// CU the launch lasts as long as its longest items, and the dense ones are
+// shorter (47 blocks of 110 x 220: 16 us against 24); and a second launch has
+// to be worth its 20 us.
+ahlp_status_t syrk_setup(ahlp_problem_t p, const std::vector<unsigned char>& stnz,
+                         const std::vector<int>& order, hipStream_t st) {
+  const int N = p->N;
+  for (auto& plan : p->syrk_plan) {
+    plan.sparse.assign(N, 0);
+    plan.dense = p->syrk_items;
+    plan.nd = p->nsyrk;
+  }
+  int max_cols = 0;
+  for (const BlockInfo& b : p->hb) max_cols = std::max(max_cols, TS * b.nt);
+  if (max_cols > SS_NMAX || p->nsyrk < 2 * p->num_cu) return AHLP_OK;
+  std::vector<int> first, off{0};   // off in batches of four entries
+  std::vector<unsigned> cnt;
+  std::vector<std::vector<int4>> per(N);
+  size_t so = 0, nitems[2] = {0, 0};
+  double gain[2] = {0.0, 0.0};
+  for (int i = 0; i < N; ++i) {
+    const BlockInfo& b = p->hb[i];
+    const int nst = (b.n + SS_K - 1) / SS_K;
+    double walked = 0.0;
+    for (int t = 0; t < b.mt; ++t) {
+      first.push_back((int)off.size() - 1);
+      for (int s = 0; s < nst; ++s) {
+        unsigned w[4] = {0, 0, 0, 0};
+        long long sum = 0, cost = 0;
+        for (int j = 0; j < TS && TS * t + j < b.m; ++j) {
+          const unsigned k = (stnz[so + (size_t)(TS * t + j) * nst + s] + 3) / 4;
+          w[j >> 2] |= k << (8 * (j & 3));
+          sum += k;
+          cost += k <= 4 ? 4 * k : 9 * k - 20;   // past 16 a row's entries are requested as they are used
+        }
+        if (4LL * (off.back() + sum) > INT32_MAX - 64) return AHLP_OK;
+        cnt.insert(cnt.end(), w, w + 4);
+        off.push_back((int)(off.back() + sum));
+        walked += (t / SS_COLS + 1) * (double)cost;   // for every group of tile columns the row meets
+      }
+    }
+    so += (size_t)b.m * nst;
+    for (int J = 0; J < b.mt; J += SS_COLS) {
+      const int rows = b.mt - J, parts = (rows + SS_ROWS - 1) / SS_ROWS;
+      for (int q = 0; q < parts; ++q) {
+        const int a = rows * q / parts, e = rows * (q + 1) / parts;
+        per[i].push_back(int4{i, J, J + a, e - a});
+      }
+    }
+    const double items = (double)per[i].size(), tiles = 0.5 * b.mt * (b.mt + 1) * b.nt;
+    const double base = 2.0 * p->syrk_cnt[i];
+    const double lists[2] = {1.5 * items + 1.75 * items * nst + 0.003 * walked,
+                             1.5 * items + 0.95 * items * nst + 0.0023 * walked};
+    const double dense[2] = {base + 0.043 * tiles, base + 0.025 * tiles};
+    for (int q = 0; q < 2; ++q)
+      if (lists[q] < 0.85 * dense[q]) {
+        p->syrk_plan[q].sparse[i] = 1;
+        gain[q] += dense[q] - lists[q];
+        nitems[q] += per[i].size();
+      }
+  }
+  bool any = false;
+  for (int q = 0; q < 2; ++q) {
+    if (nitems[q] < 2 * (size_t)p->num_cu || gain[q] < 20.0 * p->num_cu)
+      p->syrk_plan[q].sparse.assign(N, 0);
+    else
+      any = true;
+  }
+  if (!any) return AHLP_OK;
+  // every block's list items by block, then each plan's items in the dense
+  // kernel's block order
+  std::vector<int4> items;
+  p->ss_off.assign(N + 1, 0);
+  for (int i = 0; i < N; ++i) {
+    p->ss_off[i] = (int)items.size();
+    items.insert(items.end(), per[i].begin(), per[i].end());
+  }
+  p->ss_off[N] = (int)items.size();
+  size_t at[4];
+  for (int q = 0; q < 2; ++q) {
+    const auto& plan = p->syrk_plan[q];
+    at[2 * q] = items.size();
+    for (int i : order)
+      if (plan.sparse[i]) items.insert(items.end(), per[i].begin(), per[i].end());
+    at[2 * q + 1] = items.size();
+    for (int i : order)
+      if (!plan.sparse[i])
+        items.insert(items.end(), p->h_syrk.begin() + p->syrk_off[i],
+                     p->h_syrk.begin() + p->syrk_off[i] + p->syrk_cnt[i]);
+  }
+  const size_t entries = 4 * (size_t)off.back() + 16;   // the kernel requests up to 16 past the last
+  size_t bytes = 0;
+  auto place = [&](size_t n) { const size_t o = bytes; bytes += (n + 255) / 256 * 256; return o; };
+  const size_t o_v = place(8 * entries), o_x = place(2 * entries), o_f = place(4 * first.size()),
+               o_o = place(4 * off.size()), o_c = place(4 * cnt.size()), o_i = place(16 * items.size());
+  size_t mem_free = 0, mem_all = 0;
+  HIPCHK(hipMemGetInfo(&mem_free, &mem_all));
+  unsigned char* base = nullptr;
+  if (8 * bytes > mem_free || p->mem.alloc(&base, (long long)bytes) != AHLP_OK) {
+    // no memory for the lists: the dense tiles
+    (void)hipGetLastError();
+    g_err.clear();
+    for (auto& plan : p->syrk_plan) plan.sparse.assign(N, 0);
+    return AHLP_OK;
+  }
+  HIPCHK(hipMemcpyAsync(base + o_f, first.data(), 4 * first.size(), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(base + o_o, off.data(), 4 * off.size(), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(base + o_c, cnt.data(), 4 * cnt.size(), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(base + o_i, items.data(), 16 * items.size(), hipMemcpyHostToDevice, st));
+  p->ss_entries = (long long)entries;
+  p->sval = reinterpret_cast<double*>(base + o_v);
+  p->ss_items = reinterpret_cast<int4*>(base + o_i);
+  for (int q = 0; q < 2; ++q) {
+    auto& plan = p->syrk_plan[q];
+    plan.sp = p->ss_items + at[2 * q];
+    plan.nsp = (int)(at[2 * q + 1] - at[2 * q]);
+    plan.dense = p->ss_items + at[2 * q + 1];
+    plan.nd = (int)((q == 0 ? at[2] : items.size()) - at[2 * q + 1]);
+  }
+  unsigned short* idx = reinterpret_cast<unsigned short*>(base + o_x);
+  p->ssp = SyrkSp{reinterpret_cast<const int*>(base + o_f), reinterpret_cast<const int*>(base + o_o),
+                  reinterpret_cast<const unsigned*>(base + o_c), idx, max_cols};
+  launch_fill(st, 16, 0.0, p->sval + entries - 16);
+  launch_fill(st, 4, 0.0, reinterpret_cast<double*>(base + o_x + 2 * (entries - 16)));
+  set_syrk_sp_smem_limits();
+  launch_syrk_sp_fill(st, p->blk, p->rowtiles, p->nrt, p->A, p->ssp, p->sval, idx);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(st));   // the host vectors are temporaries
   return AHLP_OK;
 }
 }  // namespace
@@ -1195,26 +1440,43 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   p->vp_total = vo; p->q_total = qo;
 
   // ---- host packing: A and C into tile-major, link rows into CSR/CSC
-  std::vector<double> hA((size_t)ao, 0.0), hC((size_t)std::max(co, 1LL), 0.0);
+  CHK(p->mem.alloc(&p->A, ao));
+  std::vector<double> hC((size_t)std::max(co, 1LL), 0.0);
   std::vector<double> rowabs((size_t)p->m_tot, 0.0), colabs((size_t)p->n_tot, 0.0);
-  // nonzeros per block row of [A | C], per column of A and per block and column of C
+  // nonzeros per block row of [A | C], per row of A and stage of SS_K columns,
+  // per column of A and per block and column of C
   std::vector<int> rownz((size_t)yo, 0), colnz((size_t)xo, 0), ccolnz((size_t)N * n0, 0);
+  std::vector<unsigned char> stnz;
   {
+    size_t sz = 0;
+    for (int i = 0; i < N; ++i) sz += (size_t)p->hb[i].m * ((p->hb[i].n + SS_K - 1) / SS_K);
+    stnz.assign(sz, 0);
+  }
+  size_t sto = 0;
+  {
+    // the tiles go to the device through a staging buffer, whose pages stay
+    // mapped, instead of one host copy of all of them
+    std::vector<double> stage((size_t)std::min(ao, 4LL << 20));
+    long long fill = 0, sent = 0;
+    auto flush = [&]() -> ahlp_status_t {
+      if (fill == 0) return AHLP_OK;
+      HIPCHK(hipMemcpyAsync(p->A + sent, stage.data(), sizeof(double) * fill, hipMemcpyHostToDevice, st));
+      HIPCHK(hipStreamSynchronize(st));
+      sent += fill;
+      fill = 0;
+      return AHLP_OK;
+    };
     long long aoffs = 0, coffs = 0;
     for (int i = 0; i < N; ++i) {
       const BlockInfo& b = p->hb[i];
-      const double* Ai = d->A + aoffs;
-      for (int r = 0; r < b.m; ++r)
-        for (int c = 0; c < b.n; ++c) {
-          const double v = Ai[(long long)r * b.n + c];
-          if (!std::isfinite(v)) return fail(AHLP_ENUMERIC, "non-finite A in block %d", i);
-          const int nz = v != 0.0;   // counted without a branch: the pattern is irregular
-          rownz[b.yoff + r] += nz;
-          colnz[b.xoff + c] += nz;
-          hA[b.aoff + ((long long)(r / 16) * b.nt + c / 16) * 256 + (c % 16) * 16 + r % 16] = v;
-          rowabs[b.yoff + r] += std::fabs(v);
-          colabs[b.xoff + c] += std::fabs(v);
-        }
+      if (fill + 256LL * b.mt * b.nt > (long long)stage.size() && fill > 0) CHK(flush());
+      if (256LL * b.mt * b.nt > (long long)stage.size()) stage.resize((size_t)(256LL * b.mt * b.nt));
+      if (!pack_block(d->A + aoffs, b, stage.data() + fill, rowabs.data() + b.yoff,
+                      colabs.data() + b.xoff, rownz.data() + b.yoff, colnz.data() + b.xoff,
+                      stnz.data() + sto))
+        return fail(AHLP_ENUMERIC, "non-finite A in block %d", i);
+      fill += 256LL * b.mt * b.nt;
+      sto += (size_t)b.m * ((b.n + SS_K - 1) / SS_K);
       aoffs += (long long)b.m * b.n;
       if (n0 > 0) {
         const double* Ci = d->C + coffs;
@@ -1232,6 +1494,7 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
         coffs += (long long)b.m * n0;
       }
     }
+    CHK(flush());
   }
   // CSR of each block's link sections (rows q in [0, 16 kt), padded rows
   // empty): its part of the left and right pairs' link rows and of the global
@@ -1458,7 +1721,6 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   // ---- device allocations and uploads
   DevMem& M = p->mem;
   CHK(M.alloc(&p->blk, N));
-  CHK(M.alloc(&p->A, ao));
   CHK(M.alloc(&p->C, std::max(co, 1LL)));
   CHK(M.alloc(&p->lptr, csr_off));
   CHK(M.alloc(&p->lcol, std::max<long long>(hcol.size(), 1)));
@@ -1579,7 +1841,6 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   HIPCHK(hipEventCreateWithFlags(&p->ev_join, hipEventDisableTiming));
 
   HIPCHK(hipMemcpyAsync(p->blk, p->hb.data(), sizeof(BlockInfo) * N, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(p->A, hA.data(), sizeof(double) * ao, hipMemcpyHostToDevice, st));
   if (co > 0) HIPCHK(hipMemcpyAsync(p->C, hC.data(), sizeof(double) * co, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(p->lptr, hptr.data(), sizeof(int) * csr_off, hipMemcpyHostToDevice, st));
   if (!hcol.empty()) {
@@ -1632,6 +1893,7 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   HIPCHK(hipGetLastError());
   CHK(set_buckets(p, st));
   CHK(sparse_setup(p, rownz, colnz, ccolnz, st));
+  CHK(syrk_setup(p, stnz, syrk_order, st));
   HIPCHK(hipStreamSynchronize(st));
   p->timer.st = st;
   *out = up.release();
@@ -1842,7 +2104,7 @@ ahlp_status_t ahlp_autotune(ahlp_problem_t p, const char* cache_path, int32_t* m
           if (!can[k]) continue;
           launch_link<double>(st, p->blk, p->link_items, p->nlink, p->nb, p->A, p->C, p->lptr,
                               p->lcol, p->lval, p->Dp, p->LB, p->PQ);
-          launch_syrk<double>(st, p->blk, p->syrk_items, p->nsyrk, p->A, p->Dp, p->LB, delta);
+          run_syrk<double>(p, st, p->A, p->LB);
           HIPCHK(hipEventRecord(e0, st));
           if (k == BFK_COLUMN)
             factor_tall<double>(p, st, p->bf_order, (int)hblk.size(), rt, rt, p->LB, p->LINV);

@@ -13,6 +13,27 @@ void launch_prep(hipStream_t st, const BlockInfo* blk, int N, int n0, long long 
 template <typename T>
 void launch_syrk(hipStream_t st, const BlockInfo* blk, const int4* items, int nitems,
                  const T* A, const double* Dp, T* LB, double delta);
+// The same for blocks with few nonzeros (k_syrk_sp.hip), bitwise equal.  The
+// nonzeros of tile row t (of all blocks' in order) in stage st of SS_K columns
+// are the batches off[first[t] + st] .. off[first[t] + st + 1] of four entries,
+// row by row, row j of the 16 having cnt's byte j of them, padded with zeros;
+// idx is the column within the stage times 16 SS_COLS, plus the row.  items: block, first of
+// SS_COLS tile columns, first tile row, tile rows (at most SS_ROWS).
+constexpr int SS_K = 64, SS_COLS = 8, SS_ROWS = 8;
+constexpr int SS_NMAX = 2560;   // padded columns of a block, at most (its D shares the LDS)
+struct SyrkSp {
+  const int* first;
+  const int* off;
+  const unsigned* cnt;         // 4 words per (tile row, stage)
+  const unsigned short* idx;
+  int max_cols;                // largest 16 nt
+};
+template <typename T>
+void launch_syrk_sp(hipStream_t st, const BlockInfo* blk, const int4* items, int nitems,
+                    const SyrkSp& sp, const T* val, const double* Dp, T* LB, double delta);
+void launch_syrk_sp_fill(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
+                         const double* A, const SyrkSp& sp, double* val, unsigned short* idx);
+void set_syrk_sp_smem_limits();
 template <typename T>
 // nb: width of the border section (global rows, then x_0)
 void launch_link(hipStream_t st, const BlockInfo* blk, const int2* items, int nitems, int nb,
