@@ -14,7 +14,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libahlp.so")
 ROOT = os.path.dirname(HERE)
 
-SOURCES = ["k_factor.hip", "k_chain.hip", "k_bcr.hip", "k_bcrn.hip", "k_solve.hip", "k_sparse.hip", "k_syrk_sp.hip", "noalloc.hip",
+SOURCES = ["k_factor.hip", "k_chain.hip", "k_bcr.hip", "k_bcrn.hip", "k_bcrs.hip", "k_solve.hip", "k_sparse.hip", "k_syrk_sp.hip", "noalloc.hip",
            "k_ceiling.hip",
            "host.cpp"]
 FLAGS = [

@@ -823,15 +823,16 @@ ahlp_status_t solve_once(ahlp_problem_t p, const double* rx, const double* ry, c
   link_global_rows(p, p->ws.vx, nullptr, ry + p->mblk, 1.0, p->ws.s, st);
   if (f32) solve_blocks_fwd<float>(p, st, p->LB32, p->LINV32, tpre);
   else solve_blocks_fwd<double>(p, st, p->LB, p->LINV, tpre);
-  launch_schur_rhs(st, p->blk, p->N, p->nb, p->d_l, p->d_loff, p->nl, p->ws.qn, p->ws.rhx + p->x0off,
-                   p->ws.s);
   if (p->fast) {
     BcrSolveArgs a{};
     a.c = bcr_args(p);
     a.loff = p->d_loff; a.nl = p->nl; a.s = p->ws.s; a.u = p->ws.u;
+    a.blk = p->blk; a.qn = p->ws.qn; a.rhx0 = p->ws.rhx + p->x0off; a.dyl = dy + p->mblk;
     a.r = p->ws.br; a.w = p->ws.bw; a.up = p->ws.bup; a.pb = p->ws.bpb; a.u0p = p->ws.bu0p;
     launch_bcr_solve(st, a);
   } else {
+    launch_schur_rhs(st, p->blk, p->N, p->nb, p->d_l, p->d_loff, p->nl, p->ws.qn, p->ws.rhx + p->x0off,
+                     p->ws.s);
     ChainSolveArgs a{};
     a.c = chain_args(p);
     a.loff = p->d_loff; a.nl = p->nl; a.s = p->ws.s; a.w = p->ws.w; a.u = p->ws.u; a.segrhs = p->ws.segrhs;
@@ -843,7 +844,7 @@ ahlp_status_t solve_once(ahlp_problem_t p, const double* rx, const double* ry, c
   const DzArgs dzv{rz, p->zs, p->xs, dz};
   cols_pass(p, p->ws.dyp, p->ws.u, 2, p->ws.rhx, nullptr, gout, dx, st, dzv);
   launch_solve_tail(st, p->N, p->n0, p->nle, p->f0first, p->ws.part, p->F0, p->ws.u, p->x0off, p->mblk, gout, dx, dzv,
-                    dy);
+                    dy, !p->fast);
   p->timer.end();
   HIPCHK(hipGetLastError());
   return AHLP_OK;

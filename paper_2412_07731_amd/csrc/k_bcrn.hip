@@ -16,16 +16,10 @@
 // the chain of TP tile factorizations and the two launches; the arithmetic of
 // a whole reduction is below a MFMA-microsecond.
 // Measured against what it replaced.  511 pairs of 4-32 rows, border 64, one
-// wave per elimination and one launch per level: level 20.0 -> 10.2 + 7.8 us,
-// solve step 11.5 -> 6.0 us forward and 7.3 -> 5.0 us backward.  95 pairs of
-// 33-56 rows, border 24, a segmented chain of scalar eliminations: factor 8.4 ->
-// 0.28 ms, solve 0.94 -> 0.10 ms.
-//
-// Storage (the BcrArgs arrays, sized for TP tiles per pair side):
-//   BD[j], BC[j], FLi[o], FXL[o], FXR[o]   TP x TP tiles, tile (r, c) at c*TP + r
-//   BEt[j], FGt[o]                         t0 x TP tiles, tile (q, c) at c*t0 + q
-// Pair vectors r, w, up: 16 TP values per pair.
-#include "bcr_border.h"
+// wave per elimination and one launch per level: level 20.0 -> 10.2 + 7.8 us.
+// 95 pairs of 33-56 rows, border 24, a segmented chain of scalar eliminations:
+// factor 8.4 -> 0.28 ms.
+#include "bcr_geo.h"
 #include "common.h"
 #include "kernels.h"
 #include "tile_chol.h"
@@ -37,20 +31,11 @@ namespace {
 
 constexpr int MAXT0 = 4;               // border tiles (n0 <= 64)
 constexpr int EW = 8;                  // waves of an eliminating workgroup
-constexpr int MID_WAVES = 16;          // waves of the final-pair and border solve kernel
 // LDS tiles have leading dimension 17 (one pad value per column), so the
 // accumulator-layout and B-operand accesses of a 16-lane row group fall in
 // distinct banks.
 constexpr int PLD = TS + 1;
 constexpr int PT = 16 * PLD;           // values per LDS tile
-
-template <int TP> struct Geo {
-  static constexpr int TB = 16 * TP, BLK = TP * TP * 256;
-  __device__ static __forceinline__ int bt(int r, int c) { return (c * TP + r) * 256; }
-  __device__ static __forceinline__ long long et(long long j, int q, int c, int t0) {
-    return ((j * TP + c) * t0 + q) * 256;
-  }
-};
 
 // a tile in accumulator layout, which is also the layout of the B operand of
 // X * Y and of the A operand of X' * Y: element (4 s + lane / 16, lane % 16)
@@ -262,181 +247,6 @@ __global__ __launch_bounds__(256) void k_bcrn_update(BcrArgs c, int lvl, int n) 
   }
 }
 
-// ----------------------------------------------------------------- solve
-// Forward: w_o = L_o^-1 r_o, r_e -= X_R(o_l)' w_{o_l} + X_L(o_r)' w_{o_r};
-// backward: u_o = L_o^-T (w_o - X_L u_L - X_R u_R - Z_o u0).  A workgroup of TP
-// waves per pair, wave h for the pair's tile row h; a step's tiles are all
-// requested before the first product.
-
-// element 16 h + lane % 16 of pair j's vector at level lvl (level 0: the
-// exact right-hand side, zero on the padding)
-template <int TP>
-__device__ __forceinline__ double rvecn(const BcrSolveArgs& A, int lvl, long long j, int h) {
-  const int i = 16 * h + (threadIdx.x & 15);
-  if (lvl == 0) return i < A.c.l[j] ? A.s[A.loff[j] + i] : 0.0;
-  return A.r[j * (16 * TP) + i];
-}
-// border partials Z_o' w of the border tiles q = h, h + TP, ... (w in LDS)
-template <int TP>
-__device__ __forceinline__ void border_partial(const BcrSolveArgs& A, long long o, int h,
-                                               const double* w) {
-  const BcrArgs& c = A.c;
-  const int lane = threadIdx.x & 63;
-  for (int q = h; q < c.t0; q += TP) {
-    Op g[TP];
-#pragma unroll
-    for (int p = 0; p < TP; ++p) g[p] = op_load(c.FGt + Geo<TP>::et(o, q, p, c.t0));
-    double acc = 0.0;
-#pragma unroll
-    for (int p = 0; p < TP; ++p) acc += op_mv(g[p], w + 16 * p);
-    if (lane < 16) A.pb[(o * c.t0 + q) * 16 + lane] = acc;
-  }
-}
-
-template <int TP>
-__global__ __launch_bounds__(64 * TP) void k_bcrn_fwd(BcrSolveArgs A, int lvl, int n) {
-  typedef Geo<TP> G;
-  const BcrArgs& c = A.c;
-  __shared__ double vl[G::TB], vr[G::TB], wl[G::TB], wr[G::TB];
-  const int lane = threadIdx.x & 63;
-  const int h = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int k = 2 * blockIdx.x;
-  const long long s = 1LL << lvl, e = k * s, ol = (k - 1) * s, orr = (k + 1) * s;
-  const bool hl = k >= 1, hr = k + 1 < n;
-  double acc = rvecn<TP>(A, lvl, e, h);
-  Op ll[TP], lr[TP], xl[TP], xr[TP];
-#pragma unroll
-  for (int q = 0; q < TP; ++q) {
-    if (hl && q <= h) ll[q] = op_load(c.FLi + ol * G::BLK + G::bt(h, q));
-    if (hr && q <= h) lr[q] = op_load(c.FLi + orr * G::BLK + G::bt(h, q));
-    if (hl) xl[q] = op_load(c.FXR + ol * G::BLK + G::bt(q, h));
-    if (hr) xr[q] = op_load(c.FXL + orr * G::BLK + G::bt(q, h));
-  }
-  if (hl) vec_put(vl + 16 * h, rvecn<TP>(A, lvl, ol, h));
-  if (hr) vec_put(vr + 16 * h, rvecn<TP>(A, lvl, orr, h));
-  lds_barrier();
-  if (hl) {
-    double t = 0.0;
-#pragma unroll
-    for (int q = 0; q < TP; ++q)
-      if (q <= h) t += op_mv(ll[q], vl + 16 * q);
-    vec_put(wl + 16 * h, t);
-  }
-  if (hr) {
-    double t = 0.0;
-#pragma unroll
-    for (int q = 0; q < TP; ++q)
-      if (q <= h) t += op_mv(lr[q], vr + 16 * q);
-    vec_put(wr + 16 * h, t);
-    if (lane < 16) A.w[orr * G::TB + 16 * h + lane] = t;
-  }
-  lds_barrier();
-  if (hl)
-#pragma unroll
-    for (int q = 0; q < TP; ++q) acc -= op_mtv(xl[q], wl + 16 * q, nullptr);
-  if (hr) {
-#pragma unroll
-    for (int q = 0; q < TP; ++q) acc -= op_mtv(xr[q], wr + 16 * q, nullptr);
-    border_partial<TP>(A, orr, h, wr);
-  }
-  if (lane < 16) A.r[e * G::TB + 16 * h + lane] = acc;
-}
-
-// u_o from w_o, the neighbours' u (L, R < 0: no such neighbour) and u0 (LDS),
-// by waves h = 0 .. TP - 1 (waves beyond only take the barrier); v: 16 TP
-// values of LDS
-template <int TP>
-__device__ __forceinline__ void bwdn_pair(const BcrSolveArgs& A, long long o, long long L,
-                                          long long R, const double* u0, double* ua, double* ub,
-                                          double* v) {
-  typedef Geo<TP> G;
-  const BcrArgs& c = A.c;
-  const int lane = threadIdx.x & 63;
-  const int h = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  Op li[TP];
-  double t = 0.0;
-  if (h < TP) {
-    Op xl[TP], xr[TP], g[MAXT0];
-#pragma unroll
-    for (int q = 0; q < TP; ++q) {
-      if (L >= 0) xl[q] = op_load(c.FXL + o * G::BLK + G::bt(h, q));
-      if (R >= 0) xr[q] = op_load(c.FXR + o * G::BLK + G::bt(h, q));
-      if (q >= h) li[q] = op_load(c.FLi + o * G::BLK + G::bt(q, h));
-    }
-#pragma unroll
-    for (int q = 0; q < MAXT0; ++q)
-      if (q < c.t0) g[q] = op_load(c.FGt + G::et(o, q, h, c.t0));
-    t = A.w[o * G::TB + 16 * h + (lane & 15)];
-    // every wave keeps its own copies of the neighbours' vectors
-    double* a = ua + h * G::TB;
-    double* b = ub + h * G::TB;
-    if (lane < G::TB) {
-      if (L >= 0) a[lane] = A.up[L * G::TB + lane];
-      if (R >= 0) b[lane] = A.up[R * G::TB + lane];
-    }
-    wave_order();
-#pragma unroll
-    for (int q = 0; q < TP; ++q) {
-      if (L >= 0) t -= op_mv(xl[q], a + 16 * q);
-      if (R >= 0) t -= op_mv(xr[q], b + 16 * q);
-    }
-#pragma unroll
-    for (int q = 0; q < MAXT0; ++q)
-      if (q < c.t0) t -= op_mtv(g[q], u0 + 16 * q, nullptr);
-    vec_put(v + 16 * h, t);
-  }
-  lds_barrier();
-  if (h < TP) {
-    double u = 0.0;
-#pragma unroll
-    for (int q = 0; q < TP; ++q)
-      if (q >= h) u += op_mtv(li[q], v + 16 * q, nullptr);
-    if (lane < 16) {
-      A.up[o * G::TB + 16 * h + lane] = u;
-      if (16 * h + lane < c.l[o]) A.u[A.loff[o] + 16 * h + lane] = u;
-    }
-  }
-}
-
-template <int TP>
-__global__ __launch_bounds__(64 * TP) void k_bcrn_bwd(BcrSolveArgs A, int lvl, int n) {
-  __shared__ double ua[TP * 16 * TP], ub[TP * 16 * TP], v[16 * TP], u0[16 * MAXT0];
-  for (int i = threadIdx.x; i < 16 * A.c.t0; i += blockDim.x) u0[i] = A.u0p[i];
-  lds_barrier();
-  const int k = 2 * blockIdx.x + 1;
-  const long long s = 1LL << lvl;
-  bwdn_pair<TP>(A, k * s, (k - 1) * s, k + 1 < n ? (k + 1) * s : -1, u0, ua, ub, v);
-}
-
-// The final pair forward (w_0 = L_0^-1 r_0 and its border partial), the
-// border solve, the final pair backward.  lvl: the level after the last
-// reduction (where pair 0's right-hand side is).
-template <int TP>
-__global__ __launch_bounds__(64 * MID_WAVES) void k_bcrn_mid(BcrSolveArgs A, int lvl) {
-  typedef Geo<TP> G;
-  const BcrArgs& c = A.c;
-  __shared__ double ua[TP * G::TB], ub[TP * G::TB], vl[G::TB], w[G::TB], sc[16];
-  __shared__ double part[64 * MID_WAVES];
-  __shared__ double s0[16 * MAXT0], w0[16 * MAXT0], u0[16 * MAXT0];
-  const int lane = threadIdx.x & 63;
-  const int h = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (h < TP) vec_put(vl + 16 * h, rvecn<TP>(A, lvl, 0, h));
-  __syncthreads();
-  if (h < TP) {
-    double t = 0.0;
-#pragma unroll
-    for (int q = 0; q < TP; ++q)
-      if (q <= h) t += op_mv(op_load(c.FLi + G::bt(h, q)), vl + 16 * q);
-    vec_put(w + 16 * h, t);
-    if (lane < 16) A.w[16 * h + lane] = t;
-  }
-  __syncthreads();
-  if (h < TP) border_partial<TP>(A, 0, h, w);
-  __syncthreads();
-  bcr_border_solve(A, c.FLbi, false, part, s0, w0, u0, sc);
-  bwdn_pair<TP>(A, 0, -1, -1, u0, ua, ub, vl);
-}
-
 template <int TP>
 void reduce_tp(hipStream_t st, const BcrArgs& c) {
   const long long tiles = (long long)c.P * (2 * TP * TP + TP * c.t0);
@@ -450,19 +260,6 @@ void reduce_tp(hipStream_t st, const BcrArgs& c) {
   hipLaunchKernelGGL(k_bcrn_elim<TP>, dim3(1), dim3(64 * EW), 0, st, c, 0, 1);
 }
 
-template <int TP>
-void solve_tp(hipStream_t st, const BcrSolveArgs& a) {
-  int n = a.c.P, lvl = 0;
-  for (; n > 1; ++lvl, n = (n + 1) / 2)
-    hipLaunchKernelGGL(k_bcrn_fwd<TP>, dim3((n + 1) / 2), dim3(64 * TP), 0, st, a, lvl, n);
-  hipLaunchKernelGGL(k_bcrn_mid<TP>, dim3(1), dim3(64 * MID_WAVES), 0, st, a, lvl);
-  for (int lv = lvl - 1; lv >= 0; --lv) {
-    int nl = a.c.P;
-    for (int v = 0; v < lv; ++v) nl = (nl + 1) / 2;
-    hipLaunchKernelGGL(k_bcrn_bwd<TP>, dim3(nl / 2), dim3(64 * TP), 0, st, a, lv, nl);
-  }
-}
-
 }  // namespace
 
 void launch_bcrn_reduce(hipStream_t st, const BcrArgs& c) {
@@ -470,12 +267,6 @@ void launch_bcrn_reduce(hipStream_t st, const BcrArgs& c) {
   if (c.tp == 2) reduce_tp<2>(st, c);
   else if (c.tp == 3) reduce_tp<3>(st, c);
   else reduce_tp<4>(st, c);
-}
-
-void launch_bcrn_solve(hipStream_t st, const BcrSolveArgs& a) {
-  if (a.c.tp == 2) solve_tp<2>(st, a);
-  else if (a.c.tp == 3) solve_tp<3>(st, a);
-  else solve_tp<4>(st, a);
 }
 
 }  // namespace ahlp

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256) void k_schur_rhs(const BlockInfo* __restrict__
 // End of a solve for the x_0 columns and the link rows: g_0 = sum of the
 // per-block partials C_i' dy_i + F0' dy_L (fixed order), dx_0 = u_0 and
 // dz_0 = (rz_0 - z_0 dx_0) / x_0 (blocks below n0, one entry each); the
-// remaining blocks copy the link part u_L of the Schur solution into dy.
+// remaining blocks, if any, copy the link part u_L of the Schur solution into dy.
 __global__ __launch_bounds__(256) void k_solve_tail(int N, int n0, long long nl, long long f0first,
                                                     const double* __restrict__ part,
                                                     const double* __restrict__ F0,
@@ -1134,8 +1134,9 @@ void launch_schur_rhs(hipStream_t st, const BlockInfo* blk, int N, int nb, const
 }
 void launch_solve_tail(hipStream_t st, int N, int n0, long long nl, long long f0first,
                        const double* part, const double* F0, const double* u, long long x0off,
-                       long long mblk, double* gout, double* dx, const DzArgs& dzv, double* dy) {
-  long long nb = (nl + 255) / 256;
+                       long long mblk, double* gout, double* dx, const DzArgs& dzv, double* dy,
+                       bool copy) {
+  long long nb = copy ? (nl + 255) / 256 : 0;
   if (nb > 64) nb = 64;
   const int grid = n0 + (int)nb;
   if (grid > 0)

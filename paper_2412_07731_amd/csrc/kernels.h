@@ -142,8 +142,12 @@ struct BcrSolveArgs {
   BcrArgs c;
   const long long* loff;
   long long nl;
-  const double* s;       // right-hand side (exact pair layout, then n0 border values)
-  double* u;             // solution, same layout
+  const double* s;       // right-hand side before the blocks' part: exact pair layout, then ng
+  const BlockInfo* blk;  // the blocks' part: link and border sections of qn
+  const double* qn;
+  const double* rhx0;    // right-hand side of the border's x_0 entries
+  double* u;             // solution: exact pair layout, then n0 border values
+  double* dyl;           // its link and global rows again
   double* r; double* w; double* up;   // padded pair vectors, 16 tp per pair
   double* pb;            // border partials Z_j' w_j, 16*t0 per pair
   double* u0p;           // border solution, 16*t0
@@ -159,10 +163,8 @@ void launch_ceiling_mfma(hipStream_t st, bool fp32, int grid, int iters, double*
 void launch_ceiling_read(hipStream_t st, const double* buf, long long n, int grid, double* out);
 // grid workgroups of one factoring wave (and four MFMA-streaming waves if beside)
 void launch_ceiling_chol(hipStream_t st, bool beside, int grid, int iters, double* out);
-// pairs of two to four tiles (k_bcrn.hip): the reduction of T down to the final pair, and
-// the whole solve
+// pairs of two to four tiles (k_bcrn.hip): the reduction of T down to the final pair
 void launch_bcrn_reduce(hipStream_t st, const BcrArgs& c);
-void launch_bcrn_solve(hipStream_t st, const BcrSolveArgs& a);
 
 size_t chain_factor_smem(int lmax, int n0);
 void launch_chain_factor(hipStream_t st, const ChainArgs& c);
@@ -306,7 +308,8 @@ void launch_schur_rhs(hipStream_t st, const BlockInfo* blk, int N, int nb, const
                       double* s);
 void launch_solve_tail(hipStream_t st, int N, int n0, long long nl, long long f0first,
                        const double* part, const double* F0, const double* u, long long x0off,
-                       long long mblk, double* gout, double* dx, const DzArgs& dzv, double* dy);
+                       long long mblk, double* gout, double* dx, const DzArgs& dzv, double* dy,
+                       bool copy);
 // ex = rx - g - dz (+ q dx where b.q is given: the (x, x) block -Q of a
 // factorization with bounds); with bounds (b.ub) it also recovers b.ds, b.dw
 // from dx and forms w2 = D (dx dz / x - ds dw / s)
