@@ -90,6 +90,15 @@ __host__ __device__ inline bool link_is_row(const BlockInfo& b, int sec, int idx
   return sec < 2 || idx < b.ng;
 }
 
+// Requests kernel arguments at the start of a kernel.  The compiler loads them
+// where they are first used, and each 64-byte line of them is a round to memory.
+template <typename... A>
+__device__ __forceinline__ void touch_args(A... a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  (..., [](A x) { asm volatile("" ::"s"(x)); }(a));
+#endif
+}
+
 // D += A B for a 16x16x4 block: lane l supplies A[l%16][l/16] and B[l/16][l%16];
 // the result follows acc_index below.
 __device__ inline d4 mfma(double a, double b, d4 c) {

@@ -283,7 +283,7 @@ struct ahlp_problem_s {
   int tp = 0;                 // its tiles per pair side
   int t0 = 0, s00_chunk = 16, s00_parts = 0;
   double *BD = nullptr, *BC = nullptr, *BEt = nullptr, *FLi = nullptr, *FXL = nullptr,
-         *FXR = nullptr, *FGt = nullptr, *FLb = nullptr, *FLbi = nullptr, *s00part = nullptr;
+         *FXR = nullptr, *FGt = nullptr, *FLbi = nullptr, *s00part = nullptr;
   DevInfo* info = nullptr;   // lives in the last slot of the handle's own ws.scal
   bool factored = false;
   int fprec = AHLP_FP64;
@@ -639,7 +639,7 @@ BcrArgs bcr_args(ahlp_problem_t p) {
   c.Td = p->Td; c.To = p->To; c.E = p->E; c.S00 = p->S00; c.thrT = p->thrT;
   c.BD = p->BD; c.BC = p->BC; c.BEt = p->BEt;
   c.FLi = p->FLi; c.FXL = p->FXL; c.FXR = p->FXR; c.FGt = p->FGt;
-  c.FLb = p->FLb; c.FLbi = p->FLbi; c.s00part = p->s00part;
+  c.FLbi = p->FLbi; c.s00part = p->s00part;
   c.info = p->info;
   return c;
 }
@@ -1794,8 +1794,7 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
     for (double** v : {&p->BD, &p->BC, &p->FLi, &p->FXL, &p->FXR}) CHK(M.alloc(v, Pt * tp * tp * 256));
     CHK(M.alloc(&p->BEt, Pt * tp * T0 * 256));
     CHK(M.alloc(&p->FGt, Pt * tp * T0 * 256));
-    CHK(M.alloc(&p->s00part, (long long)(p->s00_parts + 1) * std::max(p->t0 * p->t0, 1) * 256));
-    CHK(M.alloc(&p->FLb, (long long)std::max(p->t0 * p->t0, 1) * 256));
+    CHK(M.alloc(&p->s00part, bcr_part_doubles(P, p->t0, p->tp, p->s00_parts)));
     CHK(M.alloc(&p->FLbi, (long long)std::max(p->t0 * p->t0, 1) * 256));
     set_bcr_smem_limits();
     CHK(M.alloc(&p->segout, 1));

@@ -23,70 +23,46 @@
 //                             and border rows (transposed, t0 tiles)
 //   FLi[o], FXL[o], FXR[o]    L_o^-1, X_L, X_R of the eliminated pair o
 //   FGt[o][q]                 Z' of pair o (t0 tiles), the final pair included
-//   FLb, FLbi                 border factor and its inverse, tiles (r, c) at c*t0 + r
-// Wide levels (more than TAIL_WAVES eliminations) run as one launch per level
-// (both eliminations next to an even pair and its update in one workgroup); the
-// narrow levels and the final pair run inside one workgroup.  Every sum is
-// taken in a fixed order.  The solve is in k_bcrs.hip.
+//   FLbi                      inverse of the border factor Lb, tiles (r, c) at c*t0 + r
+//
+// What a level costs is a chain: the factor of a 16x16 tile (1 us), its products
+// and the updates, a few hundred cycles each; a launch or a round of memory per
+// level costs more than that.  So a workgroup takes a group of 2^lev neighbouring
+// positions into LDS and eliminates all of them but the first (the separator)
+// over lev levels: the factors one wave each, then the products and then the
+// updates as one tile per wave, while four waves that have no factor sum Z'Z of
+// the level before.  A group leaves its separator's updated tiles in BD, BC, BEt
+// and a record of what the next stage adds: the sum of its Z'Z (with its child
+// groups' sums) and its terms of the next group's separator.  The last stage, one
+// group, eliminates its first position too and factorizes the border.  A group's
+// tiles must fit in LDS: 16 positions with a border of up to one tile, 8 with up
+// to four.
+// Measured against a launch per level, a single workgroup for the last 16 pairs
+// through memory and three launches for the border, kernel time in us per
+// factorization: 7 pairs, border 8: 37 -> 20; 63 pairs, border 22: 93 -> 49; 511
+// pairs, border 32: 115 -> 73; 2189 pairs, border 12: 128 -> 83.  A level takes 5000
+// to 6000 cycles, 3000 of them the factor; a stage another 5 us for its first round
+// of memory and the first fetch of its instructions.
+//
+// Every sum is taken in a fixed order.  The solve is in k_bcrs.hip.
 #include "common.h"
 #include "kernels.h"
 #include "tile_chol.h"
 #include "tile_ops.h"
+#include <algorithm>
 
 namespace ahlp {
 
 namespace {
 
 constexpr int BT_MAXT0 = 4;      // border tiles (n0 <= 64)
-constexpr int TAIL_WAVES = 8;    // waves of the single-workgroup factor tail
-// LDS tiles of the eliminating kernels are column-major with leading
-// dimension 17: accumulator-layout writes and B-operand reads walk a tile by
-// columns across the lanes, which with 16 would put 16 lanes in one bank
+constexpr int FW = 8;            // waves of a group's workgroup
+constexpr int ZW = 4;            // its last waves, which sum Z'Z
+// LDS tiles are column-major with leading dimension 17: accumulator-layout
+// writes and B-operand reads walk a tile by columns across the lanes, which
+// with 16 would put 16 lanes in one bank
 constexpr int PLD = TS + 1, PTE = TS * PLD;
-constexpr int ELIM_LDS = 2 * PTE;   // doubles of LDS per eliminating wave: the tile, L^-1
-
-// ---------------------------------------------------------------- factor
-// Working tiles from the assembled parts (one wave per tile).
-__global__ __launch_bounds__(256) void k_bcr_init(BcrArgs c) {
-  const int per = 2 + c.t0;
-  const long long wt = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wt >= (long long)c.P * per) return;
-  const int j = (int)(wt / per), kind = (int)(wt % per), lj = c.l[j];
-  if (kind == 0) {
-    acc_store(c.BD + (long long)j * 256, acc_load_exact(c.Td + c.tdoff[j], lj, lj, lj, true));
-  } else if (kind == 1) {
-    if (j + 1 < c.P) {
-      const int ln = c.l[j + 1];
-      acc_store(c.BC + (long long)j * 256, acc_load_exact(c.To + c.tooff[j], ln, lj, ln, false));
-    }
-  } else {
-    const int q = kind - 2;
-    acc_store(c.BEt + ((long long)j * c.t0 + q) * 256,
-              acc_load_exact_t(c.E + c.eoff[j] + 16LL * q * lj, min(16, c.n0 - 16 * q), lj, lj));
-  }
-}
-
-// Tile operands in registers: ld_a(X) gives X as the A operand of X*Y or
-// X*Y' (and Y as the B operand of X*Y'); ld_b(X) gives X as the B operand of
-// Y*X or the A/B operand of X'*Y.  All operands of a step are loaded before
-// any of them is used, so a step waits on memory once.
-struct T4 { double v[4]; };
-__device__ __forceinline__ T4 ld_a(const double* __restrict__ t) {
-  const int lane = threadIdx.x & 63;
-  T4 o;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) o.v[s] = t[64 * s + lane];
-  return o;
-}
-__device__ __forceinline__ T4 ld_b(const double* __restrict__ t) {
-  const int lane = threadIdx.x & 63;
-  const int idx = (lane & 15) * TS + (lane >> 4);
-  T4 o;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) o.v[s] = t[idx + 4 * s];
-  return o;
-}
-__device__ __forceinline__ T4 t4_zero() { return T4{{0.0, 0.0, 0.0, 0.0}}; }
+struct T4 { double v[4]; };   // a tile as a matrix operand
 // the same operations on padded LDS tiles (element col 16 + row at col 17 + row)
 __device__ __forceinline__ int pe(int e) { return e + (e >> 4); }
 __device__ __forceinline__ void acc_store_l(double* t, const d4& a) {
@@ -121,195 +97,361 @@ __device__ __forceinline__ d4 mm(d4 acc, const T4& a, const T4& b, double alpha)
   return acc;
 }
 
-// Eliminate pair o (active neighbours L if needXL, R if hasR): factor its
-// working diagonal and form X_L = L_o^-1 T'[o,L], X_R = L_o^-1 T'[R,o]' and
-// G_q = (L_o^-1 E'_o)' (accumulator layout).  scr: ELIM_LDS doubles of this
-// wave; L_o^-1 is left in scr + PTE (padded).  Returns replaced pivots.
-__device__ int elim_core(const BcrArgs& c, long long o, long long L, bool needXL, bool hasR,
-                         double* scr, d4& XL, d4& XR, d4* G) {
-  double* cur = scr;
-  double* Li = scr + PTE;
-  const double* __restrict__ BC = c.BC;
-  const double* __restrict__ BEt = c.BEt;
-  const d4 D = acc_load(c.BD + o * 256);
-  const double thr = c.thrT[o];
-  T4 cl = t4_zero(), cr = t4_zero(), et[BT_MAXT0];
-  if (needXL) cl = ld_b(BC + L * 256);
-  if (hasR) cr = ld_a(BC + o * 256);
-#pragma unroll
-  for (int q = 0; q < BT_MAXT0; ++q) et[q] = q < c.t0 ? ld_a(BEt + (o * c.t0 + q) * 256) : t4_zero();
-  acc_store_l(cur, D);
-  wave_order();
-  const int cnt = wave_chol_tile<double, PLD>(cur, cur, Li, thr, nullptr);
-  const T4 li = ld_a_l(Li);
-  XL = needXL ? mm(acc_zero(), li, cl, 1.0) : acc_zero();
-  XR = hasR ? mm(acc_zero(), li, cr, 1.0) : acc_zero();
-#pragma unroll
-  for (int q = 0; q < BT_MAXT0; ++q) G[q] = q < c.t0 ? mm(acc_zero(), et[q], li, 1.0) : acc_zero();
-  return cnt;
+
+// ---------------------------------------------------------------- factor
+int border_low(int t0) { return t0 * (t0 + 1) / 2; }
+// positions of a group with this border
+int group_size(int t0) { return t0 <= 1 ? 16 : 8; }
+size_t group_smem(int t0) {
+  return ((size_t)group_size(t0) * (2 + t0) + (1 + t0) + FW) * PTE * sizeof(double);
 }
 
-// store the factor of pair o (L^-1 from its padded LDS tile)
-__device__ void store_factor(const BcrArgs& c, long long o, const double* Li, const d4& XL,
-                             const d4& XR, bool hasR, const d4* G) {
-  tile_copy_l(c.FLi + o * 256, Li);
-  acc_store(c.FXL + o * 256, XL);
-  if (hasR) acc_store(c.FXR + o * 256, XR);
-#pragma unroll
-  for (int q = 0; q < BT_MAXT0; ++q)
-    if (q < c.t0) acc_store(c.FGt + (o * c.t0 + q) * 256, G[q]);
-}
+// Group blockIdx.x of 2^lev positions at level lvl (n positions in all); LAST:
+// the only one, down to the final pair and the border.  Records, one per group,
+// at c.s00part: Z'Z (lower tiles, row by row), then the terms of the next
+// separator's diagonal and border tiles.  slot0: this stage's first, prev: that
+// of the stage before.  LAST with n = 0 is the border alone, its record prev
+// holding only the sum of Z'Z (if kids).
+// Code that runs for the first time costs its size (about a cycle per two bytes),
+// so all factors of the kernel, the border's included, are the same instructions:
+// the steps are lev levels, then in the last stage the final pair and the border's
+// t0 tile columns.
+template <int GS, bool LAST>
+__global__ __launch_bounds__(64 * FW) void k_bcr_group(BcrArgs c, int lvl, int n, int lev, int slot0, int prev,
+                                                     int kids) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double s_thr[GS + 1];
+  touch_args(c.l, c.Td, c.thrT, c.FLi, c.s00part, lvl, kids);
+  double* lds = reinterpret_cast<double*>(smem_raw);
+  const int t0 = c.t0, per = 2 + t0, nz = t0 * (t0 + 1) / 2, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gs = 1 << lev, k0 = LAST ? 0 : (int)blockIdx.x << lev;
+  const bool right = !LAST && k0 + gs < n;    // there is a next separator
+  const long long rec = (long long)(LAST && n == 0 ? nz : nz + 1 + t0) * 256;
+  const int inv = per == 2 ? 32769 : per == 3 ? 21846 : per == 4 ? 16385 : per == 5 ? 13108 : 10923;
+  auto div_per = [&](int t) { return (t * inv) >> 16; };   // t / per for t < 2^12
+  auto tile = [&](int i, int kind) { return lds + (i * per + kind) * PTE; };   // 0: D, 1: C, 2 + q: E_q
+  double* sep = lds + GS * per * PTE;                                          // next separator's D, E_q
+  double* scr = sep + (1 + t0) * PTE;                                          // a tile per wave
 
-// One wide level (n active pairs): a workgroup of two waves per even position
-// k.  Wave 0 eliminates the right neighbour o_r (and stores its factor: every
-// odd pair has exactly one left neighbour), wave 1 eliminates the left one
-// o_l again; both leave their products in LDS and the update of the even pair
-// is split: wave 0 the diagonal and the new coupling, wave 1 the border rows.
-__global__ __launch_bounds__(128) void k_bcr_level(BcrArgs c, int lvl, int n) {
-  __shared__ double scr[2][ELIM_LDS];
-  __shared__ double xr_[2][(2 + BT_MAXT0) * PTE];   // per wave: X_L, X_R, G_q (padded)
-  const int wave = threadIdx.x >> 6, k = 2 * blockIdx.x;
-  const long long s = 1LL << lvl, e = k * s;
-  const bool hl = k >= 1, hr = k + 1 < n, hrr = k + 2 < n;
-  int cnt = 0;
-  // the even pair's own tiles, loaded before the elimination
-  d4 Dp = acc_zero(), etp[BT_MAXT0];
-#pragma unroll
-  for (int q = 0; q < BT_MAXT0; ++q) etp[q] = acc_zero();
-  if (wave == 0) {
-    Dp = acc_load(c.BD + e * 256);
-  } else {
-#pragma unroll
-    for (int q = 0; q < BT_MAXT0; ++q)
-      if (q < c.t0) etp[q] = acc_load(c.BEt + (e * c.t0 + q) * 256);
-  }
-  const bool mine = wave == 0 ? hr : hl;
-  if (mine) {
-    d4 XL, XR, G[BT_MAXT0];
-    const long long o = wave == 0 ? (k + 1) * s : (k - 1) * s;
-    const bool needXL = wave == 0, hasR = wave == 0 ? hrr : true;
-    cnt = elim_core(c, o, e, needXL, hasR, scr[wave], XL, XR, G);
-    double* x = xr_[wave];
-    acc_store_l(x, XL);
-    acc_store_l(x + PTE, XR);
-#pragma unroll
-    for (int q = 0; q < BT_MAXT0; ++q)
-      if (q < c.t0) acc_store_l(x + (2 + q) * PTE, G[q]);
-    if (wave == 0) store_factor(c, o, scr[0] + PTE, XL, XR, hasR, G);
-  }
-  __syncthreads();
-  const double* xo = xr_[0];   // products of o_r
-  const double* xl = xr_[1];   // products of o_l
-  if (wave == 0) {
-    d4 D = Dp;
-    const T4 a = hl ? ld_b_l(xl + PTE) : t4_zero();   // X_R(o_l)
-    const T4 b = hr ? ld_b_l(xo) : t4_zero();         // X_L(o_r)
-    if (hl) D = mm(D, a, a, -1.0);
-    if (hr) D = mm(D, b, b, -1.0);
-    acc_store(c.BD + e * 256, D);
-    if (hr && hrr) acc_store(c.BC + e * 256, mm(acc_zero(), ld_b_l(xo + PTE), b, -1.0));
-  } else {
-    d4 et[BT_MAXT0];
-#pragma unroll
-    for (int q = 0; q < BT_MAXT0; ++q) et[q] = etp[q];
-    const T4 a = hl ? ld_b_l(xl + PTE) : t4_zero();
-    const T4 b = hr ? ld_b_l(xo) : t4_zero();
-#pragma unroll
-    for (int q = 0; q < BT_MAXT0; ++q)
-      if (q < c.t0) {
-        if (hl) et[q] = mm(et[q], ld_a_l(xl + (2 + q) * PTE), a, -1.0);
-        if (hr) et[q] = mm(et[q], ld_a_l(xo + (2 + q) * PTE), b, -1.0);
-        acc_store(c.BEt + (e * c.t0 + q) * 256, et[q]);
-      }
-  }
-  // o_l is also the right neighbour of the even pair k - 2: its pivots are
-  // counted there
-  if (threadIdx.x == 0 && cnt) atomicAdd(&c.info->pivots, cnt);
-}
-
-// Narrow levels from lvl (n active pairs) down to one pair, then the final
-// pair; one workgroup of TAIL_WAVES waves: odd pairs eliminated (factor
-// stored), barrier, even pairs updated from the stored products, barrier.
-__global__ __launch_bounds__(64 * TAIL_WAVES) void k_bcr_tail(BcrArgs c, int lvl, int n) {
-  __shared__ double scr[TAIL_WAVES][ELIM_LDS];
-  const int wave = threadIdx.x >> 6;
-  int cnt = 0;
-  for (; n > 1; ++lvl, n = (n + 1) / 2) {
-    const long long s = 1LL << lvl;
-    for (int w = wave; w < n / 2; w += TAIL_WAVES) {
-      const int k = 2 * w + 1;
-      const bool hasR = k + 1 < n;
-      d4 XL, XR, G[BT_MAXT0];
-      cnt += elim_core(c, k * s, (k - 1) * s, true, hasR, scr[wave], XL, XR, G);
-      store_factor(c, k * s, scr[wave] + PTE, XL, XR, hasR, G);
-      wave_order();
-    }
-    __syncthreads();
-    for (int w = wave; w < (n + 1) / 2; w += TAIL_WAVES) {
-      const int k = 2 * w;
-      const long long e = k * s, ol = (k - 1) * s, orr = (k + 1) * s;
-      const bool hl = k >= 1, hr = k + 1 < n, hrr = k + 2 < n;
-      const double* __restrict__ FXL = c.FXL;
-      const double* __restrict__ FXR = c.FXR;
-      const double* __restrict__ FGt = c.FGt;
-      d4 D = acc_load(c.BD + e * 256);
-      const T4 a = hl ? ld_b(FXR + ol * 256) : t4_zero();
-      const T4 b = hr ? ld_b(FXL + orr * 256) : t4_zero();
-      const T4 xrr = (hr && hrr) ? ld_b(FXR + orr * 256) : t4_zero();
-      d4 et[BT_MAXT0];
-      T4 gl[BT_MAXT0], gr[BT_MAXT0];
-#pragma unroll
-      for (int q = 0; q < BT_MAXT0; ++q) {
-        const bool on = q < c.t0;
-        et[q] = on ? acc_load(c.BEt + (e * c.t0 + q) * 256) : acc_zero();
-        gl[q] = (on && hl) ? ld_a(FGt + (ol * c.t0 + q) * 256) : t4_zero();
-        gr[q] = (on && hr) ? ld_a(FGt + (orr * c.t0 + q) * 256) : t4_zero();
-      }
-      if (hl) D = mm(D, a, a, -1.0);
-      if (hr) D = mm(D, b, b, -1.0);
-      acc_store(c.BD + e * 256, D);
-      if (hr && hrr) acc_store(c.BC + e * 256, mm(acc_zero(), xrr, b, -1.0));
-#pragma unroll
-      for (int q = 0; q < BT_MAXT0; ++q)
-        if (q < c.t0) {
-          if (hl) et[q] = mm(et[q], gl[q], a, -1.0);
-          if (hr) et[q] = mm(et[q], gr[q], b, -1.0);
-          acc_store(c.BEt + (e * c.t0 + q) * 256, et[q]);
+  // The group's tiles, NT of the waves' turns: where they are by lane (one wait for
+  // the offsets), then all of them (one wait), then to LDS.  Element (a, b) at
+  // src + a sa + b sb for a < rows, b < cols; more: the separator's terms of the
+  // group on its left.
+  constexpr int NT = 48 / FW;
+  unsigned long long my_src = 0, my_more = 0;
+  int my_sa = 1, my_sb = 16, my_rows = 16, my_cols = 16;
+  {
+    const int t = wave + FW * lane, i = div_per(t), kind = t - i * per, k = k0 + i;
+    const double* src = nullptr;
+    if (lane < NT && i < gs && k < n && !(kind == 1 && k + 1 >= n)) {
+      const long long j = (long long)k << lvl;
+      if (lvl == 0) {
+        const long long off = (kind == 0 ? c.tdoff : kind == 1 ? c.tooff : c.eoff)[j];
+        const int lj = c.l[j];
+        src = (kind == 0 ? c.Td : kind == 1 ? c.To : c.E) + off;
+        my_cols = my_sb = my_rows = lj;
+        if (kind == 1) my_sb = my_rows = c.l[j + 1];
+        if (kind > 1) {
+          src += 16 * (kind - 2) * lj;
+          my_rows = c.n0 - 16 * (kind - 2);
+          my_sa = lj;
+          my_sb = 1;
         }
+      } else {
+        src = kind == 0 ? c.BD + j * 256 : kind == 1 ? c.BC + j * 256 : c.BEt + (j * t0 + kind - 2) * 256;
+        if (k > 0 && kind != 1)
+          my_more = (unsigned long long)(c.s00part + (prev + k - 1) * rec + (nz + (kind == 0 ? 0 : kind - 1)) * 256);
+      }
     }
-    __syncthreads();
+    my_src = (unsigned long long)src;
   }
-  if (n == 1 && wave == 0) {
-    d4 XL, XR, G[BT_MAXT0];
-    cnt += elim_core(c, 0, 0, false, false, scr[0], XL, XR, G);
-    tile_copy_l(c.FLi, scr[0] + PTE);
+  const auto lane_ptr = [](unsigned long long p, int u) {
+    return reinterpret_cast<const double*>(
+        (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)p, u) |
+        (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(p >> 32), u) << 32);
+  };
+  double v[NT][4], add[NT][4];
+  const int a15 = lane & 15, b15 = lane >> 4;
 #pragma unroll
-    for (int q = 0; q < BT_MAXT0; ++q)
-      if (q < c.t0) acc_store(c.FGt + q * 256, G[q]);
+  for (int u = 0; u < NT; ++u) {
+    const double* src = lane_ptr(my_src, u);
+    if (!src) continue;
+    const int sa = __builtin_amdgcn_readlane(my_sa, u), sb = __builtin_amdgcn_readlane(my_sb, u);
+    const int rows = __builtin_amdgcn_readlane(my_rows, u), cols = __builtin_amdgcn_readlane(my_cols, u);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int b = 4 * s + b15;
+      const int at = a15 < rows && b < cols ? a15 * sa + b * sb : 0;
+      v[u][s] = src[at];
+    }
+    const double* more = lane_ptr(my_more, u);
+    if (more)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) add[u][s] = more[64 * s + lane];
   }
-  if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(&c.info->pivots, cnt);
+  if ((int)threadIdx.x < gs && k0 + (int)threadIdx.x < n)
+    s_thr[threadIdx.x] = c.thrT[(long long)(k0 + threadIdx.x) << lvl];
+  for (int e = threadIdx.x; e < (1 + t0) * PTE; e += blockDim.x) sep[e] = 0.0;
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    const int t = wave + FW * u;
+    if (t >= GS * per || !lane_ptr(my_src, u)) continue;
+    const int rows = __builtin_amdgcn_readlane(my_rows, u), cols = __builtin_amdgcn_readlane(my_cols, u);
+    const bool diag = t == div_per(t) * per, more = lane_ptr(my_more, u) != nullptr;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int b = 4 * s + b15;
+      double x = a15 < rows && b < cols ? v[u][s] : 0.0;
+      if (more) x += add[u][s];
+      lds[t * PTE + pe(64 * s + lane)] = diag && b == a15 && b >= cols ? 1.0 : x;
+    }
+  }
+  lds_barrier();
+
+  // Z'Z: the last ZW waves share its tiles, or with one tile the pairs
+  d4 zz[3] = {acc_zero(), acc_zero(), acc_zero()};
+  const int zw = wave - (FW - ZW);
+  auto zz_tile = [&](int z) { return nz == 1 ? (z == 0 ? 0 : nz) : zw + ZW * z; };
+  // of the positions i0, i0 + step, ..: those eliminated together
+  auto zz_level = [&](int i0, int step) {
+    if (zw < 0) return;
+    int u = 0;
+    for (int i = i0; i < gs && k0 + i < n; i += step, ++u) {
+      if (nz == 1 && u % ZW != zw) continue;
+#pragma unroll
+      for (int z = 0; z < 3; ++z) {
+        const int t = zz_tile(z);
+        if (t >= nz) continue;
+        const int q = t >= 6 ? 3 : t >= 3 ? 2 : t >= 1 ? 1 : 0, q2 = t - q * (q + 1) / 2;
+        zz[z] = mm(zz[z], ld_a_l(tile(i, 2 + q)), ld_a_l(tile(i, 2 + q2)), 1.0);
+      }
+    }
+  };
+  if (zw >= 0) {   // the child groups' sums
+    if (lvl > 0) kids = min(n, k0 + gs) - k0;
+#pragma unroll
+    for (int z = 0; z < 3; ++z) {
+      const int t = zz_tile(z);
+      if (t >= nz) continue;
+#pragma unroll 4
+      for (int g = nz == 1 ? zw : 0; g < kids; g += nz == 1 ? ZW : 1)
+        zz[z] += acc_load(c.s00part + (prev + k0 + g) * rec + t * 256);
+    }
+  }
+  // their sum over the waves where those shared the pairs: to the first of them
+  auto zz_finish = [&]() {
+    if (nz != 1) return;
+    lds_barrier();
+    if (zw >= 0) acc_store_l(scr + wave * PTE, zz[0]);
+    lds_barrier();
+    if (zw == 0)
+      for (int w = 1; w < ZW; ++w)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) zz[0][s] += scr[(wave + w) * PTE + pe(acc_index<double>(lane, s))];
+  };
+  auto zz_store = [&](double* dst) {
+    if (zw < 0 || (nz == 1 && zw > 0)) return;
+#pragma unroll
+    for (int z = 0; z < 3; ++z)
+      if (zz_tile(z) < nz) acc_store(dst + zz_tile(z) * 256, zz[z]);
+  };
+
+  // the border's tiles, over the group's once those are done with: B (r, c) at
+  // c t0 + r, its inverse X and the inverted diagonal tiles Ld
+  double* B = lds + nz * PTE;
+  double* X = B + t0 * t0 * PTE;
+  double* Ld = X + t0 * t0 * PTE;
+  const unsigned long long neg = LAST ? (c.ng >= 64 ? ~0ull : ((1ull << c.ng) - 1ull)) : 0ull;
+  const int fin = LAST && n > 0 ? 1 : 0, first_b = lev + fin, steps = first_b + (LAST ? t0 : 0);
+  int cnt = 0;
+  for (int v0 = 0; v0 < steps; ++v0) {
+    const int p = v0 - first_b;                       // border: the tile column
+    const bool border = LAST && p >= 0, last_pair = LAST && v0 == lev && fin;
+    const int d = last_pair || border ? gs : 1 << v0, nel = last_pair || border ? 1 : gs / (2 * d);
+    if (LAST && p == 0) {
+      // all pairs are eliminated: the last one's Z'Z and the border's tiles,
+      // B = -(S00 - sum Z'Z), the identity on the padding
+      if (fin) zz_level(0, gs);
+      zz_finish();
+      lds_barrier();
+      zz_store(lds);
+      lds_barrier();
+      const int n0 = c.n0;
+      for (int idx = threadIdx.x; idx < 256 * t0 * t0; idx += blockDim.x) {
+        const int tl = idx >> 8, e = idx & 255, r1 = tl % t0, c1 = tl / t0;
+        const int i = 16 * r1 + (e & 15), j = 16 * c1 + (e >> 4);
+        if (r1 < c1) continue;
+        double b = (i == j) ? 1.0 : 0.0;
+        if (i < n0 && j < n0) b = -(c.S00[i + j * n0] - lds[(r1 * (r1 + 1) / 2 + c1) * 256 + e]);
+        B[tl * PTE + pe(e)] = b;
+      }
+      lds_barrier();
+      if (wave == 0) {
+        double md = 0.0;
+        if (lane < n0) md = fabs(B[((lane >> 4) * t0 + (lane >> 4)) * PTE + (lane & 15) * (PLD + 1)]);
+        for (int off = 32; off > 0; off >>= 1) md = fmax(md, __shfl_xor(md, off));
+        if (lane == 0) s_thr[GS] = PIVOT_REL * md;
+        wave_order();
+      }
+    }
+    auto pos = [&](int w) { return last_pair ? 0 : d * (2 * w + 1); };
+    if (wave < nel) {
+      const int i = pos(wave);
+      if (border || k0 + i < n) {
+        double* D = border ? B + (p * t0 + p) * PTE : tile(i, 0);
+        double* Li = border ? Ld + p * PTE : scr + wave * PTE;
+        const double thr = s_thr[border ? GS : i];
+        const unsigned np = border ? (unsigned)((neg >> (16 * p)) & 0xFFFFull) : 0u;
+        cnt += wave_chol_tile<double, PLD, LAST, false>(D, nullptr, Li, thr, np);
+        if (!border) tile_copy_l(c.FLi + ((long long)(k0 + i) << lvl) * 256, Li);
+      }
+    } else if (v0 > 0 && !border) {
+      zz_level(last_pair ? gs / 2 : d / 2, last_pair ? gs : d);
+    }
+    lds_barrier();
+    if (border) {
+      const unsigned np = (unsigned)((neg >> (16 * p)) & 0xFFFFull);
+      const int rr = p + 1 + wave;
+      if (rr < t0) {   // L_rp = B_rp L_pp^-T S_p
+        double* t = B + (p * t0 + rr) * PTE;
+        d4 x = mm(acc_zero(), ld_a_l(t), ld_a_l(Ld + p * PTE), 1.0);
+        if ((np >> a15) & 1u) x = -x;
+        wave_order();
+        acc_store_l(t, x);
+      }
+      lds_barrier();
+      int u = 0;
+      for (int r1 = p + 1; r1 < t0; ++r1)
+        for (int c1 = p + 1; c1 <= r1; ++c1, ++u) {
+          if (u % FW != wave) continue;
+          double* t = B + (c1 * t0 + r1) * PTE;
+          d4 x;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[s] = t[pe(acc_index<double>(lane, s))];
+          const T4 l = ld_a_l(B + (p * t0 + r1) * PTE), m = ld_a_l(B + (p * t0 + c1) * PTE);
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            x = mfma(((np >> (4 * s + (lane >> 4))) & 1u) ? l.v[s] : -l.v[s], m.v[s], x);
+          acc_store_l(t, x);
+        }
+      lds_barrier();
+      continue;
+    }
+    // X_L to the place of D, X_R to that of the coupling, Z' to that of E'
+    for (int t = wave; t < nel * per; t += FW) {
+      const int w = div_per(t), kind = t - w * per, i = pos(w);
+      if (k0 + i >= n || (kind == 1 && k0 + i + d >= n) || (last_pair && kind < 2)) continue;
+      const long long o = (long long)(k0 + i) << lvl;
+      const T4 li = ld_a_l(scr + w * PTE);
+      T4 x, y;
+      double* dst;
+      if (kind == 0) {
+        x = li;
+        y = ld_b_l(tile(i - d, 1));
+        dst = c.FXL + o * 256;
+      } else if (kind == 1) {
+        x = li;
+        y = ld_a_l(tile(i, 1));
+        dst = c.FXR + o * 256;
+      } else {
+        x = ld_a_l(tile(i, kind));
+        y = li;
+        dst = c.FGt + (o * t0 + kind - 2) * 256;
+      }
+      const d4 z = mm(acc_zero(), x, y, 1.0);
+      acc_store_l(tile(i, kind), z);
+      acc_store(dst, z);
+    }
+    lds_barrier();
+    if (!last_pair) {
+      // the remaining positions, and last the next separator
+      const int ne = nel + (right ? 1 : 0);
+      for (int t = wave; t < ne * per; t += FW) {
+        const int w = div_per(t), kind = t - w * per, i = 2 * d * w;
+        const bool next = w == nel;
+        if (k0 + i >= n) continue;
+        const bool hl = i > 0, hr = !next && k0 + i + d < n;
+        double* dst = !next ? tile(i, kind) : sep + (kind == 0 ? 0 : kind - 1) * PTE;
+        d4 x = acc_zero();
+        if (kind != 1)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[s] = dst[pe(acc_index<double>(lane, s))];
+        // kind 0: D - X_R'X_R - X_L'X_L, 1: -X_R'X_L, 2 + q: E'_q - Z'X_R - Z'X_L
+        if (hl && kind != 1) {
+          const T4 y = ld_b_l(tile(i - d, 1));
+          x = mm(x, kind == 0 ? y : ld_a_l(tile(i - d, kind)), y, -1.0);
+        }
+        if (kind == 1 && !(hr && k0 + i + 2 * d < n)) continue;
+        if (hr) {
+          const T4 y = ld_b_l(tile(i + d, 0));
+          x = mm(x, kind == 0 ? y : kind == 1 ? ld_b_l(tile(i + d, 1)) : ld_a_l(tile(i + d, kind)), y, -1.0);
+        }
+        acc_store_l(dst, x);
+      }
+      lds_barrier();
+    }
+  }
+  if (lane == 0 && cnt) atomicAdd(&c.info->pivots, cnt);
+  if constexpr (!LAST) {
+    zz_level(gs / 2, gs);
+    zz_finish();
+    double* R = c.s00part + (slot0 + blockIdx.x) * rec;
+    zz_store(R);
+    const long long j = (long long)k0 << lvl;
+    for (int t = wave; t < per; t += FW) {
+      if (t == 1 && !right) continue;
+      tile_copy_l(t == 0 ? c.BD + j * 256 : t == 1 ? c.BC + j * 256 : c.BEt + (j * t0 + t - 2) * 256, tile(0, t));
+    }
+    if (right)
+      for (int t = wave; t < 1 + t0; t += FW) tile_copy_l(R + (nz + t) * 256, sep + t * PTE);
+  } else if (wave < t0) {
+    // the inverse of the border's factor, a tile column a wave
+    const int cc = wave;
+    for (int r1 = 0; r1 < t0; ++r1) {
+      double* x = X + (cc * t0 + r1) * PTE;
+      if (r1 > cc) {
+        d4 a = acc_zero();
+        for (int q = cc; q < r1; ++q)
+          a = mm(a, ld_a_l(B + (q * t0 + r1) * PTE), ld_b_l(q == cc ? Ld + cc * PTE : X + (cc * t0 + q) * PTE), 1.0);
+        acc_store_l(scr + wave * PTE, a);
+        wave_order();
+        const d4 y = mm(acc_zero(), ld_a_l(Ld + r1 * PTE), ld_b_l(scr + wave * PTE), -1.0);
+        wave_order();
+        acc_store_l(x, y);
+        wave_order();
+      }
+      double* dst = c.FLbi + (cc * t0 + r1) * 256;
+      if (r1 >= cc) tile_copy_l(dst, r1 == cc ? Ld + cc * PTE : x);
+      else
+#pragma unroll
+        for (int s = 0; s < 4; ++s) dst[64 * s + lane] = 0.0;
+    }
+  }
 }
 
-// Partial sums of Z_j'Z_j = FGt_j FGt_j' over contiguous chunks of pairs, one
-// wave per (chunk, border tile (q, q2)).  Pair j's tile (q, c) of FGt is at
-// (j tp + c) t0 + q, so u = j tp + c runs over a chunk's tiles in order.
+// Partial sums of Z_j'Z_j = FGt_j FGt_j' (lower tiles) over contiguous chunks of
+// pairs, one wave per (chunk, border tile (q, q2)), for pairs of several tiles.
+// Pair j's tile (q, c) of FGt is at (j tp + c) t0 + q, so u = j tp + c runs over a
+// chunk's tiles in order.
 __global__ __launch_bounds__(64) void k_bcr_s00_partial(BcrArgs c, int chunk) {
-  const int t0 = c.t0, tp = c.tp, nt = t0 * t0;
-  const int part = blockIdx.x / nt, t = blockIdx.x % nt, q = t / t0, q2 = t % t0;
-  const long long u0 = (long long)part * chunk * tp;
-  const long long u1 = (long long)min(c.P, (part + 1) * chunk) * tp;
+  const int t0 = c.t0, nz = t0 * (t0 + 1) / 2;
+  const int part = blockIdx.x / nz, t = blockIdx.x % nz;
+  const int q = t >= 6 ? 3 : t >= 3 ? 2 : t >= 1 ? 1 : 0, q2 = t - q * (q + 1) / 2;
+  const long long u0 = (long long)part * chunk * c.tp;
+  const long long u1 = (long long)min(c.P, (part + 1) * chunk) * c.tp;
   const double* __restrict__ G = c.FGt;
   d4 acc = acc_zero();
 #pragma unroll 4
   for (long long u = u0; u < u1; ++u)
     acc = mma_xyt(acc, G + (u * t0 + q) * 256, G + (u * t0 + q2) * 256, 1.0);
-  acc_store(c.s00part + ((long long)part * nt + t) * 256, acc);
+  acc_store(c.s00part + ((long long)part * nz + t) * 256, acc);
 }
 
 // Sum of the chunk partials, one thread per element, chunks in order; the
 // sum goes after the nparts partials.
 __global__ __launch_bounds__(256) void k_bcr_s00_sum(BcrArgs c, int nparts) {
-  const int n = c.t0 * c.t0 * 256;
+  const int n = c.t0 * (c.t0 + 1) / 2 * 256;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n) return;
   const double* src = c.s00part + idx;
@@ -322,71 +464,40 @@ __global__ __launch_bounds__(256) void k_bcr_s00_sum(BcrArgs c, int nparts) {
   c.s00part[(long long)nparts * n + idx] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
-// Border: B = -(S00 - sum of Z_j'Z_j) in t0 x t0 tiles (all four waves), then
-// one wave: blocked Cholesky with tile inverses and the block inverse of the
-// factor.  With global rows in the border (c.ng > 0) B is quasi-definite
-// (negative definite on the global rows, positive on x_0) and the
-// factorization is the signed one, B = Lb T Lb' with T = diag(-I, I).
-__global__ __launch_bounds__(256) void k_bcr_border(BcrArgs c, int nparts) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int n0 = c.n0, t0 = c.t0, lane = threadIdx.x & 63;
-  double* B = reinterpret_cast<double*>(smem_raw);   // t0*t0 tiles (r, c) at c*t0 + r
-  double* X = B + t0 * t0 * 256;                      // inverse tiles
-  double* Ld = X + t0 * t0 * 256;                     // inverted diagonal tiles
-  double* tmp = Ld + t0 * 256;
-  double* xbuf = tmp + 256;
-  __shared__ double s_max;
-  for (int idx = threadIdx.x; idx < 256 * t0 * t0; idx += blockDim.x) {
-    const int tile = idx / 256, e = idx % 256;
-    const int r = tile % t0, cc = tile / t0;
-    const int i = 16 * r + (e & 15), j = 16 * cc + (e >> 4);
-    double v;
-    if (i < n0 && j < n0) {
-      const double zz = nparts > 0 ? c.s00part[((long long)nparts * t0 * t0 + r * t0 + cc) * 256 + e] : 0.0;
-      v = -(c.S00[i + j * n0] - zz);
-    } else {
-      v = (i == j) ? 1.0 : 0.0;
-    }
-    B[idx] = v;
+// The stages of P pairs: as few as the groups allow, the levels before the last
+// split evenly, the fewer first, where there are most groups to fill the chip.
+struct Stages { int count, lvl[32], n[32], lev[32], slot[33]; };   // the last stage at index count
+Stages make_stages(int P, int t0) {
+  Stages s{};
+  int most = 0, total = 0, lvl = 0, n = P;
+  while ((1 << most) < group_size(t0)) ++most;
+  while ((1 << total) < P) ++total;
+  const int before = std::max(0, total - most);
+  s.count = (before + most - 1) / most;
+  for (int v = 0; v < s.count; ++v) {
+    s.lvl[v] = lvl;
+    s.n[v] = n;
+    s.lev[v] = (before - lvl) / (s.count - v);
+    n = (n + (1 << s.lev[v]) - 1) >> s.lev[v];
+    s.slot[v + 1] = s.slot[v] + n;
+    lvl += s.lev[v];
   }
-  __syncthreads();
-  if (threadIdx.x >= 64) return;   // one wave from here on (wave-scope ordering only)
-  if (lane == 0) {
-    double md = 0.0;
-    for (int i = 0; i < n0; ++i) {
-      const int r = i >> 4;
-      md = fmax(md, fabs(B[(r * t0 + r) * 256 + (i & 15) * 17]));
-    }
-    s_max = md;
-  }
-  wave_order();
-  const double thr = PIVOT_REL * s_max;
-  // the global rows' part of B is negative definite: signed factorization there
-  const unsigned long long neg = c.ng >= 64 ? ~0ull : ((1ull << c.ng) - 1ull);
-  const int cnt = wave_block_chol(B, t0, X, Ld, tmp, xbuf, thr, neg);
-  for (int idx = lane; idx < 256 * t0 * t0; idx += 64) {
-    const int tile = idx / 256;
-    const int r = tile % t0, cc = tile / t0;
-    c.FLb[idx] = (r >= cc) ? B[idx] : 0.0;
-    c.FLbi[idx] = X[idx];
-  }
-  if (lane == 0 && cnt) atomicAdd(&c.info->pivots, cnt);
+  s.lvl[s.count] = lvl;
+  s.n[s.count] = n;
+  s.lev[s.count] = total - lvl;
+  return s;
 }
 
-size_t border_smem(int t0) {
-  return (size_t)(2 * t0 * t0 + t0 + 1) * 256 * sizeof(double) + 48 * sizeof(double);
-}
-
-// first level handled by a tail kernel of `waves` waves: the first with at
-// most that many eliminations
-int tail_level(int P, int waves, int* n_out) {
-  int lvl = 0, n = P;
-  while (n > 1 && n / 2 > waves) {
-    ++lvl;
-    n = (n + 1) / 2;
-  }
-  *n_out = n;
-  return lvl;
+template <int GS>
+void reduce_groups(hipStream_t st, const BcrArgs& c) {
+  const Stages s = make_stages(c.P, c.t0);
+  const size_t smem = group_smem(c.t0);
+  for (int v = 0; v < s.count; ++v)
+    hipLaunchKernelGGL((k_bcr_group<GS, false>), dim3(s.slot[v + 1] - s.slot[v]), dim3(64 * FW), smem, st, c,
+                       s.lvl[v], s.n[v], s.lev[v], s.slot[v], v ? s.slot[v - 1] : 0, 0);
+  const int v = s.count;
+  hipLaunchKernelGGL((k_bcr_group<GS, true>), dim3(1), dim3(64 * FW), smem, st, c, s.lvl[v], s.n[v], s.lev[v],
+                     0, v ? s.slot[v - 1] : 0, 0);
 }
 
 }  // namespace
@@ -396,31 +507,39 @@ int bcr_tiles(int lmax, int n0) {
   return lmax <= 16 ? 1 : (lmax + 15) / 16;
 }
 
+long long bcr_part_doubles(int P, int t0, int tp, int nparts) {
+  if (tp >= 2) return (long long)(nparts + 1) * std::max(border_low(t0), 1) * 256;
+  const Stages s = make_stages(P, t0);
+  return (long long)std::max(s.slot[s.count], 1) * (border_low(t0) + 1 + t0) * 256;
+}
+
 void launch_bcr_factor(hipStream_t st, const BcrArgs& c, int nparts, int chunk) {
-  if (c.tp >= 2) {
-    launch_bcrn_reduce(st, c);
-  } else if (c.P > 0) {
-    const long long tiles = (long long)c.P * (2 + c.t0);
-    hipLaunchKernelGGL(k_bcr_init, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st, c);
-    int nt = 0;
-    const int lt = tail_level(c.P, TAIL_WAVES, &nt);
-    int n = c.P;
-    for (int lvl = 0; lvl < lt; ++lvl, n = (n + 1) / 2)
-      hipLaunchKernelGGL(k_bcr_level, dim3((n + 1) / 2), dim3(128), 0, st, c, lvl, n);
-    hipLaunchKernelGGL(k_bcr_tail, dim3(1), dim3(64 * TAIL_WAVES), 0, st, c, lt, nt);
+  if (c.tp < 2) {
+    if (group_size(c.t0) == 16) reduce_groups<16>(st, c);
+    else reduce_groups<8>(st, c);
+    return;
   }
+  launch_bcrn_reduce(st, c);
   if (c.n0 > 0) {
     if (nparts > 0) {
-      hipLaunchKernelGGL(k_bcr_s00_partial, dim3(nparts * c.t0 * c.t0), dim3(64), 0, st, c, chunk);
-      hipLaunchKernelGGL(k_bcr_s00_sum, dim3((c.t0 * c.t0 * 256 + 255) / 256), dim3(256), 0, st, c, nparts);
+      const int nz = border_low(c.t0);
+      hipLaunchKernelGGL(k_bcr_s00_partial, dim3(nparts * nz), dim3(64), 0, st, c, chunk);
+      hipLaunchKernelGGL(k_bcr_s00_sum, dim3(nz), dim3(256), 0, st, c, nparts);
     }
-    hipLaunchKernelGGL(k_bcr_border, dim3(1), dim3(256), border_smem(c.t0), st, c, nparts);
+    // (the tiles' layout of a group of 8 holds any border)
+    hipLaunchKernelGGL((k_bcr_group<8, true>), dim3(1), dim3(64 * FW), group_smem(BT_MAXT0), st, c, 0, 0, 0, 0,
+                       nparts, nparts > 0 ? 1 : 0);
   }
 }
 
 void set_bcr_smem_limits() {
-  hipFuncSetAttribute((const void*)k_bcr_border, hipFuncAttributeMaxDynamicSharedMemorySize,
-                      (int)border_smem(BT_MAXT0));
+  const auto set = [](const void* f, size_t bytes) {
+    hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  };
+  set((const void*)k_bcr_group<16, false>, group_smem(1));
+  set((const void*)k_bcr_group<16, true>, group_smem(1));
+  set((const void*)k_bcr_group<8, false>, group_smem(BT_MAXT0));
+  set((const void*)k_bcr_group<8, true>, group_smem(BT_MAXT0));
 }
 
 }  // namespace ahlp

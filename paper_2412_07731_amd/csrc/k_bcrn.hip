@@ -6,7 +6,7 @@
 //   T'_LL -= X_L'X_L,  T'_RR -= X_R'X_R,  T'_RL = -X_R'X_L,
 //   E'_L -= X_L'Z,  E'_R -= X_R'Z.
 // A level is two launches.  In the first a workgroup eliminates one odd pair:
-// one wave after another factors the TP diagonal tiles (the chain, about 2 us
+// one wave after another factors the TP diagonal tiles (the chain, 1.3 us
 // a tile), all waves share the tile column below and the trailing update; then
 // every wave takes whole columns of L_o^-1 [I, T'_oL, T'_oR, E'_o] by forward
 // substitution in registers (an FP64 accumulator tile is laid out as the next
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(64 * EW, 2) void k_bcrn_elim(BcrArgs c, int lvl, in
   int cnt = 0;
 #pragma unroll
   for (int p = 0; p < TP; ++p) {
-    if (wave == 0) cnt += wave_chol_tile<double, PLD>(B + tl(p, p), B + tl(p, p), Ld + p * PT, thr, nullptr);
+    if (wave == 0) cnt += wave_chol_tile<double, PLD, false, false>(B + tl(p, p), nullptr, Ld + p * PT, thr);
     if (p + 1 == TP) break;
     __syncthreads();
     if (wave >= 1 && wave < TP - p) {   // rows p + 1 .. TP - 1

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(320) void k_chol_latency(int iters, double* __restr
   __syncthreads();
   if (w == 0) {
     int cnt = 0;
-    for (int it = 0; it < iters; ++it) cnt += wave_chol_tile<double, LD>(P, Lt, Li, 1e-300, nullptr);
+    for (int it = 0; it < iters; ++it) cnt += wave_chol_tile<double, LD>(P, Lt, Li, 1e-300);
     __hip_atomic_store(&done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (cnt != 0 || Lt[lane] == -1.0) out[blockIdx.x] = Lt[lane] + Li[lane];
   } else {

@@ -494,7 +494,7 @@ __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
       const int rbp = lane + (lane >> 4);   // operand element s of a padded tile at rbp + 68 s
       for (int p = 0; p < pw; ++p) {
         T* D = Bd + tl(p, p) * TEP;
-        if (w == 0) cnt += wave_chol_tile<T, LD>(D, D, Ld + p * TEP, thr, nullptr);
+        if (w == 0) cnt += wave_chol_tile<T, LD>(D, D, Ld + p * TEP, thr);
         __syncthreads();
         if (p + 1 == pw) break;
         if (w >= 1 && w < pw - p) {
@@ -973,7 +973,7 @@ __device__ __forceinline__ void panel_factor(const BlockInfo& b, T* __restrict__
             st_acc(dt, acc[t][j]);
           }
         wave_order();
-        cnt += wave_chol_tile<T, LD>(dt, dt, li, thr, nullptr);
+        cnt += wave_chol_tile<T, LD, false, true, (BF_RMAX >= 6)>(dt, dt, li, thr);
       }
       sy.sync();
       // rows below: L(r, c) = acc(r, c) L_cc^-T

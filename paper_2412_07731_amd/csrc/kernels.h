@@ -134,8 +134,8 @@ struct BcrArgs {
   const double* Td; const double* To; const double* E; const double* S00; const double* thrT;
   double* BD; double* BC; double* BEt;            // working tiles (P tp^2, P tp^2, P tp t0)
   double* FLi; double* FXL; double* FXR; double* FGt;   // factor tiles (same counts)
-  double* FLb; double* FLbi;                      // border factor, t0*t0 tiles each
-  double* s00part;                                // per chunk of pairs: t0*t0 tiles
+  double* FLbi;                                   // inverse border factor, t0*t0 tiles
+  double* s00part;                                // sums of Z'Z over parts of the pairs, by tiles
   DevInfo* info;
 };
 struct BcrSolveArgs {
@@ -155,6 +155,8 @@ struct BcrSolveArgs {
 // tiles per pair side of the cyclic-reduction path for these sizes (1 to 4),
 // 0 if it does not apply
 int bcr_tiles(int lmax, int n0);
+// doubles of s00part
+long long bcr_part_doubles(int P, int t0, int tp, int nparts);
 void launch_bcr_factor(hipStream_t st, const BcrArgs& c, int nparts, int chunk);
 void launch_bcr_solve(hipStream_t st, const BcrSolveArgs& a);
 void set_bcr_smem_limits();

@@ -141,65 +141,4 @@ __device__ __forceinline__ void vec_put(double* dst, double y) {
   const int lane = threadIdx.x & 63;
   if (lane < 16) dst[lane] = y;
 }
-// Blocked Cholesky of a t x t matrix of tiles, by one wave.  B holds tile
-// (r, c) at (c t + r) 16 LD (LDS; only tiles with r >= c are read).  On return
-// those tiles hold the factor L, Ld the inverses of its t diagonal tiles and X
-// (t x t tiles, zero above the diagonal) the block inverse L^-1.  tmp: one
-// tile of LDS scratch (xbuf is not used); every tile has leading dimension LD.
-// A pivot <= thr is replaced (the pivot rule); returns the number replaced
-// (all lanes).  With neg != 0 (bit j:
-// row j's sign is negative) B is quasi-definite and the factorization signed,
-// B = L S L' with S = diag(-1 on neg's bits, +1 elsewhere): tile column p is
-// L_rp = B_rp L_pp^-T S_p, and the trailing update subtracts L_rp S_p L_cp'.
-template <int LD = TS>
-__device__ inline int wave_block_chol(double* B, int t, double* X, double* Ld, double* tmp,
-                                      double* xbuf, double thr, unsigned long long neg = 0) {
-  constexpr int TT = 16 * LD;   // values per tile
-  const int lane = threadIdx.x & 63;
-  int cnt = 0;
-  for (int p = 0; p < t; ++p) {
-    double* Bpp = B + (p * t + p) * TT;
-    const unsigned np = (unsigned)((neg >> (16 * p)) & 0xFFFFull);
-    if (neg) cnt += wave_chol_tile<double, LD, true>(Bpp, Bpp, Ld + p * TT, thr, xbuf, np);
-    else cnt += wave_chol_tile<double, LD>(Bpp, Bpp, Ld + p * TT, thr, xbuf);
-    for (int r = p + 1; r < t; ++r) {
-      d4 acc = mma_xyt<LD>(acc_zero(), B + (p * t + r) * TT, Ld + p * TT, 1.0);
-      if (neg && ((np >> (lane & 15)) & 1u)) acc = -acc;   // times S_p (column lane % 16)
-      wave_order();
-      acc_store<LD>(B + (p * t + r) * TT, acc);
-    }
-    wave_order();
-    for (int r = p + 1; r < t; ++r)
-      for (int cc = p + 1; cc <= r; ++cc) {
-        d4 acc = acc_load<LD>(B + (cc * t + r) * TT);
-        if (neg) acc = mma_xsyt<LD>(acc, B + (p * t + r) * TT, B + (p * t + cc) * TT, -1.0, np);
-        else acc = mma_xyt<LD>(acc, B + (p * t + r) * TT, B + (p * t + cc) * TT, -1.0);
-        wave_order();
-        acc_store<LD>(B + (cc * t + r) * TT, acc);
-      }
-    wave_order();
-  }
-  // X = L^-1 by block columns
-  for (int cc = 0; cc < t; ++cc) {
-    for (int r = 0; r < t; ++r) {
-      if (r < cc) {
-        op_store<LD>(X + (cc * t + r) * TT, Op{});
-      } else if (r == cc) {
-        tile_copy<LD, LD>(X + (cc * t + r) * TT, Ld + r * TT);
-      } else {
-        d4 acc = acc_zero();
-        for (int q = cc; q < r; ++q) acc = mma_xy<LD>(acc, B + (q * t + r) * TT, X + (cc * t + q) * TT, 1.0);
-        acc_store<LD>(tmp, acc);
-        wave_order();
-        d4 x = mma_xy<LD>(acc_zero(), Ld + r * TT, tmp, -1.0);
-        wave_order();
-        acc_store<LD>(X + (cc * t + r) * TT, x);
-      }
-      wave_order();
-    }
-  }
-  return cnt;
-}
-
-
 }  // namespace ahlp
