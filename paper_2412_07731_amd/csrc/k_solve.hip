@@ -7,6 +7,7 @@
 // x_0 and block rows likewise, so tile products need no bounds checks.
 #include "common.h"
 #include "kernels.h"
+#include "tile_chol.h"
 
 namespace ahlp {
 
@@ -300,117 +301,148 @@ __global__ __launch_bounds__(256) void k_x0_sum(int N, int n0, long long nl, lon
 }
 
 // ------------------------------------------------------------ substitutions
-// The block solves walk the mt tile columns of L_i in a dependent chain; the
-// tiles a step reads do not depend on the chain, so each step loads the next
-// step's tiles into registers (two register sets, alternating) while it
-// works.  BS_PF tiles of a column per wave are held (rows p+1+w, p+5+w, ...);
-// rows beyond them, in blocks with more than 4 BS_PF bordered tile rows below
-// the diagonal, are loaded in place.  Loads past either end (column mt after
-// the last forward step, column -1 after the last backward one, rows past
-// rt) are clamped to a valid tile and not used.
-constexpr int BS_PF = 5;
+// The block solves walk the mt tile columns of L_i in a dependent chain; the tiles
+// do not depend on it.  A workgroup of W waves takes a block.  Wave w owns the tile
+// rows (backward: columns) w, w + W, .., R at most, and keeps their sums in
+// registers as the lanes' parts; when a row's turn comes it adds them up, applies
+// the inverted diagonal tile and puts the 16 values in LDS for all, with one
+// barrier a step.  The tiles of the next D steps are on their way in registers (a
+// whole block of up to eight tile rows); lane (i, g) holds four elements of a tile's
+// row (backward: column) i.
+// Bound by memory where there are blocks enough (512 blocks of 256 rows: 33 us for
+// 205 MB), else by the steps' waits for their tiles.  Measured against a walk with
+// the sums in LDS, three barriers a step and one step's tiles ahead, us forward and
+// backward, FP64: 2190 blocks of 20-60 rows 30 and 32 -> 14 and 15; 64 of 96 rows
+// 10.4 and 10.4 -> 6.2 and 6.9; 512 of 256 rows 42 and 38 -> 33 and 33; 512 of 64-512
+// rows 112 and 104 -> 91 and 92; 48 of 600-900 rows 161 and 143 -> 73 and 113.
+// Loads without branches (bounds-checked, zeros for a finished row) have exact waits
+// but cost their issue: 28 us where 14 were.
+template <typename T, int R> struct SubTiles { T t[R][4]; };
 
-template <typename T>
-struct ColRegs {
-  T t[BS_PF][4];   // tiles (p+1+w+4q, p), element 64 k + lane
-  T li[4];         // inverted diagonal tile p
-};
-
-template <typename T>
-__device__ __forceinline__ void load_col(const BlockInfo& b, const T* __restrict__ LB,
-                                         const T* __restrict__ LINV, int p, int wave, int lane,
-                                         ColRegs<T>& c) {
-  const int pc = max(min(p, b.mt - 1), 0);
+// index in a tile's row (BWD: column) of element s of lane row g: four in a row, or
+// two pairs, so that a 16-byte load of all lanes takes whole 64-byte pieces
+template <bool BWD>
+__device__ __forceinline__ int sub_at(int g, int s) { return BWD ? 2 * g + (s & 1) + 8 * (s >> 1) : 4 * g + s; }
+// acc + this lane's four products with the 16 values v in LDS
+template <bool BWD, typename T>
+__device__ __forceinline__ double sub_dot(double acc, const T (&t)[4], const double* v) {
+  const int g = (threadIdx.x & 63) >> 4;
 #pragma unroll
-  for (int q = 0; q < BS_PF; ++q) {
-    const int r = max(min(p + 1 + wave + 4 * q, b.rt - 1), pc);
-    const T* L = LB + lb_tile(b, r, pc);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) c.t[q][k] = L[64 * k + lane];
-  }
-  const T* Li = LINV + b.linvoff + (long long)pc * TE;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) c.li[k] = Li[64 * k + lane];
+  for (int s = 0; s < 4; ++s) acc = fma((double)t[s], v[sub_at<BWD>(g, s)], acc);
+  return acc;
+}
+// the same, done here and not where the sum is used: the tile's registers are loaded
+// again next
+template <bool BWD, typename T>
+__device__ __forceinline__ double sub_sum(double acc, const T (&t)[4], const double* v) {
+  acc = sub_dot<BWD>(acc, t, v);
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(acc));
+#endif
+  return acc;
+}
+// x of the tile Linv from the right-hand side put in v by this wave, back to v
+template <bool BWD, typename T>
+__device__ __forceinline__ void sub_diag(const T (&linv)[4], double rhs, double* v) {
+  const int lane = threadIdx.x & 63;
+  if (lane < 16) v[lane] = rhs;
+  wave_order();
+  const double x = col_sum4(sub_dot<BWD>(0.0, linv, v));
+  wave_order();
+  if (lane < 16) v[lane] = x;
 }
 
 // Forward substitution with the bordered factor of block i: v = L_i^-1 t and,
 // on the bordered rows, qn = -W_i' v.  t is read from tin (padded block-row
 // vector) and v written to tv (tin may equal tv).
-template <typename T>
-__global__ __launch_bounds__(256) void k_block_fwd(const BlockInfo* __restrict__ blk,
-                                                   const T* __restrict__ LB,
-                                                   const T* __restrict__ LINV,
-                                                   const double* __restrict__ tin,
-                                                   double* __restrict__ tv,
-                                                   double* __restrict__ qn) {
+template <typename T, int W, int R, int D>
+__global__ __launch_bounds__(64 * W) void k_block_fwd(const BlockInfo* __restrict__ blk,
+                                                      const T* __restrict__ LB, const T* __restrict__ LINV,
+                                                      const double* __restrict__ tin, double* __restrict__ tv,
+                                                      double* __restrict__ qn) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* t = reinterpret_cast<double*>(smem_raw);
+  double* y = reinterpret_cast<double*>(smem_raw);
   const BlockInfo b = blk[blockIdx.x];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nr = TS * b.rt, nm = TS * b.mt;
-  for (int r = tid; r < nr; r += blockDim.x) t[r] = (r < nm) ? tin[b.voff + r] : 0.0;
-  // step p with the tiles in c; the next step's go to n
-  auto step = [&](int p, const ColRegs<T>& c, ColRegs<T>& n) {
-    load_col(b, LB, LINV, p + 1, wave, lane, n);
-    __syncthreads();
-    if (wave == 0) {
-      double s = 0.0;
+  const int lane = threadIdx.x & 63, i16 = lane & 15, at = (lane >> 4) * 4 * TS + i16;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nm = TS * b.mt;
+  SubTiles<T, R> c[D];
+  double acc[R];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) s += (double)c.li[k] * t[TS * p + 4 * k + (lane >> 4)];
-      s = col_sum4(s);
-      // all lanes have read t[p-block]; lanes 0..15 now overwrite it
-      if (lane < 16) t[TS * p + lane] = s;
-    }
-    __syncthreads();
+  for (int q = 0; q < R; ++q) acc[q] = 0.0;
+  // tile column p of the wave's rows; in the diagonal's place its inverse
+  auto load = [&](int p, SubTiles<T, R>& x) {
+    if (p >= b.mt) return;
 #pragma unroll
-    for (int q = 0; q < BS_PF; ++q) {
-      const int r = p + 1 + wave + 4 * q;
-      if (r < b.rt) {
-        double s = 0.0;
+    for (int q = 0; q < R; ++q) {
+      const int r = w + W * q;
+      if (r < p || r >= b.rt) continue;
+      const T* src = r == p ? LINV + b.linvoff + (long long)p * TE : LB + lb_tile(b, r, p);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) s += (double)c.t[q][k] * t[TS * p + 4 * k + (lane >> 4)];
-        s = col_sum4(s);
-        if (lane < 16) t[TS * r + lane] -= s;
-      }
-    }
-    for (int r = p + 1 + wave + 4 * BS_PF; r < b.rt; r += 4) {
-      const T* L = LB + lb_tile(b, r, p);
-      double s = 0.0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) s += (double)L[64 * k + lane] * t[TS * p + 4 * k + (lane >> 4)];
-      s = col_sum4(s);
-      if (lane < 16) t[TS * r + lane] -= s;
+      for (int s = 0; s < 4; ++s) x.t[q][s] = src[at + TS * s];
     }
   };
-  ColRegs<T> ra, rb;
-  load_col(b, LB, LINV, 0, wave, lane, ra);
-  for (int p = 0; p < b.mt; p += 2) {
-    step(p, ra, rb);
-    if (p + 1 < b.mt) step(p + 1, rb, ra);
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, c[d]);
+  for (int r = threadIdx.x; r < nm; r += blockDim.x) y[r] = tin[b.voff + r];
+  lds_barrier();
+#pragma unroll 1
+  for (int p0 = 0; p0 < b.mt; p0 += D)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int p = p0 + d;
+      if (p >= b.mt) break;
+      double* yp = y + TS * p;
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (w + W * q == p) sub_diag<false>(c[d].t[q], yp[i16] - col_sum4(acc[q]), yp);
+      lds_barrier();
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (w + W * q > p && w + W * q < b.rt) acc[q] = sub_sum<false>(acc[q], c[d].t[q], yp);
+      load(p + D, c[d]);
+    }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int r = w + W * q;
+    if (r < b.mt || r >= b.rt) continue;
+    const double s = col_sum4(acc[q]);
+    if (lane < 16) qn[b.qoff + TS * (r - b.mt) + lane] = 0.0 - s;
   }
-  __syncthreads();
-  for (int r = tid; r < nm; r += blockDim.x) tv[b.voff + r] = t[r];
-  for (int r = nm + tid; r < nr; r += blockDim.x) qn[b.qoff + (r - nm)] = t[r];
+  for (int r = threadIdx.x; r < nm; r += blockDim.x) tv[b.voff + r] = y[r];
 }
 
 // Backward substitution: y = L_i^-T (v - W_i u_i), where u_i (the block's view
 // of the Schur solution: left pair, right pair, x_0) fills the bordered rows.
 // Writes dy (canonical) and the padded copy dyp.
-template <typename T>
-__global__ __launch_bounds__(256) void k_block_bwd(const BlockInfo* __restrict__ blk, int nb,
-                                                   long long nl, const T* __restrict__ LB,
-                                                   const T* __restrict__ LINV,
-                                                   const double* __restrict__ v,
-                                                   const double* __restrict__ u,
-                                                   double* __restrict__ dy,
-                                                   double* __restrict__ dyp) {
+template <typename T, int W, int R, int D>
+__global__ __launch_bounds__(64 * W) void k_block_bwd(const BlockInfo* __restrict__ blk, int nb, long long nl,
+                                                      const T* __restrict__ LB, const T* __restrict__ LINV,
+                                                      const double* __restrict__ v, const double* __restrict__ u,
+                                                      double* __restrict__ dy, double* __restrict__ dyp) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* y = reinterpret_cast<double*>(smem_raw);
-  __shared__ double part[4][TS];
   const BlockInfo b = blk[blockIdx.x];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nr = TS * b.rt, nm = TS * b.mt;
-  for (int r = tid; r < nr; r += blockDim.x) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15, at = i16 * TS + 2 * (lane >> 4);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nr = TS * b.rt, nm = TS * b.mt;
+  SubTiles<T, R> c[D];
+  double acc[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) acc[q] = 0.0;
+  // tile row r of the wave's columns; in the diagonal's place its inverse
+  auto load = [&](int r, SubTiles<T, R>& x) {
+    if (r < 0) return;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int p = w + W * q;
+      if (p > r || p >= b.mt) continue;
+      const T* src = r == p ? LINV + b.linvoff + (long long)p * TE : LB + lb_tile(b, r, p);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) x.t[q][s] = src[at + sub_at<true>(0, s)];
+    }
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(b.rt - 1 - d, c[d]);
+  for (int r = threadIdx.x; r < nr; r += blockDim.x) {
     double val;
     if (r < nm) {
       val = v[b.voff + r];
@@ -427,58 +459,26 @@ __global__ __launch_bounds__(256) void k_block_bwd(const BlockInfo* __restrict__
     }
     y[r] = val;
   }
-  auto step = [&](int p, const ColRegs<T>& c, ColRegs<T>& n) {
-    load_col(b, LB, LINV, p - 1, wave, lane, n);
-    __syncthreads();
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  lds_barrier();
+#pragma unroll 1
+  for (int k0 = 0; k0 < b.rt; k0 += D)
 #pragma unroll
-    for (int q = 0; q < BS_PF; ++q) {
-      const int r = p + 1 + wave + 4 * q;
-      if (r < b.rt) {
-        const double yv = y[TS * r + (lane & 15)];
+    for (int d = 0; d < D; ++d) {
+      const int r = b.rt - 1 - k0 - d;
+      if (r < 0) break;
+      double* yr = y + TS * r;
+      if (r < b.mt) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) acc[s] += (double)c.t[q][s] * yv;
+        for (int q = 0; q < R; ++q)
+          if (w + W * q == r) sub_diag<true>(c[d].t[q], yr[i16] - col_sum4(acc[q]), yr);
+        lds_barrier();
       }
-    }
-    for (int r = p + 1 + wave + 4 * BS_PF; r < b.rt; r += 4) {
-      const T* L = LB + lb_tile(b, r, p);
-      const double yv = y[TS * r + (lane & 15)];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) acc[s] += (double)L[64 * s + lane] * yv;
+      for (int q = 0; q < R; ++q)
+        if (w + W * q < r && w + W * q < b.mt) acc[q] = sub_sum<true>(acc[q], c[d].t[q], yr);
+      load(r - D, c[d]);
     }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const double x = row_sum16(acc[s]);
-      if ((lane & 15) == 0) part[wave][4 * s + (lane >> 4)] = x;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      // w = v_p - sum over waves (fixed order); y_p = Linv_p' w
-      const int kcol = lane & 15;
-      const double w = y[TS * p + kcol] - (part[0][kcol] + part[1][kcol] + part[2][kcol] + part[3][kcol]);
-      // element (i, k) of Linv at 64 s + l:  i = l%16, k = 4 s + l/16;  y_p[k] = sum_i Linv[i][k] w[i]
-      double s4[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        // this lane's w is w[lane % 16], the row index i it needs
-        s4[s] = row_sum16((double)c.li[s] * w);
-      }
-      if ((lane & 15) == 0) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) part[0][4 * s + (lane >> 4)] = s4[s];
-      }
-    }
-    __syncthreads();
-    if (tid < TS) y[TS * p + tid] = part[0][tid];
-  };
-  ColRegs<T> ra, rb;
-  load_col(b, LB, LINV, b.mt - 1, wave, lane, ra);
-  for (int p = b.mt - 1; p >= 0; p -= 2) {
-    step(p, ra, rb);
-    if (p >= 1) step(p - 1, rb, ra);
-  }
-  __syncthreads();
-  for (int r = tid; r < nm; r += blockDim.x) {
+  for (int r = threadIdx.x; r < nm; r += blockDim.x) {
     dyp[b.voff + r] = (r < b.m) ? y[r] : 0.0;
     if (r < b.m) dy[b.yoff + r] = y[r];
   }
@@ -1099,19 +1099,28 @@ void launch_x0_sum(hipStream_t st, int N, int n0, long long nl, long long f0firs
     hipLaunchKernelGGL(k_x0_sum, dim3(n0), dim3(256), 0, st, N, n0, nl, f0first, part, F0, yL, mode,
                        cvec, zvec, x0off, gout, out);
 }
+// Waves, rows a wave and steps ahead by the largest block's tile rows, so that the
+// tiles held are some 64 to 120 registers.
+#define SUB_DISPATCH(KERNEL, ...)                                                              \
+  do {                                                                                         \
+    const size_t sh = (size_t)TS * max_rt * sizeof(double);                                    \
+    if (max_rt <= 8) hipLaunchKernelGGL((KERNEL<T, 4, 2, 4>), dim3(N), dim3(256), sh, st, __VA_ARGS__);       \
+    else if (max_rt <= 16) hipLaunchKernelGGL((KERNEL<T, 4, 4, 3>), dim3(N), dim3(256), sh, st, __VA_ARGS__); \
+    else if (max_rt <= 24) hipLaunchKernelGGL((KERNEL<T, 8, 3, 3>), dim3(N), dim3(512), sh, st, __VA_ARGS__); \
+    else if (max_rt <= 40) hipLaunchKernelGGL((KERNEL<T, 8, 5, 2>), dim3(N), dim3(512), sh, st, __VA_ARGS__); \
+    else hipLaunchKernelGGL((KERNEL<T, 16, 5, 2>), dim3(N), dim3(1024), sh, st, __VA_ARGS__);                 \
+  } while (0)
+static_assert(16 * 5 >= 160 * 1024 / (17 * TS * 8) - 1, "the largest block that create accepts");
 template <typename T>
 void launch_block_fwd(hipStream_t st, const BlockInfo* blk, int N, int max_rt, const T* LB,
                       const T* LINV, const double* tin, double* tv, double* qn) {
-  const size_t sh = (size_t)TS * max_rt * sizeof(double);
-  hipLaunchKernelGGL(k_block_fwd<T>, dim3(N), dim3(256), sh, st, blk, LB, LINV, tin, tv, qn);
+  SUB_DISPATCH(k_block_fwd, blk, LB, LINV, tin, tv, qn);
 }
 template <typename T>
 void launch_block_bwd(hipStream_t st, const BlockInfo* blk, int N, int nb, long long nl,
                       int max_rt, const T* LB, const T* LINV, const double* v, const double* u,
                       double* dy, double* dyp) {
-  const size_t sh = (size_t)TS * max_rt * sizeof(double);
-  hipLaunchKernelGGL(k_block_bwd<T>, dim3(N), dim3(256), sh, st, blk, nb, nl, LB, LINV, v, u, dy,
-                     dyp);
+  SUB_DISPATCH(k_block_bwd, blk, nb, nl, LB, LINV, v, u, dy, dyp);
 }
 template void launch_block_fwd<double>(hipStream_t, const BlockInfo*, int, int, const double*,
                                        const double*, const double*, double*, double*);
