@@ -281,6 +281,7 @@ struct ahlp_problem_s {
   // tile path of the Schur factorization (pairs <= 32 rows, border <= 64)
   bool fast = false;          // Schur factor by cyclic reduction (else the segmented chain)
   int tp = 0;                 // its tiles per pair side
+  int* red_arrived = nullptr;   // arrivals of a reduction's workgroups, zero between launches
   int t0 = 0, s00_chunk = 16, s00_parts = 0;
   double *BD = nullptr, *BC = nullptr, *BEt = nullptr, *FLi = nullptr, *FXL = nullptr,
          *FXR = nullptr, *FGt = nullptr, *FLbi = nullptr, *s00part = nullptr;
@@ -753,21 +754,27 @@ void solve_blocks_bwd(ahlp_problem_t p, hipStream_t st, const T* LB, const T* LI
 // The dual rows after the blocks: out = base + alpha (F xp [+ F0 x0]) for the
 // link rows and the global rows (out and base point at the first link row;
 // x0 and the x_0 coupling only when x0 is given).
-void link_global_rows(ahlp_problem_t p, const double* xp, const double* x0, const double* base,
-                      double alpha, double* out, hipStream_t st) {
-  const double* F0 = x0 ? p->F0 : nullptr;
-  launch_linkrows(st, p->blk, p->P, p->ng, p->n0, p->d_l, p->d_loff, p->nl, p->lptr, p->lcol,
-                  p->lval, p->gptr, p->gidx, p->gval, xp, x0, F0, p->f0first == 0 ? F0 : nullptr,
-                  base, alpha, out);
+LinkArgs link_args(ahlp_problem_t p, const double* xp, const double* x0, const double* base, double alpha,
+                   double* out) {
+  LinkArgs a{};
+  a.P = p->P; a.ng = p->ng; a.n0 = p->n0; a.wgs = link_wgs(p->P, p->ng);
+  a.lsz = p->d_l; a.loff = p->d_loff; a.nl = p->nl;
+  a.lptr = p->lptr; a.lcol = p->lcol; a.lval = p->lval;
+  a.gptr = p->gptr; a.gidx = p->gidx; a.gval = p->gval;
+  a.xp = xp; a.x0 = x0;
+  a.F0 = x0 ? p->F0 : nullptr; a.F0L = p->f0first == 0 ? a.F0 : nullptr;
+  a.base = base; a.alpha = alpha; a.out = out;
+  return a;
 }
 
 // A row pass (AHLP_ST_AROWS) with its algorithmic bytes: the A tiles, the C
 // tiles if any vector takes the x_0 columns, each vector, each base read and
-// each output written (real sizes, not the tile padding).
-void rows_pass(ahlp_problem_t p, const RowsArgs& ra, hipStream_t st) {
+// each output written (real sizes, not the tile padding).  The link and global
+// rows la go along in the same launch.
+void rows_pass(ahlp_problem_t p, const RowsArgs& ra, const LinkArgs& la, hipStream_t st) {
   p->timer.begin(AHLP_ST_AROWS);
-  if (p->sparse) launch_sp_rows(st, p->blk, p->sp, p->d0off, ra);
-  else launch_rows_multi(st, p->blk, p->rowtiles, p->nrt, p->A, p->C, p->d0off, ra);
+  if (p->sparse) launch_sp_rows(st, p->blk, p->sp, p->d0off, ra, la);
+  else launch_rows_multi(st, p->blk, p->rowtiles, p->nrt, p->A, p->C, p->d0off, ra, la);
   p->timer.end();
   if (p->timer.records(AHLP_ST_AROWS)) {
     bool anyC = false;
@@ -782,12 +789,12 @@ void rows_pass(ahlp_problem_t p, const RowsArgs& ra, hipStream_t st) {
   }
 }
 void rows_pass1(ahlp_problem_t p, const double* v, const double* base, double alpha, int with_C,
-                int padded, double* out, hipStream_t st) {
+                int padded, double* out, const LinkArgs& la, hipStream_t st) {
   RowsArgs ra{};
   ra.nv = 1;
   ra.v[0] = v; ra.base[0] = base; ra.alpha[0] = alpha; ra.out[0] = out;
   ra.with_C[0] = with_C; ra.padded[0] = padded;
-  rows_pass(p, ra, st);
+  rows_pass(p, ra, la, st);
 }
 
 // The column pass g = A_i' yp + F_i' yL and the per-block partials C_i' yp
@@ -816,11 +823,13 @@ ahlp_status_t solve_once(ahlp_problem_t p, const double* rx, const double* ry, c
   p->timer.begin(AHLP_ST_SOLVE);
   launch_rhx(st, p->blk, p->N, p->n0, p->x0off, p->d0off, rx, rz, p->xs, p->Dp, p->ws.rhx, p->ws.vx);
   // t_i = ry_i + A_i D_i rhx_i (padded), s_L = ry_L + F D rhx
+  const LinkArgs la = link_args(p, p->ws.vx, nullptr, ry + p->mblk, 1.0, p->ws.s);
   if (!tpre) {
-    rows_pass1(p, p->ws.vx, ry, 1.0, 0, 1, p->ws.tv, st);
+    rows_pass1(p, p->ws.vx, ry, 1.0, 0, 1, p->ws.tv, la, st);
     tpre = p->ws.tv;
+  } else {
+    launch_linkrows(st, p->blk, la);
   }
-  link_global_rows(p, p->ws.vx, nullptr, ry + p->mblk, 1.0, p->ws.s, st);
   if (f32) solve_blocks_fwd<float>(p, st, p->LB32, p->LINV32, tpre);
   else solve_blocks_fwd<double>(p, st, p->LB, p->LINV, tpre);
   if (p->fast) {
@@ -873,9 +882,9 @@ void apply_At_both(ahlp_problem_t p, const double* y, const double* cvec, const 
 void apply_A(ahlp_problem_t p, const double* x, const double* base, double alpha, double* out,
              hipStream_t st) {
   launch_pad_x(st, p->blk, p->N, p->n0, p->x0off, p->d0off, x, p->ws.xp, nullptr);
-  rows_pass1(p, p->ws.xp, base, alpha, 1, 0, out, st);
-  link_global_rows(p, p->ws.xp, p->ws.xp + p->d0off, base ? base + p->mblk : nullptr, alpha,
-                   out + p->mblk, st);
+  rows_pass1(p, p->ws.xp, base, alpha, 1, 0, out,
+             link_args(p, p->ws.xp, p->ws.xp + p->d0off, base ? base + p->mblk : nullptr, alpha, out + p->mblk),
+             st);
 }
 
 ahlp_status_t read_scal(ahlp_problem_t p, int count, hipStream_t st) {
@@ -889,7 +898,13 @@ ahlp_status_t read_scal(ahlp_problem_t p, int count, hipStream_t st) {
 void red(ahlp_problem_t p, int op, long long n, const double* a, const double* b, int slot,
          hipStream_t st, const double* c = nullptr, const double* d = nullptr, double s1 = 0,
          double s2 = 0) {
-  launch_reduce(st, op, n, a, b, c, d, s1, s2, p->ws.red_part, p->ws.scal + slot);
+  MultiRed m{};
+  m.nred = 1;
+  m.r[0] = RedSpec{op, slot, n, a, b, c, d, s1, s2, nullptr, nullptr};
+  m.partial = p->ws.red_part;
+  m.arrived = p->red_arrived;
+  m.out = p->ws.scal;
+  launch_mreduce(st, m);
 }
 
 // Batches independent reductions into one pair of launches.
@@ -898,6 +913,7 @@ struct Reds {
   Reds(ahlp_problem_t p) {
     m.nred = 0;
     m.partial = p->ws.red_part;
+    m.arrived = p->red_arrived;
     m.out = p->ws.scal;
   }
   Reds& add(int op, long long n, const double* a, const double* b, int slot,
@@ -929,8 +945,7 @@ void check_pass(ahlp_problem_t p, const double* rx, const double* ry, const doub
     ra.nv = 2;
     ra.v[1] = p->w2p; ra.alpha[1] = 1.0; ra.out[1] = p->aw2; ra.padded[1] = 1;
   }
-  rows_pass(p, ra, st);
-  link_global_rows(p, p->ws.xp, p->ws.xp + p->d0off, ry + p->mblk, -1.0, p->ws.ey + p->mblk, st);
+  rows_pass(p, ra, link_args(p, p->ws.xp, p->ws.xp + p->d0off, ry + p->mblk, -1.0, p->ws.ey + p->mblk), st);
   p->timer.end();
 }
 
@@ -975,10 +990,8 @@ ahlp_status_t refine(ahlp_problem_t p, const double* rx, const double* ry, const
   while (*be > tol && !(abs_tol > 0.0 && check_en(p) <= abs_tol) && *steps < max_refine) {
     const double be_prev = *be;
     CHK(solve_once(p, p->ws.ex, p->ws.ey, p->ws.ez, p->ws.cx, p->ws.cy, p->ws.cz, st, nullptr, p->ws.gc));
-    launch_axpy(st, p->n_tot, 1.0, p->ws.cx, dx);
-    launch_axpy(st, p->m_tot, 1.0, p->ws.cy, dy);
-    launch_axpy(st, p->n_tot, 1.0, p->ws.cz, dz);
-    launch_axpy(st, p->n_tot, 1.0, p->ws.gc, p->ws.g);
+    launch_axpys(st, 1.0, {{p->n_tot, p->ws.cx, dx}, {p->m_tot, p->ws.cy, dy}, {p->n_tot, p->ws.cz, dz},
+                           {p->n_tot, p->ws.gc, p->ws.g}});
     check_pass(p, rx, ry, rz, dx, dz, w2, st, bnd);
     Reds R(p);
     add_check_reds(p, R, rx, ry, rz, dx, dy, dz, false);
@@ -1765,6 +1778,8 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   CHK(M.alloc(&p->To, std::max(to, 1LL)));
   CHK(M.alloc(&p->E, std::max(p->nl * nbw, 1LL)));
   CHK(M.alloc(&p->S00, std::max(nbw * nbw, 1)));
+  CHK(M.alloc(&p->red_arrived, MAXRED * RED_APART));
+  launch_fill(st, MAXRED * RED_APART / 2, 0.0, reinterpret_cast<double*>(p->red_arrived));
   CHK(M.alloc(&p->thrT, std::max(P, 1)));
   CHK(M.alloc(&p->CL, std::max(td, 1LL)));
   CHK(M.alloc(&p->CLi, std::max(td, 1LL)));
@@ -2402,9 +2417,8 @@ ahlp_status_t ipm_solve_impl(ahlp_problem_t p, const ahlp_ipm_opts_t* o, double*
       ra.v[0] = p->ws.xp; ra.base[0] = p->b; ra.alpha[0] = -1.0; ra.out[0] = p->rp; ra.with_C[0] = 1;
       ra.v[1] = p->ws.vx; ra.alpha[1] = 1.0; ra.out[1] = p->ta; ra.padded[1] = 1; ra.chain[1] = 1;
       ra.v[2] = p->w1p; ra.alpha[2] = 1.0; ra.out[2] = p->aw1; ra.padded[2] = 1;
-      rows_pass(p, ra, st);
+      rows_pass(p, ra, link_args(p, p->ws.xp, p->ws.xp + p->d0off, p->b + p->mblk, -1.0, p->rp + p->mblk), st);
     }
-    link_global_rows(p, p->ws.xp, p->ws.xp + p->d0off, p->b + p->mblk, -1.0, p->rp + p->mblk, st);
     Reds Rr(p);
     Rr.add(RED_DOT, n, x, z, 0).add(RED_DOT, n, p->c, x, 1).add(RED_DOT, m, p->b, y, 2)
         .add(RED_MAXABS, m, p->rp, nullptr, 3).add(RED_MAXABS, n, p->rd, nullptr, 4)
@@ -2628,9 +2642,7 @@ ahlp_status_t ipm_solve_impl(ahlp_problem_t p, const ahlp_ipm_opts_t* o, double*
       CHK(solve_refined(p, p->zerosn, p->zerosm, p->g_r, p->g_dx, p->g_dy, p->g_dz,
                         o->max_refine, o->refine_tol, kn, &gbe, &gsteps, st));
       account(gbe, gsteps);
-      launch_axpy(st, n, 1.0, p->dx, p->g_dx);
-      launch_axpy(st, m, 1.0, p->dy, p->g_dy);
-      launch_axpy(st, n, 1.0, p->dz, p->g_dz);
+      launch_axpys(st, 1.0, {{n, p->dx, p->g_dx}, {m, p->dy, p->g_dy}, {n, p->dz, p->g_dz}});
       Reds(p).add(RED_RATIO, n, x, p->g_dx, S_GP).add(RED_RATIO, n, z, p->g_dz, S_GD).launch(st);
       CHK(read_scal(p, NSCAL, st));
       const double ap_n = std::min(1.0, o->eta * hs[S_GP]);

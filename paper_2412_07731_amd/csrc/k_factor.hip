@@ -1416,14 +1416,13 @@ __device__ inline double pq_get(const double* PQ, const BlockInfo& b, int q, int
 // (col-major) and E_j (l_j x nb, col-major; columns: the global rows, then
 // x_0), each entry the fixed-order sum of its two contributing blocks (plus
 // F0 in the x_0 columns), and the pivot threshold of the pair.
-__global__ __launch_bounds__(256) void k_assemble_pairs(
-    const BlockInfo* __restrict__ blk, int P, int nb, int n0, const int* __restrict__ lsz,
+__device__ __forceinline__ void assemble_pair(
+    const BlockInfo* __restrict__ blk, int j, int P, int nb, int n0, const int* __restrict__ lsz,
     const long long* __restrict__ tdoff, const long long* __restrict__ tooff,
     const long long* __restrict__ eoff, const double* __restrict__ PQ,
     const double* __restrict__ F0, const long long* __restrict__ loff, double delta,
     double* __restrict__ Td, double* __restrict__ To, double* __restrict__ E,
     double* __restrict__ thrT) {
-  const int j = blockIdx.x;
   const BlockInfo bl = blk[j], br = blk[j + 1];
   const int l = lsz[j], ng = nb - n0;
   const int offR = TS * bl.ktL;          // pair j inside block j (its right section)
@@ -1464,18 +1463,17 @@ __global__ __launch_bounds__(256) void k_assemble_pairs(
 // S00 (nb x nb; the global rows, then x_0) = K0's border + sum_i (F D F' -
 // W'W)_i[border, border]: K0' holds delta I on the global rows, their x_0 part
 // Wg0 (rows nl.. of the extended F0) off the diagonal, and -D_0^-1 on x_0.
-// One workgroup per entry, each thread a fixed strided subset of the blocks,
-// then a fixed reduction tree.
-__global__ __launch_bounds__(256) void k_assemble_s00(const BlockInfo* __restrict__ blk, int N,
-                                                      int nb, int n0, long long nl,
-                                                      const double* __restrict__ PQ,
-                                                      const double* __restrict__ D0,
-                                                      const double* __restrict__ F0, double delta,
-                                                      double* __restrict__ S00) {
+// One workgroup per entry of the lower triangle (idx row by row), each thread a
+// fixed strided subset of the blocks, then a fixed reduction tree.
+__device__ __forceinline__ void assemble_s00(const BlockInfo* __restrict__ blk, int idx, int N, int nb,
+                                             int n0, long long nl, const double* __restrict__ PQ,
+                                             const double* __restrict__ D0,
+                                             const double* __restrict__ F0, double delta,
+                                             double* __restrict__ S00) {
   __shared__ double sh[4];
-  const int idx = blockIdx.x;
-  const int a = idx % nb, c = idx / nb, ng = nb - n0;
-  if (c > a) return;   // lower triangle computed, mirrored below
+  int a = 0;
+  while ((a + 1) * (a + 2) / 2 <= idx) ++a;
+  const int c = idx - a * (a + 1) / 2, ng = nb - n0;
   double v = 0.0;
   for (int i = threadIdx.x; i < N; i += blockDim.x) {
     const BlockInfo& b = blk[i];
@@ -1494,6 +1492,19 @@ __global__ __launch_bounds__(256) void k_assemble_s00(const BlockInfo* __restric
     S00[a + c * nb] = t;
     S00[c + a * nb] = t;
   }
+}
+
+// Pairs, then entries of S00: one launch for both.
+__global__ __launch_bounds__(256) void k_assemble(
+    const BlockInfo* __restrict__ blk, int N, int nb, int n0, long long nl, const int* __restrict__ lsz,
+    const long long* __restrict__ tdoff, const long long* __restrict__ tooff,
+    const long long* __restrict__ eoff, const double* __restrict__ PQ, const double* __restrict__ F0L,
+    const double* __restrict__ F0, const long long* __restrict__ loff, double delta,
+    const double* __restrict__ D0, double* __restrict__ Td, double* __restrict__ To,
+    double* __restrict__ E, double* __restrict__ S00, double* __restrict__ thrT) {
+  const int P = N - 1, j = blockIdx.x;
+  if (j < P) assemble_pair(blk, j, P, nb, n0, lsz, tdoff, tooff, eoff, PQ, F0L, loff, delta, Td, To, E, thrT);
+  else assemble_s00(blk, j - P, N, nb, n0, nl, PQ, D0, F0, delta, S00);
 }
 
 __global__ void k_zero_int(int* p) {
@@ -1653,13 +1664,10 @@ void launch_assemble(hipStream_t st, const BlockInfo* blk, int N, int nb, int n0
                      const long long* eoff, const double* PQ, const double* F0L,
                      const double* F0, const long long* loff, double delta, const double* D0,
                      double* Td, double* To, double* E, double* S00, double* thrT) {
-  const int P = N - 1;
-  if (P > 0)
-    hipLaunchKernelGGL(k_assemble_pairs, dim3(P), dim3(256), 0, st, blk, P, nb, n0, lsz, tdoff,
-                       tooff, eoff, PQ, F0L, loff, delta, Td, To, E, thrT);
-  if (nb > 0)
-    hipLaunchKernelGGL(k_assemble_s00, dim3(nb * nb), dim3(256), 0, st, blk, N, nb, n0, nl, PQ,
-                       D0, F0, delta, S00);
+  const int grid = N - 1 + nb * (nb + 1) / 2;
+  if (grid > 0)
+    hipLaunchKernelGGL(k_assemble, dim3(grid), dim3(256), 0, st, blk, N, nb, n0, nl, lsz, tdoff, tooff, eoff,
+                       PQ, F0L, F0, loff, delta, D0, Td, To, E, S00, thrT);
 }
 
 }  // namespace ahlp

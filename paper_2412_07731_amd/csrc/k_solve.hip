@@ -7,7 +7,10 @@
 // x_0 and block rows likewise, so tile products need no bounds checks.
 #include "common.h"
 #include "kernels.h"
+#include "link_rows.h"
 #include "tile_chol.h"
+
+#include <algorithm>
 
 namespace ahlp {
 
@@ -69,8 +72,9 @@ __global__ __launch_bounds__(256) void k_rows_nv(const BlockInfo* __restrict__ b
                                                  const int2* __restrict__ rowtiles, int nrt,
                                                  const double* __restrict__ A,
                                                  const double* __restrict__ C, long long d0off,
-                                                 RowsArgs ra) {
-  const int wt = blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                 RowsArgs ra, const LinkArgs la) {
+  if ((int)blockIdx.x < la.wgs) return link_rows(blk, la, blockIdx.x);
+  const int wt = (blockIdx.x - la.wgs) * 4 + (threadIdx.x >> 6);
   if (wt >= nrt) return;
   const int lane = threadIdx.x & 63, cb = lane >> 3, r2 = 2 * (lane & 7);
   const int2 rt = rowtiles[wt];
@@ -133,53 +137,8 @@ __global__ __launch_bounds__(256) void k_rows_nv(const BlockInfo* __restrict__ b
   }
 }
 
-// The dual rows after the blocks, out = base + alpha * (F xp [+ F0 x0]),
-// 256 threads per workgroup: the link rows, out[pair j, row a] = base + alpha
-// (FR_j xp_j + FL_j xp_{j+1} [+ F0 x0]), a pair per workgroup (its first wave)
-// in the first gridP workgroups; then global row k by workgroup gridP + k,
-// out[nl + k] = base +
-// alpha (sum_i Wg_i xp_i [+ Wg0 x0]), its entries kept as one compressed row
-// over the padded x (gptr, gidx, gval): each thread a fixed strided share,
-// then a fixed reduction tree.  F0 (when given) is the extended (nl + ng) x n0
-// coupling; F0L the same pointer, or null when the link rows' part of it is
-// zero.
-__device__ double block_reduce(int op, double v);
-__global__ __launch_bounds__(256) void k_linkrows(
-    const BlockInfo* __restrict__ blk, int P, int gridP, int n0, const int* __restrict__ lsz,
-    const long long* __restrict__ loff, long long nl, const int* __restrict__ lptr,
-    const int* __restrict__ lcol, const double* __restrict__ lval, const int* __restrict__ gptr,
-    const int* __restrict__ gidx, const double* __restrict__ gval, const double* __restrict__ xp,
-    const double* __restrict__ x0, const double* __restrict__ F0, const double* __restrict__ F0L,
-    const double* __restrict__ base, double alpha, double* __restrict__ out) {
-  if ((int)blockIdx.x >= gridP) {
-    const int k = blockIdx.x - gridP;
-    double v = 0.0;
-    const int e1 = gptr[k + 1];
-    for (int e = gptr[k] + threadIdx.x; e < e1; e += blockDim.x) v += gval[e] * xp[gidx[e]];
-    if (F0 && x0)
-      for (int c = threadIdx.x; c < n0; c += blockDim.x) v += F0[(nl + k) * n0 + c] * x0[c];
-    const double t = block_reduce(0, v);
-    if (threadIdx.x == 0) out[nl + k] = (base ? base[nl + k] : 0.0) + alpha * t;
-    return;
-  }
-  if (threadIdx.x >= 64) return;
-  const int lane = threadIdx.x;
-  for (int j = blockIdx.x; j < P; j += gridP) {
-    const BlockInfo bl = blk[j], br = blk[j + 1];
-    const int l = lsz[j];
-    for (int a = lane; a < l; a += 64) {
-      double s = 0.0;
-      const int qr = TS * bl.ktL + a;   // right section of block j
-      for (int e = lptr[bl.csr_off + qr]; e < lptr[bl.csr_off + qr + 1]; ++e)
-        s += lval[e] * xp[bl.dpoff + lcol[e]];
-      for (int e = lptr[br.csr_off + a]; e < lptr[br.csr_off + a + 1]; ++e)
-        s += lval[e] * xp[br.dpoff + lcol[e]];
-      if (F0L && x0)
-        for (int c = 0; c < n0; ++c) s += F0L[(loff[j] + a) * n0 + c] * x0[c];
-      const long long o = loff[j] + a;
-      out[o] = (base ? base[o] : 0.0) + alpha * s;
-    }
-  }
+__global__ __launch_bounds__(256) void k_linkrows(const BlockInfo* __restrict__ blk, const LinkArgs la) {
+  link_rows(blk, la, blockIdx.x);
 }
 
 // ------------------------------------------------------------ block columns
@@ -639,11 +598,12 @@ __global__ void k_resid_prep(const BlockInfo* __restrict__ blk, int N, int n0, l
 }
 
 // ------------------------------------------------------------ elementwise
-__global__ void k_axpy(long long n, double a, const double* __restrict__ x,
-                       double* __restrict__ y) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
+// y += a x for each vector of the set, one per blockIdx.y
+__global__ void k_axpy(double a, const AxpySet s) {
+  const Axpy& v = s.v[blockIdx.y];
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < v.n;
        i += (long long)gridDim.x * blockDim.x)
-    y[i] += a * x[i];
+    v.y[i] += a * v.x[i];
 }
 
 // The transposed Newton matrix is a diagonal scaling of the Newton matrix:
@@ -864,7 +824,6 @@ __global__ void k_addscalar(long long n, double v, double* __restrict__ dst) {
 // ops: 0 sum a*b, 1 max |a|, 2 min over b<0 of -a/b (inf if none),
 //      3 sum (a + s1 b)(c + s2 d)  [mu_aff], 4 max (a + b), 5 min a,
 //      6 min over b<0 of -a/b and over d<0 of -c/d
-constexpr int RED_BLOCKS = RED_PARTIALS;
 constexpr int RED_THREADS = 256;
 
 __device__ inline double red_combine(int op, double x, double y) {
@@ -874,15 +833,6 @@ __device__ inline double red_identity(int op) {
   return (op == 0 || op == 3) ? 0.0
                               : ((op == 2 || op == 5 || op == 6) ? INFINITY : (op == 4 ? -INFINITY : 0.0));
 }
-
-struct RedArgs {
-  int op;
-  long long n;
-  const double* a; const double* b; const double* c; const double* d;
-  double s1, s2;                        // step lengths (op 3)
-  double* partial;                      // [RED_BLOCKS]
-  double* out;                          // device scalar
-};
 
 __device__ double block_reduce(int op, double v) {
   __shared__ double sh[RED_THREADS / 64];
@@ -941,53 +891,59 @@ __device__ double red_chunk(const R& r, long long lo, long long hi, double s1, d
   }
 }
 
-__global__ __launch_bounds__(RED_THREADS) void k_reduce1(RedArgs r) {
-  const long long chunk = (r.n + gridDim.x - 1) / gridDim.x;
-  const long long lo = blockIdx.x * chunk;
-  const long long hi = lo + chunk < r.n ? lo + chunk : r.n;
-  const double s1 = r.s1, s2 = r.s2;
-  double v = red_chunk(r, lo, hi, s1, s2);
-  v = block_reduce(r.op, v);
-  if (threadIdx.x == 0) r.partial[blockIdx.x] = v;
+// Several independent reductions in one launch: blockIdx.y selects the reduction,
+// whose workgroups are the first red_wgs(n) of that row.  With more than one, the
+// last to arrive combines the partials, in a fixed tree; results do not depend on
+// how many reductions share a launch.  Four elements a thread (ratios are divisions),
+// but few enough workgroups that their arrivals do not queue: 70 sets of up to nine
+// reductions of 520 elements 9.5 -> 4.8 us each against two launches of 256
+// workgroups, of 262144 elements 10.8 -> 8.8 us (20.8 us with 256 workgroups, 12.9
+// with 16384 elements each).
+__host__ __device__ inline int red_wgs(long long n) {
+  const long long w = (n + 4 * RED_THREADS - 1) / (4 * RED_THREADS);
+  return w < 1 ? 1 : w > RED_PARTIALS ? RED_PARTIALS : (int)w;
 }
-
-__global__ __launch_bounds__(RED_THREADS) void k_reduce2(RedArgs r, int nparts) {
-  double v = red_identity(r.op);
-  for (int i = threadIdx.x; i < nparts; i += blockDim.x) v = red_combine(r.op, v, r.partial[i]);
-  v = block_reduce(r.op, v);
-  if (threadIdx.x == 0) *r.out = v;
-}
-
-// Several independent reductions in one pair of launches: blockIdx.y selects
-// the reduction; the per-reduction work split and trees are the same fixed
-// ones as k_reduce1/k_reduce2, so results do not depend on how many share a
-// launch.
-__global__ __launch_bounds__(RED_THREADS) void k_mreduce1(MultiRed m) {
+__global__ __launch_bounds__(RED_THREADS) void k_mreduce(const MultiRed m) {
   const RedSpec& r = m.r[blockIdx.y];
-  const long long chunk = (r.n + gridDim.x - 1) / gridDim.x;
+  const int wgs = red_wgs(r.n);
+  if ((int)blockIdx.x >= wgs) return;
+  const long long chunk = (r.n + wgs - 1) / wgs;
   const long long lo = blockIdx.x * chunk;
   const long long hi = lo + chunk < r.n ? lo + chunk : r.n;
   const double s1 = r.ps1 ? fmin(1.0, *r.ps1) : r.s1;
   const double s2 = r.ps2 ? fmin(1.0, *r.ps2) : r.s2;
   double v = red_chunk(r, lo, hi, s1, s2);
   v = block_reduce(r.op, v);
-  if (threadIdx.x == 0) m.partial[(long long)blockIdx.y * gridDim.x + blockIdx.x] = v;
-}
-
-__global__ __launch_bounds__(RED_THREADS) void k_mreduce2(MultiRed m, int nparts) {
-  const RedSpec& r = m.r[blockIdx.x];
-  double v = red_identity(r.op);
-  for (int i = threadIdx.x; i < nparts; i += blockDim.x)
-    v = red_combine(r.op, v, m.partial[(long long)blockIdx.x * nparts + i]);
-  v = block_reduce(r.op, v);
+  if (wgs > 1) {
+    __shared__ bool last;
+    double* part = m.partial + (long long)blockIdx.y * RED_PARTIALS;
+    if (threadIdx.x == 0) {
+      // the partial is written through to where all compute units see it, and is
+      // there before the arrival counts; a release fence would write back the
+      // whole L2 (70 us on a refined solve of 512 blocks)
+      __hip_atomic_store(part + blockIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#if defined(__HIP_DEVICE_COMPILE__)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+      last = __hip_atomic_fetch_add(m.arrived + RED_APART * blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == wgs - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    v = red_identity(r.op);
+    for (int i = threadIdx.x; i < wgs; i += blockDim.x)
+      v = red_combine(r.op, v, __hip_atomic_load(part + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    v = block_reduce(r.op, v);
+    if (threadIdx.x == 0) m.arrived[RED_APART * blockIdx.y] = 0;   // for the next launch
+  }
   if (threadIdx.x == 0) m.out[r.slot] = v;
 }
 
 // ------------------------------------------------------------ launchers
 void launch_mreduce(hipStream_t st, const MultiRed& m) {
   if (m.nred <= 0) return;
-  hipLaunchKernelGGL(k_mreduce1, dim3(RED_BLOCKS, m.nred), dim3(RED_THREADS), 0, st, m);
-  hipLaunchKernelGGL(k_mreduce2, dim3(m.nred), dim3(RED_THREADS), 0, st, m, RED_BLOCKS);
+  int wgs = 1;
+  for (int k = 0; k < m.nred; ++k) wgs = std::max(wgs, red_wgs(m.r[k].n));
+  hipLaunchKernelGGL(k_mreduce, dim3(wgs, m.nred), dim3(RED_THREADS), 0, st, m);
 }
 
 static inline int grid1d(long long n) {
@@ -1052,30 +1008,16 @@ void launch_rhx(hipStream_t st, const BlockInfo* blk, int N, int n0, long long x
                      Dp, rhx, vx);
 }
 void launch_rows_multi(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
-                       const double* A, const double* C, long long d0off, const RowsArgs& ra) {
-  const dim3 g((nrt + 3) / 4), b(256);
-  if (ra.nv == 1) hipLaunchKernelGGL(k_rows_nv<1>, g, b, 0, st, blk, rowtiles, nrt, A, C, d0off, ra);
-  else if (ra.nv == 2) hipLaunchKernelGGL(k_rows_nv<2>, g, b, 0, st, blk, rowtiles, nrt, A, C, d0off, ra);
-  else hipLaunchKernelGGL(k_rows_nv<3>, g, b, 0, st, blk, rowtiles, nrt, A, C, d0off, ra);
+                       const double* A, const double* C, long long d0off, const RowsArgs& ra,
+                       const LinkArgs& la) {
+  const dim3 g((nrt + 3) / 4 + la.wgs), b(256);
+  if (ra.nv == 1) hipLaunchKernelGGL(k_rows_nv<1>, g, b, 0, st, blk, rowtiles, nrt, A, C, d0off, ra, la);
+  else if (ra.nv == 2) hipLaunchKernelGGL(k_rows_nv<2>, g, b, 0, st, blk, rowtiles, nrt, A, C, d0off, ra, la);
+  else hipLaunchKernelGGL(k_rows_nv<3>, g, b, 0, st, blk, rowtiles, nrt, A, C, d0off, ra, la);
 }
-void launch_rows(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
-                 const double* A, const double* C, const double* xp, long long d0off,
-                 const double* base, double alpha, int with_C, int padded_out, double* out) {
-  RowsArgs ra{};
-  ra.nv = 1;
-  ra.v[0] = xp; ra.base[0] = base; ra.alpha[0] = alpha; ra.out[0] = out;
-  ra.with_C[0] = with_C; ra.padded[0] = padded_out; ra.chain[0] = 0;
-  launch_rows_multi(st, blk, rowtiles, nrt, A, C, d0off, ra);
-}
-void launch_linkrows(hipStream_t st, const BlockInfo* blk, int P, int ng, int n0,
-                     const int* lsz, const long long* loff, long long nl, const int* lptr,
-                     const int* lcol, const double* lval, const int* gptr, const int* gidx,
-                     const double* gval, const double* xp, const double* x0, const double* F0,
-                     const double* F0L, const double* base, double alpha, double* out) {
-  const int gridP = P > 0 ? (P < 1024 ? P : 1024) : 0;
-  if (gridP + ng <= 0) return;
-  hipLaunchKernelGGL(k_linkrows, dim3(gridP + ng), dim3(256), 0, st, blk, P, gridP, n0, lsz, loff,
-                     nl, lptr, lcol, lval, gptr, gidx, gval, xp, x0, F0, F0L, base, alpha, out);
+int link_wgs(int P, int ng) { return ng + std::min((P + 3) / 4, 256); }
+void launch_linkrows(hipStream_t st, const BlockInfo* blk, const LinkArgs& la) {
+  if (la.wgs > 0) hipLaunchKernelGGL(k_linkrows, dim3(la.wgs), dim3(256), 0, st, blk, la);
 }
 void launch_cols(hipStream_t st, const BlockInfo* blk, const int2* coltiles, int nct,
                  const double* A, const double* yp, const double* yL, const int* cptr,
@@ -1172,7 +1114,17 @@ void launch_adj_scale(hipStream_t st, long long n, int mode, const double* zs, c
   if (n > 0) hipLaunchKernelGGL(k_adj_scale, dim3(grid1d(n)), dim3(256), 0, st, n, mode, zs, v, out);
 }
 void launch_axpy(hipStream_t st, long long n, double a, const double* x, double* y) {
-  if (n > 0) hipLaunchKernelGGL(k_axpy, dim3(grid1d(n)), dim3(256), 0, st, n, a, x, y);
+  launch_axpys(st, a, {{n, x, y}});
+}
+void launch_axpys(hipStream_t st, double a, std::initializer_list<Axpy> list) {
+  AxpySet s{};
+  long long most = 0;
+  int k = 0;
+  for (const Axpy& v : list) {
+    s.v[k++] = v;
+    most = std::max(most, v.n);
+  }
+  if (most > 0) hipLaunchKernelGGL(k_axpy, dim3(grid1d(most), k), dim3(256), 0, st, a, s);
 }
 void launch_dz(hipStream_t st, long long n, const double* rz, const double* zs, const double* xs,
                const double* dx, double* dz) {
@@ -1203,13 +1155,6 @@ void launch_fill(hipStream_t st, long long n, double v, double* dst) {
 }
 void launch_addscalar(hipStream_t st, long long n, double v, double* dst) {
   if (n > 0) hipLaunchKernelGGL(k_addscalar, dim3(grid1d(n)), dim3(256), 0, st, n, v, dst);
-}
-void launch_reduce(hipStream_t st, int op, long long n, const double* a, const double* b,
-                   const double* c, const double* d, double s1, double s2,
-                   double* partial, double* out) {
-  RedArgs r{op, n, a, b, c, d, s1, s2, partial, out};
-  hipLaunchKernelGGL(k_reduce1, dim3(RED_BLOCKS), dim3(RED_THREADS), 0, st, r);
-  hipLaunchKernelGGL(k_reduce2, dim3(1), dim3(RED_THREADS), 0, st, r, RED_BLOCKS);
 }
 
 }  // namespace ahlp

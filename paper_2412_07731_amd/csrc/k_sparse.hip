@@ -17,6 +17,7 @@
 // sparse_setup in the host driver states when the copy is used.
 #include "common.h"
 #include "kernels.h"
+#include "link_rows.h"
 
 namespace ahlp {
 
@@ -165,10 +166,11 @@ __device__ __forceinline__ void sp_slices(const double* __restrict__ val,
 // time.  A vector that does not take the x_0 columns has zeros staged there.
 template <int NV>
 __global__ __launch_bounds__(256) void k_sp_rows(const BlockInfo* __restrict__ blk, const SpMat sp,
-                                                 long long d0off, RowsArgs ra) {
+                                                 long long d0off, RowsArgs ra, const LinkArgs la) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* v = reinterpret_cast<double*>(smem_raw);
-  const int4 it = sp.row_items[blockIdx.x];   // block, first tile row, end, slice of the first
+  if ((int)blockIdx.x < la.wgs) return link_rows(blk, la, blockIdx.x);
+  const int4 it = sp.row_items[blockIdx.x - la.wgs];   // block, first tile row, end, slice of the first
   const BlockInfo b = blk[it.x];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -249,12 +251,12 @@ void launch_sp_fill(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, 
 }
 
 void launch_sp_rows(hipStream_t st, const BlockInfo* blk, const SpMat& sp, long long d0off,
-                    const RowsArgs& ra) {
+                    const RowsArgs& ra, const LinkArgs& la) {
   const size_t sh = (size_t)ra.nv * sp.max_cols * sizeof(double);
-  const dim3 g(sp.nrow_items), b(256);
-  if (ra.nv == 1) hipLaunchKernelGGL(k_sp_rows<1>, g, b, sh, st, blk, sp, d0off, ra);
-  else if (ra.nv == 2) hipLaunchKernelGGL(k_sp_rows<2>, g, b, sh, st, blk, sp, d0off, ra);
-  else hipLaunchKernelGGL(k_sp_rows<3>, g, b, sh, st, blk, sp, d0off, ra);
+  const dim3 g(sp.nrow_items + la.wgs), b(256);
+  if (ra.nv == 1) hipLaunchKernelGGL(k_sp_rows<1>, g, b, sh, st, blk, sp, d0off, ra, la);
+  else if (ra.nv == 2) hipLaunchKernelGGL(k_sp_rows<2>, g, b, sh, st, blk, sp, d0off, ra, la);
+  else hipLaunchKernelGGL(k_sp_rows<3>, g, b, sh, st, blk, sp, d0off, ra, la);
 }
 
 void launch_sp_cols(hipStream_t st, const BlockInfo* blk, const SpMat& sp, const double* yp,

@@ -1,6 +1,8 @@
 // Host-callable launchers of the device kernels (one stream each).
 #pragma once
 
+#include <initializer_list>
+
 #include "common.h"
 
 namespace ahlp {
@@ -240,19 +242,26 @@ struct BndArgs {
   int mode;              // 0: predictor (r_sw = -SWe), 1: corrector
 };
 void launch_steps(hipStream_t st, double eta, const StepSet& s);
+// The dual rows after the blocks, out = base + alpha (F xp [+ F0 x0]): link rows, then
+// the ng global rows (base and out at the first link row).
+struct LinkArgs {
+  int P, ng, n0, wgs;             // wgs: workgroups it takes (0: none)
+  const int* lsz; const long long* loff; long long nl;
+  const int* lptr; const int* lcol; const double* lval;   // link rows by block, compressed
+  const int* gptr; const int* gidx; const double* gval;   // global rows over the padded x
+  const double* xp; const double* x0;
+  const double* F0; const double* F0L;   // x_0 coupling ((nl + ng) x n0); of the link rows, or null
+  const double* base; double alpha; double* out;
+};
+int link_wgs(int P, int ng);
+void launch_linkrows(hipStream_t st, const BlockInfo* blk, const LinkArgs& la);
+// The row passes take the link and global rows along, in workgroups of their own.
 void launch_rows_multi(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
-                       const double* A, const double* C, long long d0off, const RowsArgs& ra);
-void launch_rows(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
-                 const double* A, const double* C, const double* xp, long long d0off,
-                 const double* base, double alpha, int with_C, int padded_out, double* out);
+                       const double* A, const double* C, long long d0off, const RowsArgs& ra, const LinkArgs& la);
 // the dual rows after the blocks (link rows, then global rows):
 // out = base + alpha (F xp [+ F0 x0]); F0 the extended (nl + ng) x n0 coupling,
 // F0L the same or null when its link rows are zero
-void launch_linkrows(hipStream_t st, const BlockInfo* blk, int P, int ng, int n0,
-                     const int* lsz, const long long* loff, long long nl, const int* lptr,
-                     const int* lcol, const double* lval, const int* gptr, const int* gidx,
-                     const double* gval, const double* xp, const double* x0, const double* F0,
-                     const double* F0L, const double* base, double alpha, double* out);
+
 // Optional fused output of the column pass (mode 2): dz = (rz - zs dx) / xs
 struct DzArgs {
   const double* rz; const double* zs; const double* xs; double* dz;
@@ -288,7 +297,7 @@ void launch_sp_fill(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, 
                     const int2* coltiles, int nct, const double* A, const double* C,
                     const SpMat& sp);
 void launch_sp_rows(hipStream_t st, const BlockInfo* blk, const SpMat& sp, long long d0off,
-                    const RowsArgs& ra);
+                    const RowsArgs& ra, const LinkArgs& la);
 void launch_sp_cols(hipStream_t st, const BlockInfo* blk, const SpMat& sp, const double* yp,
                     const ColsArgs& ca);
 void launch_ccols(hipStream_t st, const BlockInfo* blk, const int2* ctiles, int nctile, int n0,
@@ -327,6 +336,10 @@ void launch_resid_prep(hipStream_t st, const BlockInfo* blk, int N, int n0, long
                        const double* xs, const double* Dp, double* rzv, double* rhx, double* vx,
                        double* w1p, double* xp, const BndArgs& b, double* rdt_out);
 void launch_axpy(hipStream_t st, long long n, double a, const double* x, double* y);
+// the same for up to four vectors in one launch
+struct Axpy { long long n; const double* x; double* y; };
+struct AxpySet { Axpy v[4]; };
+void launch_axpys(hipStream_t st, double a, std::initializer_list<Axpy> list);
 // mode 0: out = zs * v; mode 1: out = v / zs (the diagonal scalings that turn
 // the transposed Newton solve into a Newton solve)
 void launch_adj_scale(hipStream_t st, long long n, int mode, const double* zs, const double* v,
@@ -360,10 +373,6 @@ void launch_bnd_shift(hipStream_t st, long long n, const double* ub, double a, d
                       double* x, double* z, double* s, double* w, double* sm, double* wm);
 void launch_fill(hipStream_t st, long long n, double v, double* dst);
 void launch_addscalar(hipStream_t st, long long n, double v, double* dst);
-void launch_reduce(hipStream_t st, int op, long long n, const double* a, const double* b,
-                   const double* c, const double* d, double s1, double s2, double* partial,
-                   double* out);
-
 struct RedSpec {
   int op, slot;          // operation, output slot
   long long n;
@@ -373,10 +382,12 @@ struct RedSpec {
   const double* ps2;     // read from the device (results of an earlier reduction)
 };
 constexpr int MAXRED = 16;
+constexpr int RED_APART = 32;   // a line of memory each
 struct MultiRed {
   int nred;
   RedSpec r[MAXRED];
   double* partial;       // [MAXRED * RED_PARTIALS]
+  int* arrived;          // [MAXRED], RED_APART apart, zero between launches
   double* out;
 };
 void launch_mreduce(hipStream_t st, const MultiRed& m);
@@ -384,7 +395,7 @@ void launch_mreduce(hipStream_t st, const MultiRed& m);
 // RED_RATIO2: the ratio test over two pairs, min over i of -a/b (b < 0) and -c/d (d < 0)
 enum RedOp { RED_DOT = 0, RED_MAXABS = 1, RED_RATIO = 2, RED_MUAFF = 3, RED_MAXSUM = 4, RED_MIN = 5,
              RED_RATIO2 = 6 };
-constexpr int RED_PARTIALS = 256;
+constexpr int RED_PARTIALS = 64;
 
 // ---- static workspace (noalloc.hip)
 // Size of the per-device static array that ahlp_kkt_solve_noalloc works in.
