@@ -19,17 +19,18 @@
 // multiply-adds and one sum over g.
 // Measured against one launch per level, a tail of the last 32 pairs and a
 // launch for the blocks' part of the right-hand side, kernel time in us per
-// solve: 7 pairs, border 8: 16.9 -> 8.3; 511 of 16 rows, border 32: 77 -> 39;
-// 2189 of 2-8 rows, border 12: 96 -> 44; 511 of 4-32 rows, border 64: 124 -> 69;
-// 95 of 33-56 rows, border 24: 105 -> 71.  What is left is the launches and the
-// tiles: one compute unit loads 32 positions of the last stage twice (16 us of
-// the 21; 9 us with 8 positions).  Smaller groups trade that for launches: at
-// most 4 or 3 levels a stage measures within 2%, 2 levels 3 to 7% worse.
+// solve: 7 pairs, border 8: 16.9 -> 8.3; 63 of 8 rows, border 22: 43 -> 21; 511 of
+// 16 rows, border 32: 77 -> 37; 2189 of 2-8 rows, border 12: 96 -> 39; 511 of 4-32
+// rows, border 64: 124 -> 68; 95 of 33-56 rows, border 24: 105 -> 70.  What is left
+// is the launches and the tiles, which one compute unit loads twice in the last
+// stage: with 32 positions there 21 us, with 8 9 us.
 #include "bcr_geo.h"
 #include "common.h"
 #include "kernels.h"
 #include "tile_chol.h"
 #include "tile_ops.h"
+
+#include <algorithm>
 
 namespace ahlp {
 
@@ -535,17 +536,18 @@ int levels(int n) {   // ceil(log2 n)
   return v;
 }
 
-// As few stages as the groups allow; the levels before the last stage are split
-// evenly, the fewer first, where there are most groups to fill the chip.
+// As few stages as the groups allow, the levels split evenly over them: the last
+// stage, one compute unit that loads its tiles for both directions, gets the fewest,
+// then the first, which has the most groups.
 template <int TP, int NP, int T0M>
 void solve_tp(hipStream_t st, const BcrSolveArgs& a) {
   typedef Grp<TP, NP> R;
   const int total = levels(a.c.P), before = total > R::LLEV ? total - R::LLEV : 0;
-  const int stages = (before + R::LEV - 1) / R::LEV;
+  const int stages = (before + R::LEV - 1) / R::LEV, ahead = total - std::min(total / (stages + 1), R::LLEV);
   int lvl = 0, n = a.c.P, slots = 0, lv[32], ln[32], lg[32];
   double* out[2] = {a.up, a.w};
   for (int s = 0; s < stages; ++s) {
-    const int lev = (before - lvl) / (stages - s), groups = (n + (1 << lev) - 1) >> lev;
+    const int lev = (ahead - lvl) / (stages - s), groups = (n + (1 << lev) - 1) >> lev;
     lv[s] = lvl; ln[s] = n; lg[s] = lev;
     hipLaunchKernelGGL((k_bcrs_fwd<TP, NP, T0M>), dim3(groups), dim3(64 * ((1 << lev) - R::OFF) * TP / NP), 0, st, a, lvl, n, lev,
                        slots, out[(s + 1) & 1], out[s & 1]);
