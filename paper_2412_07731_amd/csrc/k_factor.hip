@@ -651,9 +651,9 @@ __device__ __forceinline__ void schur_rows(const BlockInfo& b, const T* __restri
 // Two workgroups share a CU, so one block's tile Cholesky overlaps the
 // other's MFMA work.  The kernel ends with the block's Schur contribution
 // (schur_rows), so no separate a5 product pass is needed on this path.
-// BF_RMAX is a template parameter: 5 (blocks of up to 20 tile rows) or 6 (up
-// to 24, where the sixth row's accumulators fill the 256 VGPRs); a launch takes
-// the smaller that fits its widest block.
+// BF_RMAX is a template parameter: 2 (blocks of up to 8 tile rows), 5 (up to 20) or
+// 6 (up to 24, where the sixth row's accumulators fill the 256 VGPRs); a launch
+// takes the smallest that fits its widest block.
 constexpr int BF_PW = 2, BF_RMAX_MAX = 6;
 static_assert(BF_PW == 2, "the pipelined panel update takes its steps in pairs");
 // The panel kernel's LDS tiles are column-major with leading dimension 17:
@@ -973,7 +973,7 @@ __device__ __forceinline__ void panel_factor(const BlockInfo& b, T* __restrict__
             st_acc(dt, acc[t][j]);
           }
         wave_order();
-        cnt += wave_chol_tile<T, LD, false, true, (BF_RMAX >= 6)>(dt, dt, li, thr);
+        cnt += wave_chol_tile<T, LD, false, true, (BF_RMAX != 5)>(dt, dt, li, thr);
       }
       sy.sync();
       // rows below: L(r, c) = acc(r, c) L_cc^-T
@@ -1071,11 +1071,15 @@ __device__ __forceinline__ void panel_factor(const BlockInfo& b, T* __restrict__
   if (lane == 0 && cnt) atomicAdd(&info->pivots, cnt);
 }
 
-// Standalone panel kernel: NW waves per block (4: two workgroups per CU, for
+// Workgroups per CU that the panel kernel's registers are cut for.  Blocks of up to
+// 8 tile rows come by the thousand, and their chains hide each other: 2190 blocks of
+// 20-60 rows take 55 us with three a CU, 69 with two (and 88 with four, which spills).
+constexpr int bf_per_cu(int rmax, int nw) { return nw == 8 ? 1 : rmax == 2 ? 3 : 2; }
+// Standalone panel kernel: NW waves per block (4: several workgroups per CU, for
 // bordered blocks of up to 4 BF_RMAX tile rows; 8: one per CU, up to
 // 8 BF_RMAX).
 template <typename T, int BF_RMAX, int NW>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void k_block_factor_panel(
+__global__ __launch_bounds__(64 * NW, bf_per_cu(BF_RMAX, NW) * NW / 4) void k_block_factor_panel(
     const BlockInfo* __restrict__ blk, const int* __restrict__ order, T* __restrict__ LB,
     T* __restrict__ LINV, double* __restrict__ PQ, DevInfo* info, int sch_cap) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1571,26 +1575,21 @@ void launch_block_factor_panel(hipStream_t st, const BlockInfo* blk, const int* 
   // LDS: the panel column (max_rt tiles), L_cc^-1, the diagonal tile and one
   // per-wave tile, at the form's leading dimension; then as many FP64
   // Schur-contribution tiles as fit beside it without lowering the
-  // occupancy the launch bounds ask for (two four-wave workgroups or one
-  // eight-wave workgroup per CU, of the CU's 160 KiB)
+  // occupancy the launch bounds ask for (of the CU's 160 KiB)
   const size_t tile = (size_t)TS * BfLd<5>::LD * sizeof(T);
   const size_t base = (size_t)(max_rt + 2 + waves) * tile;
-  const size_t budget = (waves == 8 ? 156 : 78) * 1024;
+  const int rmax = waves == 8 ? 5 : max_rt <= 8 ? 2 : max_rt <= 20 ? 5 : 6;
+  const size_t budget = 156 / bf_per_cu(rmax, waves) * 1024;
   const size_t tile64 = (size_t)TS * BfLd<5>::LD * sizeof(double);
   int cap = 0;
   if (budget > base) cap = (int)((budget - base) / tile64);
   if (max_kt >= 0) cap = std::min(cap, max_kt * (max_kt + 1) / 2);
   const size_t shmem = base + (size_t)cap * tile64;
-  if (waves == 8) {
-    hipLaunchKernelGGL((k_block_factor_panel<T, 5, 8>), dim3(n), dim3(512), shmem, st, blk, order,
-                       LB, LINV, PQ, info, cap);
-  } else if (max_rt <= 20) {
-    hipLaunchKernelGGL((k_block_factor_panel<T, 5, 4>), dim3(n), dim3(256), shmem, st, blk, order,
-                       LB, LINV, PQ, info, cap);
-  } else {
-    hipLaunchKernelGGL((k_block_factor_panel<T, 6, 4>), dim3(n), dim3(256), shmem, st, blk, order,
-                       LB, LINV, PQ, info, cap);
-  }
+  const auto kernel = waves == 8  ? k_block_factor_panel<T, 5, 8>
+                      : rmax == 2 ? k_block_factor_panel<T, 2, 4>
+                      : rmax == 5 ? k_block_factor_panel<T, 5, 4>
+                                  : k_block_factor_panel<T, 6, 4>;
+  hipLaunchKernelGGL(kernel, dim3(n), dim3(64 * waves), shmem, st, blk, order, LB, LINV, PQ, info, cap);
 }
 // The fused launch over the panel bucket (blocks order[0, n), bordered tile
 // rows at most max_rt <= 4 BF_RMAX_MAX, tile columns at most 2 FUSED_MTP):

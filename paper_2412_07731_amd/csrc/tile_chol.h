@@ -253,7 +253,7 @@ __device__ __forceinline__ int chol_tile_f32(const float* P, float* L, float* Li
 // The rule costs a pivot five instructions on the chain and is seldom applied, so
 // an FP64 tile is factorized without it first, and again with it if any pivot falls
 // under it (ONCE: with it at once, half the code, for kernels whose registers the
-// two don't fit: the panels of six tiles, 240 against 218 us).
+// two don't fit: the panels of six tiles a wave, 240 against 218 us, and of two).
 template <typename T, int LD = TS, bool SG = false, bool WL = true, bool ONCE = false>
 __device__ __forceinline__ int wave_chol_tile(const T* P, T* L, T* Li, double thr, unsigned neg = 0) {
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
