@@ -306,39 +306,64 @@ __global__ __launch_bounds__(256) void k_link(const BlockInfo* __restrict__ blk,
 // ---------------------------------------------------------------- a3 + a4
 // Tall bordered blocks (more tile rows than the panel kernels hold): left-
 // looking over panels of TALL_W tile columns, one launch per panel, several
-// workgroups per block.  Every workgroup of a block updates and factors the
-// panel's diagonal block for itself (the same arithmetic, so the same values)
-// and takes eight of the tile rows below, one per wave, through the update by
-// the earlier columns and the solve with the diagonal block.  A tile column of
-// the panel (TALL_W tiles) is shared by the eight waves through LDS, staged two
-// columns ahead by direct-to-LDS loads; a row's own tile comes straight to
-// registers.  Rows are kept transposed in the accumulators, where a tile of X'
-// is laid out as the next product's B operand, so the solve stays in
+// workgroups per block.  Every workgroup of a block factors the panel's
+// diagonal block for itself (the same arithmetic, so the same values) and
+// takes four of the tile rows below, one per wave, through the update by
+// the earlier columns and the solve with the diagonal block.  The four rows are
+// those of a later panel's diagonal block, which the workgroup then updates by
+// this panel's columns, so that a panel finds its diagonal block up to date.  A
+// tile column of the panel (TALL_W tiles) is shared by the waves through LDS,
+// staged two columns ahead by direct-to-LDS loads; a row's own tile comes
+// straight to registers.  Rows are kept transposed in the accumulators, where a
+// tile of X' is laid out as the next product's B operand, so the solve stays in
 // registers.  With few tall blocks the chain of a block is what bounds a
-// factorization; one workgroup per block and one tile column at a time (the
-// form this replaces) left 208 of 256 CUs idle: 48 blocks of 600-900 rows took
-// 4.67 ms, now 1.10 ms in 16 launches, which the MFMA work of the CUs with two
-// workgroups bounds (three times the balanced 0.35 ms).
+// factorization; one workgroup per block and one tile column at a time left 208
+// of 256 CUs idle: 48 blocks of 600-900 rows took 4.67 ms, and 1.04 ms in 16
+// launches of workgroups of eight rows that each updated the diagonal block by
+// all earlier columns; now 0.91 ms, of which the diagonal blocks' factors are a
+// third (20 us a launch, twice where a unit has several workgroups in turn).
 //
 // The diagonal block's factor must not overwrite its input while other
 // workgroups of the launch may still read it: it goes to a scratch slot of the
 // block (two slots, alternating) and the next launch's first workgroup copies
 // it into place.  Columns < c0 of the factor's diagonal tiles are read by
 // nobody until then.
-constexpr int TALL_W = 4, TALL_NW = 8, TALL_ND = TALL_W * (TALL_W + 1) / 2;
+constexpr int TALL_W = 4, TALL_NW = 4, TALL_ND = TALL_W * (TALL_W + 1) / 2;
 constexpr int TALL_KS = 2;   // tile columns per stage (c0 is a multiple of it)
+
+static_assert(TALL_NW == TALL_W, "a workgroup's rows are a diagonal block's");
+
+// pivot threshold of each block from the largest real diagonal entry of M_i
+template <typename T>
+__global__ __launch_bounds__(256) void k_tall_thr(const BlockInfo* __restrict__ blk,
+                                                  const int* __restrict__ order,
+                                                  const T* __restrict__ LB, double* __restrict__ bthr) {
+  __shared__ double s_max[4];
+  const BlockInfo b = blk[order[blockIdx.x]];
+  double md = 0.0;
+  for (int idx = threadIdx.x; idx < b.m; idx += 256)
+    md = fmax(md, (double)LB[lb_tile(b, idx >> 4, idx >> 4) + (idx & 15) * 17]);
+  for (int off = 32; off > 0; off >>= 1) md = fmax(md, __shfl_xor(md, off));
+  if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = md;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    bthr[order[blockIdx.x]] = PIVOT_REL * fmax(fmax(s_max[0], s_max[1]), fmax(s_max[2], s_max[3]));
+}
 
 template <typename T>
 __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
     const BlockInfo* __restrict__ blk, const int* __restrict__ order, T* LB,
-    T* __restrict__ LINV, double* __restrict__ bthr, T* __restrict__ scratch, DevInfo* info,
+    T* __restrict__ LINV, const double* __restrict__ bthr, T* __restrict__ scratch, DevInfo* info,
     int c0) {
   constexpr int LD = TS + 1, TEP = TS * LD, AST = sizeof(T) == 8 ? 4 : 1;
   typedef typename Acc<T>::type AT;
-  __shared__ __align__(16) T stg0[TALL_KS * TALL_W * TE], stg1[TALL_KS * TALL_W * TE];
+  // two stages of the panel's tiles; then the rows' tiles of this panel
+  __shared__ __align__(16) T stg[2 * TALL_KS * TALL_W * TE];
+  static_assert(TALL_NW * TALL_W <= 2 * TALL_KS * TALL_W, "the rows' tiles fit");
+  T* const stg0 = stg;
+  T* const stg1 = stg + TALL_KS * TALL_W * TE;
   __shared__ T Bd[TALL_ND * TEP];    // diagonal block: lower tiles (r, c) at r (r + 1) / 2 + c
   __shared__ T Ld[TALL_W * TEP];     // inverted diagonal tiles
-  __shared__ double s_max[TALL_NW];
   const BlockInfo b = blk[order[blockIdx.y]];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -358,24 +383,7 @@ __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
   const int pw = min(TALL_W, b.mt - c0), r0 = c0 + pw, nrow = b.rt - r0;
   if (blockIdx.x > 0 && (int)blockIdx.x * TALL_NW >= nrow) return;
 
-  // pivot threshold from the largest real diagonal entry of M_i
-  double thr;
-  if (c0 == 0) {
-    double md = 0.0;
-    for (int idx = tid; idx < b.m; idx += 64 * TALL_NW) {
-      const int p = idx >> 4, i = idx & 15;
-      md = fmax(md, (double)LB[lb_tile(b, p, p) + i * 17]);
-    }
-    for (int off = 32; off > 0; off >>= 1) md = fmax(md, __shfl_xor(md, off));
-    if (lane == 0) s_max[w] = md;
-    __syncthreads();
-    md = 0.0;
-    for (int k = 0; k < TALL_NW; ++k) md = fmax(md, s_max[k]);
-    thr = PIVOT_REL * md;
-    if (tid == 0 && blockIdx.x == 0) bthr[order[blockIdx.y]] = thr;
-  } else {
-    thr = bthr[order[blockIdx.y]];
-  }
+  const double thr = bthr[order[blockIdx.y]];
 
   // stage tile columns k .. k + TALL_KS - 1 of the panel rows c0 + i: 16 bytes
   // per thread and load, tile t = kk * TALL_W + i (rows past the block's last
@@ -401,8 +409,8 @@ __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
     const int r = r0 + rb + w;
     const bool row = rb + w < nrow;
     const int rc = min(r, b.rt - 1);
-    // this wave's row of the panel, transposed, and its diagonal tiles
-    AT acc[TALL_W], da[2];
+    // this wave's row of the panel, transposed
+    AT acc[TALL_W];
 #pragma unroll
     for (int j = 0; j < TALL_W; ++j) {
       acc[j] = AT{0, 0, 0, 0};
@@ -411,20 +419,16 @@ __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
         for (int k = 0; k < 4; ++k)
           acc[j][k] = LB[lb_tile(b, r, c0 + j) + acc_row<T>(lane, k) * TS + (lane & 15)];
     }
-    int dr[2], dc[2];
+    if (first)   // the diagonal block, up to date with the earlier panels
+      for (int u = w; u < TALL_ND; u += TALL_NW) {
+        int i = 0;
+        while ((i + 1) * (i + 2) / 2 <= u) ++i;
+        const int j = u - i * (i + 1) / 2;
+        if (i >= pw) break;
+        const T* src = LB + lb_tile(b, c0 + i, c0 + j);
 #pragma unroll
-    for (int d = 0; d < 2; ++d) {
-      const int u = w + TALL_NW * d;
-      dr[d] = 0;
-      while ((dr[d] + 1) * (dr[d] + 2) / 2 <= u) ++dr[d];
-      dc[d] = u - dr[d] * (dr[d] + 1) / 2;
-      da[d] = AT{0, 0, 0, 0};
-      if (first && dr[d] < pw) {
-        const T* src = LB + lb_tile(b, c0 + dr[d], c0 + dc[d]);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) da[d][k] = src[acc_index<T>(lane, k)];
+        for (int k = 0; k < 4; ++k) Bd[u * TEP + lane + (lane >> 4) + 68 * k] = src[64 * k + lane];
       }
-    }
     T own[TALL_KS][4], nxt[TALL_KS][4];
     auto load_own = [&](T (*o)[4], int k) {
 #pragma unroll
@@ -452,16 +456,6 @@ __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
             for (int j = 0; j < TALL_W; ++j)
               acc[j] = mfma(-P[j * TE + 64 * s + lane], own[kk][s], acc[j]);
         }
-        if (first) {
-#pragma unroll
-          for (int d = 0; d < 2; ++d)
-            if (dr[d] < pw) {
-              const T* X = P + dr[d] * TE;
-              const T* Y = P + dc[d] * TE;
-#pragma unroll
-              for (int s = 0; s < 4; ++s) da[d] = mfma(-X[64 * s + lane], Y[64 * s + lane], da[d]);
-            }
-        }
       }
 #pragma unroll
       for (int kk = 0; kk < TALL_KS; ++kk)
@@ -483,13 +477,6 @@ __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
     if (first) {
       // factor the diagonal block: wave 0 the diagonal tiles, the others the
       // tile column below and the trailing tiles
-#pragma unroll
-      for (int d = 0; d < 2; ++d)
-        if (dr[d] < pw) {
-          T* t = Bd + tl(dr[d], dc[d]) * TEP;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) t[wb + AST * k] = da[d][k];
-        }
       __syncthreads();
       const int rbp = lane + (lane >> 4);   // operand element s of a padded tile at rbp + 68 s
       for (int p = 0; p < pw; ++p) {
@@ -562,9 +549,34 @@ __global__ __launch_bounds__(64 * TALL_NW, 2) void k_tall_panel(
         acc[j] = x;
         T* dst = LB + lb_tile(b, r, c0 + j);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) dst[acc_row<T>(lane, k) * TS + (lane & 15)] = x[k];
+        for (int k = 0; k < 4; ++k) {
+          dst[acc_row<T>(lane, k) * TS + (lane & 15)] = x[k];
+          stg[(w * TALL_W + j) * TE + acc_row<T>(lane, k) * TS + (lane & 15)] = x[k];
+        }
       }
     }
+    // the diagonal block of these rows: minus X_i X_j' of this panel
+    const int nr = min(TALL_NW, b.mt - (r0 + rb));
+    __syncthreads();
+    for (int u = w; u < TALL_ND; u += TALL_NW) {
+      int i = 0;
+      while ((i + 1) * (i + 2) / 2 <= u) ++i;
+      const int j = u - i * (i + 1) / 2;
+      if (i >= nr) break;
+      T* dst = LB + lb_tile(b, r0 + rb + i, r0 + rb + j);
+      AT d;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) d[k] = dst[acc_index<T>(lane, k)];
+      for (int q = 0; q < pw; ++q) {
+        const T* X = stg + (i * TALL_W + q) * TE;
+        const T* Y = stg + (j * TALL_W + q) * TE;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) d = mfma(-X[64 * s + lane], Y[64 * s + lane], d);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) dst[acc_index<T>(lane, k)] = d[k];
+    }
+    __syncthreads();   // before the buffers are staged again
     first = false;
   }
   if (tid == 0 && blockIdx.x == 0 && cnt) atomicAdd(&info->pivots, cnt);
@@ -1632,10 +1644,11 @@ void launch_block_factor_tall(hipStream_t st, const BlockInfo* blk, const int* o
                               int max_mt, int max_rt, int max_kt, T* LB, T* LINV, double* PQ,
                               double* bthr, double* scratch, DevInfo* info, int num_cu) {
   if (n == 0) return;
+  hipLaunchKernelGGL(k_tall_thr<T>, dim3(n), dim3(256), 0, st, blk, order, LB, bthr);
   for (int c0 = 0;; c0 += TALL_W) {
     const int rows = max_rt - std::min(c0 + TALL_W, max_mt);
     const int g = c0 >= max_mt ? 1 : std::max(1, std::min((rows + TALL_NW - 1) / TALL_NW,
-                                                           std::max(1, 2 * num_cu / n)));
+                                                           std::max(1, 4 * num_cu / n)));
     hipLaunchKernelGGL(k_tall_panel<T>, dim3(g, n), dim3(64 * TALL_NW), 0, st, blk, order, LB, LINV,
                        bthr, reinterpret_cast<T*>(scratch), info, c0);
     if (c0 >= max_mt) break;
