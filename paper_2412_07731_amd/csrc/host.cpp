@@ -1173,9 +1173,12 @@ ahlp_status_t sparse_setup(ahlp_problem_t p, const std::vector<int>& rownz,
   if (max_cols > 2560 || max_rows > 2560) return AHLP_OK;
   const double dense = 8.0 * (double)(p->a_total + p->c_total);
   if (10.0 * 64.0 * (double)std::max(roff.back(), coff.back()) > SPARSE_SHARE * dense) return AHLP_OK;
-  size_t mem_free = 0, mem_all = 0;
-  HIPCHK(hipMemGetInfo(&mem_free, &mem_all));
-  if (8.0 * 640.0 * (double)(roff.back() + coff.back()) > (double)mem_free) return AHLP_OK;
+  const double need = 640.0 * (double)(roff.back() + coff.back());
+  if (need > 64e6) {   // (the query takes longer than a small problem's fill)
+    size_t mem_free = 0, mem_all = 0;
+    HIPCHK(hipMemGetInfo(&mem_free, &mem_all));
+    if (8.0 * need > (double)mem_free) return AHLP_OK;
+  }
   DevMem& M = p->mem;
   SpMat& s = p->sp;
   // one allocation, the parts at 256-byte steps
@@ -1192,11 +1195,14 @@ ahlp_status_t sparse_setup(ahlp_problem_t p, const std::vector<int>& rownz,
     g_err.clear();
     return AHLP_OK;
   }
-  HIPCHK(hipMemcpyAsync(base + o_ro, roff.data(), 8 * roff.size(), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(base + o_co, coff.data(), 8 * coff.size(), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(base + o_rt, ritems.data(), 16 * ritems.size(), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(base + o_ct, citems.data(), 16 * citems.size(), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(base + o_tl, ctiles.data(), 8 * ctiles.size(), hipMemcpyHostToDevice, st));
+  // the tables in one copy
+  std::vector<unsigned char> tab(bytes - o_ro);
+  std::memcpy(tab.data(), roff.data(), 8 * roff.size());
+  std::memcpy(tab.data() + o_co - o_ro, coff.data(), 8 * coff.size());
+  std::memcpy(tab.data() + o_rt - o_ro, ritems.data(), 16 * ritems.size());
+  std::memcpy(tab.data() + o_ct - o_ro, citems.data(), 16 * citems.size());
+  std::memcpy(tab.data() + o_tl - o_ro, ctiles.data(), 8 * ctiles.size());
+  HIPCHK(hipMemcpyAsync(base + o_ro, tab.data(), tab.size(), hipMemcpyHostToDevice, st));
   s.rval = reinterpret_cast<double*>(base + o_rv);
   s.cval = reinterpret_cast<double*>(base + o_cv);
   s.ridx = reinterpret_cast<unsigned short*>(base + o_ri);
