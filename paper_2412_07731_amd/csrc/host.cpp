@@ -188,6 +188,7 @@ struct SolveWs {
   double *br, *bw, *bup, *bpb, *bu0p;
   double *ex, *ey, *ez, *cx, *cy, *cz, *gc;
   double *red_part, *scal;
+  double* arrived;   // (int) arrivals of the reductions' workgroups, zero between launches
 };
 
 struct ahlp_problem_s {
@@ -281,7 +282,6 @@ struct ahlp_problem_s {
   // tile path of the Schur factorization (pairs <= 32 rows, border <= 64)
   bool fast = false;          // Schur factor by cyclic reduction (else the segmented chain)
   int tp = 0;                 // its tiles per pair side
-  int* red_arrived = nullptr;   // arrivals of a reduction's workgroups, zero between launches
   int t0 = 0, s00_chunk = 16, s00_parts = 0;
   double *BD = nullptr, *BC = nullptr, *BEt = nullptr, *FLi = nullptr, *FXL = nullptr,
          *FXR = nullptr, *FGt = nullptr, *FLbi = nullptr, *s00part = nullptr;
@@ -294,8 +294,9 @@ struct ahlp_problem_s {
   // workspace of a refined solve (allocated at create; ahlp_kkt_solve_noalloc
   // points it into the library's static device array for one call)
   SolveWs ws{};
-  double *wide_r = nullptr, *wide_w = nullptr, *wide_up = nullptr, *wide_pb = nullptr,
-         *wide_u0p = nullptr;   // pair vectors of the Schur solve for pairs of over 32 rows
+  // pair vectors of the Schur solve for pairs of over 32 rows: the handle's own
+  // workspace's, and those of ahlp_kkt_solve_noalloc, which may run beside it
+  double *ws_base = nullptr, *wide[2] = {nullptr, nullptr};
   double *aty = nullptr, *gdir = nullptr;
   double *ones = nullptr, *zerosn = nullptr;
   // predictor/corrector right-hand sides by linearity (padded v-space) and scaled vectors
@@ -399,14 +400,17 @@ size_t solve_ws_layout(const ahlp_problem_s* p, double* base, SolveWs* ws) {
   take(&w.ex, n); take(&w.ey, m); take(&w.ez, n);
   take(&w.cx, n); take(&w.cy, m); take(&w.cz, n); take(&w.gc, n);
   take(&w.red_part, (long long)MAXRED * RED_PARTIALS); take(&w.scal, NSCAL);
+  take(&w.arrived, MAXRED * RED_APART / 2);
   if (p->fast && p->tp <= 2) {
     const long long Pt = std::max(p->P, 1), T0 = std::max(p->t0, 1), tp = p->tp;
     take(&w.br, Pt * tp * 16); take(&w.bw, Pt * tp * 16); take(&w.bup, Pt * tp * 16);
     take(&w.bpb, Pt * T0 * 16); take(&w.bu0p, T0 * 16);
   } else if (p->fast) {
-    // pairs of over 32 rows: the handle's own pair vectors, so that the solve
-    // needs no more of the static workspace than with the segmented chain
-    w.br = p->wide_r; w.bw = p->wide_w; w.bup = p->wide_up; w.bpb = p->wide_pb; w.bu0p = p->wide_u0p;
+    // pairs of over 32 rows: outside, so that the solve needs no more of the
+    // static workspace than with the segmented chain
+    const long long pw = (long long)std::max(p->P, 1) * p->tp * 16, T0 = std::max(p->t0, 1);
+    w.br = p->wide[base == p->ws_base ? 0 : 1];
+    w.bw = w.br + pw; w.bup = w.bw + pw; w.bpb = w.bup + pw; w.bu0p = w.bpb + std::max(p->P, 1) * T0 * 16;
   }
   return off;
 }
@@ -902,7 +906,7 @@ void red(ahlp_problem_t p, int op, long long n, const double* a, const double* b
   m.nred = 1;
   m.r[0] = RedSpec{op, slot, n, a, b, c, d, s1, s2, nullptr, nullptr};
   m.partial = p->ws.red_part;
-  m.arrived = p->red_arrived;
+  m.arrived = reinterpret_cast<int*>(p->ws.arrived);
   m.out = p->ws.scal;
   launch_mreduce(st, m);
 }
@@ -913,7 +917,7 @@ struct Reds {
   Reds(ahlp_problem_t p) {
     m.nred = 0;
     m.partial = p->ws.red_part;
-    m.arrived = p->red_arrived;
+    m.arrived = reinterpret_cast<int*>(p->ws.arrived);
     m.out = p->ws.scal;
   }
   Reds& add(int op, long long n, const double* a, const double* b, int slot,
@@ -1784,8 +1788,6 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   CHK(M.alloc(&p->To, std::max(to, 1LL)));
   CHK(M.alloc(&p->E, std::max(p->nl * nbw, 1LL)));
   CHK(M.alloc(&p->S00, std::max(nbw * nbw, 1)));
-  CHK(M.alloc(&p->red_arrived, MAXRED * RED_APART));
-  launch_fill(st, MAXRED * RED_APART / 2, 0.0, reinterpret_cast<double*>(p->red_arrived));
   CHK(M.alloc(&p->thrT, std::max(P, 1)));
   CHK(M.alloc(&p->CL, std::max(td, 1LL)));
   CHK(M.alloc(&p->CLi, std::max(td, 1LL)));
@@ -1819,11 +1821,8 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
     CHK(M.alloc(&p->FLbi, (long long)std::max(p->t0 * p->t0, 1) * 256));
     set_bcr_smem_limits();
     CHK(M.alloc(&p->segout, 1));
-    if (p->tp > 2) {
-      for (double** v : {&p->wide_r, &p->wide_w, &p->wide_up}) CHK(M.alloc(v, Pt * tp * 16));
-      CHK(M.alloc(&p->wide_pb, Pt * T0 * 16));
-      CHK(M.alloc(&p->wide_u0p, T0 * 16));
-    }
+    if (p->tp > 2)
+      for (double*& v : p->wide) CHK(M.alloc(&v, 3 * Pt * tp * 16 + Pt * T0 * 16 + T0 * 16));
   } else {
     CHK(M.alloc(&p->segout, (long long)std::max(p->G, 1) * SEG_STRIDE));
   }
@@ -1831,7 +1830,9 @@ ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* d, hipStream_t st,
   {
     double* wsbuf = nullptr;
     CHK(M.alloc(&wsbuf, (long long)(solve_ws_layout(p, nullptr, nullptr) / sizeof(double))));
+    p->ws_base = wsbuf;
     solve_ws_layout(p, wsbuf, &p->ws);
+    launch_fill(st, MAXRED * RED_APART / 2, 0.0, p->ws.arrived);
   }
   p->info = reinterpret_cast<DevInfo*>(p->ws.scal + NSCAL - 1);
   for (double** v : {&p->ones, &p->zerosn, &p->rd, &p->rzv, &p->dxa, &p->dza, &p->dx, &p->dz})

@@ -46,3 +46,26 @@ def test_wide_pairs(dev, shape):  # noqa: F811
     for a, b in zip(d1, d2):
         assert np.array_equal(H(a), H(b))
     P.close()
+
+
+def test_two_workspaces_side_by_side(dev):  # noqa: F811
+    """A solve in the handle's workspace and one in the static workspace, on two
+    streams at a time, leave what they leave one after the other."""
+    from paper_2412_07731_amd.ahlp import Problem
+    inst = gen.generate(dict(SHAPES[5], density=0.3), 5)
+    print("case", SHAPES[5], flush=True)
+    x, z, r = point(inst)
+    P = Problem(inst)
+    P.factor(T(x, dev), T(z, dev), 1e-6, 1e-4)
+    ra, rb = [T(v, dev) for v in r], [T(-2.0 * v, dev) for v in r]
+    wa = [H(v) for v in P.solve(*ra)[:3]]
+    wb = [H(v) for v in P.solve_noalloc(*rb)[:3]]
+    torch.cuda.synchronize()
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(10):
+        da = P.solve(*ra, stream=sa)[:3]
+        db = P.solve_noalloc(*rb, stream=sb)[:3]
+        torch.cuda.synchronize()
+        for got, want in zip((*da, *db), wa + wb):
+            assert np.array_equal(H(got), want)
+    P.close()
