@@ -321,9 +321,8 @@ struct ahlp_problem_s {
   double *rp = nullptr, *rd = nullptr, *rzv = nullptr, *dxa = nullptr, *dya = nullptr,
          *dza = nullptr, *dx = nullptr, *dy = nullptr, *dz = nullptr;
   double* h_scal = nullptr;   // pinned host mirror of ws.scal
-  // side stream (default priority) for the link-column gather, which runs
-  // beside the block SYRK: event fork from the caller's stream, join before
-  // the block factor
+  // side stream (default priority) for the eight-wave and tall factor buckets, which
+  // run beside the four-wave one: event fork from the caller's stream and join
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // graph mode of ahlp_ipm_solve: the solve runs on gstream (capturable; event
@@ -586,18 +585,15 @@ template <typename T>
 ahlp_status_t factor_blocks(ahlp_problem_t p, hipStream_t st, T* LB, T* LINV, const T* A) {
   if (p->launch_mode == AHLP_LAUNCH_PER_BLOCK) return factor_blocks_per_block<T>(p, st, LB, LINV, A);
   if (p->launch_mode == AHLP_LAUNCH_FUSED) return factor_blocks_fused<T>(p, st, LB, LINV, A);
-  // the link gather (HBM-bound) runs on the side stream while the SYRK
-  // (MFMA-bound) runs on st; they write disjoint tiles of LB
-  HIPCHK(hipEventRecord(p->ev_fork, st));
-  HIPCHK(hipStreamWaitEvent(p->side, p->ev_fork, 0));
-  launch_link<T>(p->side, p->blk, p->link_items, p->nlink, p->nb, p->A, p->C, p->lptr, p->lcol,
-                 p->lval, p->Dp, LB, p->PQ);
-  HIPCHK(hipEventRecord(p->ev_join, p->side));
   p->timer.begin(AHLP_ST_SYRK);
   run_syrk<T>(p, st, A, LB);
   p->timer.end();
   p->timer.begin(AHLP_ST_FACTOR);
-  HIPCHK(hipStreamWaitEvent(st, p->ev_join, 0));
+  // after the SYRK and not beside it on the side stream: the fork and the join
+  // cost more than the gather takes (8 blocks of 32 rows, a step 138 us beside,
+  // 100 in turn; 512 of 256 894 and 850; 96 pairs of 33-56 rows 737 and 675)
+  launch_link<T>(st, p->blk, p->link_items, p->nlink, p->nb, p->A, p->C, p->lptr, p->lcol, p->lval,
+                 p->Dp, LB, p->PQ);
   const int nb8 = p->n_panel8, nbc = p->n_col;
   const int* o8 = p->bf_order + p->n_panel;
   const int* oc = o8 + nb8;
