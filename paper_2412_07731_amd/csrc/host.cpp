@@ -585,15 +585,28 @@ template <typename T>
 ahlp_status_t factor_blocks(ahlp_problem_t p, hipStream_t st, T* LB, T* LINV, const T* A) {
   if (p->launch_mode == AHLP_LAUNCH_PER_BLOCK) return factor_blocks_per_block<T>(p, st, LB, LINV, A);
   if (p->launch_mode == AHLP_LAUNCH_FUSED) return factor_blocks_fused<T>(p, st, LB, LINV, A);
+  // The link columns after the SYRK: beside it on the side stream the fork and
+  // the join cost more than the gather takes (8 blocks of 32 rows, a step 138 us
+  // beside, 100 in turn; 512 of 256 894 and 850; 96 pairs of 33-56 rows 737 and
+  // 675).  In the SYRK's own launch where all its workgroups are dense ones and
+  // in flight at once (four a CU): 100 -> 95 us; above that the gather's
+  // accesses slow the SYRK by more than it takes alone (512 of 256 852 -> 926).
+  const auto& plan = p->syrk_plan[sizeof(T) == 4];
   p->timer.begin(AHLP_ST_SYRK);
-  run_syrk<T>(p, st, A, LB);
+  const bool along = plan.nsp == 0 && plan.nd > 0 && plan.nd + p->nlink <= 4 * p->num_cu;
+  if (along) {
+    LinkCols lc;
+    lc.items = p->link_items; lc.n = p->nlink; lc.nb = p->nb;
+    lc.A = p->A; lc.C = p->C; lc.lptr = p->lptr; lc.lcol = p->lcol; lc.lval = p->lval; lc.PQ = p->PQ;
+    launch_syrk<T>(st, p->blk, plan.dense, plan.nd, A, p->Dp, LB, p->delta, lc);
+  } else {
+    run_syrk<T>(p, st, A, LB);
+  }
   p->timer.end();
   p->timer.begin(AHLP_ST_FACTOR);
-  // after the SYRK and not beside it on the side stream: the fork and the join
-  // cost more than the gather takes (8 blocks of 32 rows, a step 138 us beside,
-  // 100 in turn; 512 of 256 894 and 850; 96 pairs of 33-56 rows 737 and 675)
-  launch_link<T>(st, p->blk, p->link_items, p->nlink, p->nb, p->A, p->C, p->lptr, p->lcol, p->lval,
-                 p->Dp, LB, p->PQ);
+  if (!along)
+    launch_link<T>(st, p->blk, p->link_items, p->nlink, p->nb, p->A, p->C, p->lptr, p->lcol, p->lval,
+                   p->Dp, LB, p->PQ);
   const int nb8 = p->n_panel8, nbc = p->n_col;
   const int* o8 = p->bf_order + p->n_panel;
   const int* oc = o8 + nb8;

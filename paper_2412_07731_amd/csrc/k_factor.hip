@@ -15,6 +15,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "link_tiles.h"
 #include "tile_chol.h"
 
 namespace ahlp {
@@ -84,14 +85,15 @@ __global__ __launch_bounds__(256) void k_syrk(const BlockInfo* __restrict__ blk,
                                               const int4* __restrict__ items, int nitems,
                                               const T* __restrict__ A,
                                               const double* __restrict__ Dp,
-                                              T* __restrict__ LB, double delta) {
+                                              T* __restrict__ LB, double delta, const LinkCols lc) {
   typedef typename Bits<T>::type B;
   constexpr int E = 16 / sizeof(T);             // elements per 16-byte load
   constexpr int NJ = 8 * TE / (E * 256);        // loads per thread and stage
   typedef T V __attribute__((ext_vector_type(E)));
-  int w = blockIdx.x;
-  int per = gridDim.x / 8;
-  int g = (w % 8) * per + (w / 8);
+  const int w = link_split(blockIdx.x, lc);
+  if (w < 0) return link_cols<T>(blk, lc, ~w, threadIdx.x, Dp, LB);
+  const int per = (nitems + 7) / 8;
+  const int g = (w % 8) * per + (w / 8);
   if (g >= nitems) return;
   const int4 it = items[g];
   const BlockInfo b = blk[it.x];
@@ -204,91 +206,7 @@ __global__ __launch_bounds__(256) void k_syrk(const BlockInfo* __restrict__ blk,
   }
 }
 
-// ---------------------------------------------------------------- a1: B_i'
-// One workgroup per (block, tile row of the link columns).  Writes B_i' =
-// [F_i D_i A_i' ; C_i'] into the bordered rows and F_i D_i F_i' (FP64) into the
-// Schur-contribution tiles, F_i being block i's part of its two link pairs
-// and of the global rows.  These rows are sparse (compressed rows, sorted
-// columns), so the products are gathers rather than GEMMs.
-// Tile row rr of block b's link columns, by 256 threads (t = 0..255).
-template <typename T>
-__device__ __forceinline__ void link_tile_row(const BlockInfo& b, int rr, int t, int nb,
-                                              const double* __restrict__ A,
-                                              const double* __restrict__ C,
-                                              const int* __restrict__ lptr,
-                                              const int* __restrict__ lcol,
-                                              const double* __restrict__ lval,
-                                              const double* __restrict__ Dp,
-                                              T* __restrict__ LB, double* __restrict__ PQ) {
-  const int r = b.mt + rr;
-  const int ql = t & 15, al = t >> 4;
-  const int q = TS * rr + ql;
-  int qi;
-  bool real;
-  const int sec = link_section(b, q, &qi, nb, &real);
-  const bool is_row = link_is_row(b, sec, qi);
-  int p0 = 0, p1 = 0;
-  if (real && is_row) {
-    p0 = lptr[b.csr_off + q];
-    p1 = lptr[b.csr_off + q + 1];
-  }
-  // LINK_CB column tiles at a time, their gathers independent so that they
-  // are all in flight together; the sparse row is walked once per chunk
-  constexpr int LINK_CB = 8;
-  for (int c0 = 0; c0 < b.mt; c0 += LINK_CB) {
-    double v[LINK_CB];
-#pragma unroll
-    for (int u = 0; u < LINK_CB; ++u) v[u] = 0.0;
-    if (real && is_row) {
-      for (int e = p0; e < p1; ++e) {
-        const int j = lcol[e];
-        const double coef = lval[e] * Dp[b.dpoff + j];
-        const double* col = A + a_tile(b, 0, j >> 4) + (j & 15) * TS + al;
-#pragma unroll
-        for (int u = 0; u < LINK_CB; ++u) {
-          const int c = c0 + u;
-          if (c < b.mt && TS * c + al < b.m) v[u] += coef * col[(long long)c * b.nt * TE];
-        }
-      }
-    } else if (real) {
-      const int qc = qi - b.ng;   // column of C_i
-      const double* col = C + c_tile(b, 0, qc >> 4) + (qc & 15) * TS + al;
-#pragma unroll
-      for (int u = 0; u < LINK_CB; ++u) {
-        const int c = c0 + u;
-        if (c < b.mt && TS * c + al < b.m) v[u] = col[(long long)c * b.kc0 * TE];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < LINK_CB; ++u)
-      if (c0 + u < b.mt) LB[lb_tile(b, r, c0 + u) + t] = (T)v[u];
-  }
-  // F D F' for tiles (rr, cc), cc <= rr
-  for (int cc = 0; cc <= rr; ++cc) {
-    const int q2 = TS * cc + al;
-    int qi2;
-    bool real2;
-    const int sec2 = link_section(b, q2, &qi2, nb, &real2);
-    double v = 0.0;
-    if (real && real2 && is_row && link_is_row(b, sec2, qi2)) {
-      int e1 = p0, e2 = lptr[b.csr_off + q2];
-      const int e2end = lptr[b.csr_off + q2 + 1];
-      while (e1 < p1 && e2 < e2end) {
-        const int j1 = lcol[e1], j2 = lcol[e2];
-        if (j1 == j2) {
-          v += lval[e1] * Dp[b.dpoff + j1] * lval[e2];
-          ++e1; ++e2;
-        } else if (j1 < j2) {
-          ++e1;
-        } else {
-          ++e2;
-        }
-      }
-    }
-    PQ[pq_tile(b, rr, cc) + t] = v;
-  }
-}
-
+// ---------------------------------------------------------------- a1: B_i' alone (link_tiles.h)
 template <typename T>
 __global__ __launch_bounds__(256) void k_link(const BlockInfo* __restrict__ blk,
                                               const int2* __restrict__ items, int nb,
@@ -1550,15 +1468,14 @@ void launch_prep(hipStream_t st, const BlockInfo* blk, int N, int n0, long long 
 
 template <typename T>
 void launch_syrk(hipStream_t st, const BlockInfo* blk, const int4* items, int nitems,
-                 const T* A, const double* Dp, T* LB, double delta) {
-  const int grid = 8 * ((nitems + 7) / 8);
-  hipLaunchKernelGGL(k_syrk<T>, dim3(grid), dim3(256), 0, st, blk, items, nitems, A, Dp, LB,
-                     delta);
+                 const T* A, const double* Dp, T* LB, double delta, LinkCols lc) {
+  hipLaunchKernelGGL(k_syrk<T>, dim3(link_grid(nitems, lc)), dim3(256), 0, st, blk, items, nitems,
+                     A, Dp, LB, delta, lc);
 }
 template void launch_syrk<double>(hipStream_t, const BlockInfo*, const int4*, int, const double*,
-                                  const double*, double*, double);
+                                  const double*, double*, double, LinkCols);
 template void launch_syrk<float>(hipStream_t, const BlockInfo*, const int4*, int, const float*,
-                                 const double*, float*, double);
+                                 const double*, float*, double, LinkCols);
 
 template <typename T>
 void launch_link(hipStream_t st, const BlockInfo* blk, const int2* items, int nitems, int nb,

@@ -12,9 +12,19 @@ namespace ahlp {
 void launch_prep(hipStream_t st, const BlockInfo* blk, int N, int n0, long long x0off,
                  long long d0off, const double* x, const double* z, const double* q, double rho,
                  double* Dp, double* xs, double* zs, DevInfo* info);
+// link columns that go along in a dense SYRK launch (none: n = 0)
+struct LinkCols {
+  const int2* items = nullptr;   // block, tile row of its link columns
+  int n = 0, nb = 0;
+  const double *A = nullptr, *C = nullptr;
+  const int *lptr = nullptr, *lcol = nullptr;
+  const double* lval = nullptr;
+  double* PQ = nullptr;
+  int units = 0, every = 1;      // set by link_grid
+};
 template <typename T>
 void launch_syrk(hipStream_t st, const BlockInfo* blk, const int4* items, int nitems,
-                 const T* A, const double* Dp, T* LB, double delta);
+                 const T* A, const double* Dp, T* LB, double delta, LinkCols lc = LinkCols{});
 // The same for blocks with few nonzeros (k_syrk_sp.hip), bitwise equal.  The
 // nonzeros of tile row t (of all blocks' in order) in stage st of SS_K columns
 // are the batches off[first[t] + st] .. off[first[t] + st + 1] of four entries,
