@@ -18,7 +18,8 @@
 // from the lane of each row of 16 that loaded it, as operands of the
 // multiply-add and of the address sum, so that the vector unit stays below the
 // LDS time.  512 blocks of 256 x 512 at 3.2% nonzeros: 252 us against the dense
-// kernel's 377 us in FP64, 181 against 209 us in FP32.  (Broadcast by scalar
+// kernel's 377 us in FP64, 181 against 209 us in FP32, all with the link columns'
+// gather beside them; 200 and 146 us since it has its turn.  (Broadcast by scalar
 // loads waits on their latency, since those share their counter with the LDS
 // reads: 333 us; one column a lane and a stage of 128: 273 us.)
 #include "common.h"
