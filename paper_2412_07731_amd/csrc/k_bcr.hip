@@ -45,6 +45,7 @@
 // of memory and the first fetch of its instructions.
 //
 // Every sum is taken in a fixed order.  The solve is in k_bcrs.hip.
+#include "bcr_plan.h"
 #include "common.h"
 #include "kernels.h"
 #include "tile_chol.h"
@@ -148,16 +149,9 @@ __global__ __launch_bounds__(64 * FW) void k_bcr_group(BcrArgs c, int lvl, int n
       const long long j = (long long)k << lvl;
       if (lvl == 0) {
         const long long off = (kind == 0 ? c.tdoff : kind == 1 ? c.tooff : c.eoff)[j];
-        const int lj = c.l[j];
-        src = (kind == 0 ? c.Td : kind == 1 ? c.To : c.E) + off;
-        my_cols = my_sb = my_rows = lj;
-        if (kind == 1) my_sb = my_rows = c.l[j + 1];
-        if (kind > 1) {
-          src += 16 * (kind - 2) * lj;
-          my_rows = c.n0 - 16 * (kind - 2);
-          my_sa = lj;
-          my_sb = 1;
-        }
+        const PairTile p = pair_tile(kind, c.l[j], kind == 1 ? c.l[j + 1] : 0, c.n0, off);
+        src = (kind == 0 ? c.Td : kind == 1 ? c.To : c.E) + p.off;
+        my_sa = p.sa; my_sb = p.sb; my_rows = p.rows; my_cols = p.cols;
       } else {
         src = kind == 0 ? c.BD + j * 256 : kind == 1 ? c.BC + j * 256 : c.BEt + (j * t0 + kind - 2) * 256;
         if (k > 0 && kind != 1)
@@ -182,8 +176,7 @@ __global__ __launch_bounds__(64 * FW) void k_bcr_group(BcrArgs c, int lvl, int n
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int b = 4 * s + b15;
-      const int at = a15 < rows && b < cols ? a15 * sa + b * sb : 0;
-      v[u][s] = src[at];
+      v[u][s] = src[tile_at(sa, sb, rows, cols, a15, b)];
     }
     const double* more = lane_ptr(my_more, u);
     if (more)
