@@ -14,6 +14,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "grid_rows.h"
 #include "kernels.h"
 #include "link_tiles.h"
 #include "tile_chol.h"
@@ -1562,17 +1563,21 @@ void launch_block_factor_tall(hipStream_t st, const BlockInfo* blk, const int* o
                               double* bthr, double* scratch, DevInfo* info, int num_cu) {
   if (n == 0) return;
   hipLaunchKernelGGL(k_tall_thr<T>, dim3(n), dim3(256), 0, st, blk, order, LB, bthr);
-  for (int c0 = 0;; c0 += TALL_W) {
-    const int rows = max_rt - std::min(c0 + TALL_W, max_mt);
-    const int g = c0 >= max_mt ? 1 : std::max(1, std::min((rows + TALL_NW - 1) / TALL_NW,
-                                                           std::max(1, 4 * num_cu / n)));
-    hipLaunchKernelGGL(k_tall_panel<T>, dim3(g, n), dim3(64 * TALL_NW), 0, st, blk, order, LB, LINV,
-                       bthr, reinterpret_cast<T*>(scratch), info, c0);
-    if (c0 >= max_mt) break;
-  }
-  if (max_kt > 0)
-    hipLaunchKernelGGL(k_schur_contrib<T>, dim3((max_kt * (max_kt + 1) / 2 + 3) / 4, n), dim3(256), 0,
-                       st, blk, order, LB, PQ);
+  // (autotuning takes blocks of any height here, by the ten thousand if they are small)
+  grid_rows(n, [&](int first, int count) {
+    const int* part = order + first;
+    for (int c0 = 0;; c0 += TALL_W) {
+      const int rows = max_rt - std::min(c0 + TALL_W, max_mt);
+      const int g = c0 >= max_mt ? 1 : std::max(1, std::min((rows + TALL_NW - 1) / TALL_NW,
+                                                             std::max(1, 4 * num_cu / count)));
+      hipLaunchKernelGGL(k_tall_panel<T>, dim3(g, count), dim3(64 * TALL_NW), 0, st, blk, part, LB, LINV,
+                         bthr, reinterpret_cast<T*>(scratch), info, c0);
+      if (c0 >= max_mt) break;
+    }
+    if (max_kt > 0)
+      hipLaunchKernelGGL(k_schur_contrib<T>, dim3((max_kt * (max_kt + 1) / 2 + 3) / 4, count), dim3(256), 0,
+                         st, blk, part, LB, PQ);
+  });
 }
 size_t tall_scratch_doubles(int n) { return (size_t)n * 2 * TALL_ND * TE; }
 bool block_factor_panel_fits(int rt) { return rt <= 4 * BF_RMAX_MAX; }
