@@ -41,60 +41,62 @@ template <typename T> struct Pair;
 template <> struct Pair<double> { typedef double type __attribute__((ext_vector_type(2))); };
 template <> struct Pair<float> { typedef float type __attribute__((ext_vector_type(2))); };
 
-// acc + (lane J of the 16-lane row's a) * x.  The FP64 form is written out: the
-// compiler broadcasts into a register first.  The leading wait states cover a
-// just written a (a DPP operand needs two).
+// A DPP operand must not have been written by the vector unit in the two wait states
+// before, and the compiler does not look into asm for that: every asm that reads one
+// starts with these waits, so that it stands wherever it is scheduled.  (With the waits
+// on the first of a chunk alone, each instruction an asm of its own, the kernel took 5%
+// less: 200 us where it is 209; with a chunk's four entries in one asm 212 us, since its
+// products then wait for all four reads.)
+
+// acc + (lane J, then J + 1 of the 16-lane row's a) * x for both columns.  The FP64 form
+// is written out: the compiler broadcasts into a register first.
 template <int J>
-__device__ __forceinline__ void fmac_bcast(double a, double x, double& acc) {
+__device__ __forceinline__ void fmac_bcast(double a, const Pair<double>::type* x, double& c0, double& c1) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  if constexpr (J == 0)
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(x));
-  else
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(x), "n"(J));
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
+      : "+&v"(c0), "+&v"(c1)
+      : "v"(a), "v"(x[0].x), "v"(x[0].y), "v"(x[1].x), "v"(x[1].y), "n"(J), "n"(J + 1));
 #endif
 }
 template <int J>
-__device__ __forceinline__ void fmac_bcast(float a, float x, float& acc) {
-  acc = fmaf(row_bcast<J>(a), x, acc);
+__device__ __forceinline__ void fmac_bcast(float a, const Pair<float>::type* x, float& c0, float& c1) {
+  const float a0 = row_bcast<J>(a), a1 = row_bcast<J + 1>(a);
+  c0 = fmaf(a1, x[1].x, fmaf(a0, x[0].x, c0));
+  c1 = fmaf(a1, x[1].y, fmaf(a0, x[0].y, c1));
 }
 
-// Entries J .. N - 1 of a chunk into both columns, in order: the LDS reads go
-// out before the first product.  xb: LDS address of this lane's place in row 0
-// of X, o: each lane's entry's byte offset of its row, added lane to lane.
+// xb plus lanes J .. J + 3 of the row's o
 template <int J>
-__device__ __forceinline__ unsigned add_bcast(unsigned o, unsigned xb) {
-  unsigned r = 0;
+__device__ __forceinline__ void add_bcast(unsigned o, unsigned xb, unsigned (&r)[4]) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  if constexpr ((J & 3) == 0)
-    asm("s_nop 1\n\tv_add_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(o), "v"(xb), "n"(J));
-  else
-    asm("v_add_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(o), "v"(xb), "n"(J));
+  asm("s_nop 1\n\t"
+      "v_add_u32_dpp %0, %4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_u32_dpp %1, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_u32_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_u32_dpp %3, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+      : "v"(o), "v"(xb), "n"(J), "n"(J + 1), "n"(J + 2), "n"(J + 3));
 #endif
-  return r;
 }
 template <typename T>
 using LdsPair = const __attribute__((address_space(3))) typename Pair<T>::type*;
-template <int J, int N, typename T>
-__device__ __forceinline__ void sp_read(unsigned o, unsigned xb, typename Pair<T>::type* x) {
-  if constexpr (J < N) {
-    x[0] = *(LdsPair<T>)add_bcast<J>(o, xb);
-    sp_read<J + 1, N, T>(o, xb, x + 1);
-  }
-}
-template <int J, int N, typename T>
-__device__ __forceinline__ void sp_fma(T a, const typename Pair<T>::type* x, T& c0, T& c1) {
-  if constexpr (J < N) {
-    fmac_bcast<J>(a, x[0].x, c0);
-    fmac_bcast<J>(a, x[0].y, c1);
-    sp_fma<J + 1, N, T>(a, x + 1, c0, c1);
-  }
-}
-template <int J, int N, typename T>
+// Entries J .. J + 3 of a chunk into both columns, in order: the LDS reads go
+// out before the first product.  xb: LDS address of this lane's place in row 0
+// of X, o: each lane's entry's byte offset of its row, added lane to lane.
+template <int J, typename T>
 __device__ __forceinline__ void sp_chunk(T a, unsigned o, unsigned xb, T& c0, T& c1) {
-  typename Pair<T>::type x[N - J];
-  sp_read<J, N, T>(o, xb, x);
+  unsigned at[4];
+  typename Pair<T>::type x[4];
+  add_bcast<J>(o, xb, at);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) x[u] = *(LdsPair<T>)at[u];
   __builtin_amdgcn_sched_barrier(0);   // all reads before the first product
-  sp_fma<J, N, T>(a, x, c0, c1);
+  fmac_bcast<J>(a, x, c0, c1);
+  fmac_bcast<J + 2>(a, x + 2, c0, c1);
 }
 
 template <typename T>
@@ -210,12 +212,12 @@ __global__ __launch_bounds__(64 * SS_W, 4) void k_syrk_sp(const BlockInfo* __res
         const T a = ra[j % SS_AHEAD];
         const unsigned o = (ro[j % SS_AHEAD] & ~15u) * (unsigned)sizeof(T);
         if (j + SS_AHEAD < 16) load_row(j + SS_AHEAD);
-        if (c > 0) sp_chunk<0, 4>(a, o, xb, acc[j][0], acc[j][1]);
-        if (c > 1) sp_chunk<4, 8>(a, o, xb, acc[j][0], acc[j][1]);
-        if (c > 2) sp_chunk<8, 12>(a, o, xb, acc[j][0], acc[j][1]);
-        if (c > 3) sp_chunk<12, 16>(a, o, xb, acc[j][0], acc[j][1]);
+        if (c > 0) sp_chunk<0>(a, o, xb, acc[j][0], acc[j][1]);
+        if (c > 1) sp_chunk<4>(a, o, xb, acc[j][0], acc[j][1]);
+        if (c > 2) sp_chunk<8>(a, o, xb, acc[j][0], acc[j][1]);
+        if (c > 3) sp_chunk<12>(a, o, xb, acc[j][0], acc[j][1]);
         for (int d = 4; d < c; ++d)
-          sp_chunk<0, 4>(vs[4 * d + l16], (xs[4 * d + l16] & ~15u) * (unsigned)sizeof(T), xb, acc[j][0],
+          sp_chunk<0>(vs[4 * d + l16], (xs[4 * d + l16] & ~15u) * (unsigned)sizeof(T), xb, acc[j][0],
                          acc[j][1]);
         vs += 4 * c;
         xs += 4 * c;
