@@ -3,11 +3,7 @@
 // be checked on the host.
 #pragma once
 
-#if defined(__HIPCC__)
-#define AHLP_HD __host__ __device__ inline
-#else
-#define AHLP_HD inline
-#endif
+#include "hd.h"
 
 namespace ahlp {
 

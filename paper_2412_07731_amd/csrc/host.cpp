@@ -400,6 +400,7 @@ size_t solve_ws_layout(const ahlp_problem_s* p, double* base, SolveWs* ws) {
   take(&w.cx, n); take(&w.cy, m); take(&w.cz, n); take(&w.gc, n);
   take(&w.red_part, (long long)MAXRED * RED_PARTIALS); take(&w.scal, NSCAL);
   take(&w.arrived, MAXRED * RED_APART / 2);
+  static_assert(RED_PARTIALS + RED_APART / 2 <= 256, "both fit where 256 partials did: the static workspace's limit");
   if (p->fast && p->tp <= 2) {
     const long long Pt = std::max(p->P, 1), T0 = std::max(p->t0, 1), tp = p->tp;
     take(&w.br, Pt * tp * 16); take(&w.bw, Pt * tp * 16); take(&w.bup, Pt * tp * 16);

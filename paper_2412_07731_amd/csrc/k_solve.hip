@@ -8,6 +8,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "link_rows.h"
+#include "red_split.h"
 #include "tile_chol.h"
 
 #include <algorithm>
@@ -824,7 +825,6 @@ __global__ void k_addscalar(long long n, double v, double* __restrict__ dst) {
 // ops: 0 sum a*b, 1 max |a|, 2 min over b<0 of -a/b (inf if none),
 //      3 sum (a + s1 b)(c + s2 d)  [mu_aff], 4 max (a + b), 5 min a,
 //      6 min over b<0 of -a/b and over d<0 of -c/d
-constexpr int RED_THREADS = 256;
 
 __device__ inline double red_combine(int op, double x, double y) {
   return (op == 0 || op == 3) ? x + y : ((op == 2 || op == 5 || op == 6) ? fmin(x, y) : fmax(x, y));
@@ -892,17 +892,9 @@ __device__ double red_chunk(const R& r, long long lo, long long hi, double s1, d
 }
 
 // Several independent reductions in one launch: blockIdx.y selects the reduction,
-// whose workgroups are the first red_wgs(n) of that row.  With more than one, the
-// last to arrive combines the partials, in a fixed tree; results do not depend on
-// how many reductions share a launch.  Four elements a thread (ratios are divisions),
-// but few enough workgroups that their arrivals do not queue: 70 sets of up to nine
-// reductions of 520 elements 9.5 -> 4.8 us each against two launches of 256
-// workgroups, of 262144 elements 10.8 -> 8.8 us (20.8 us with 256 workgroups, 12.9
-// with 16384 elements each).
-__host__ __device__ inline int red_wgs(long long n) {
-  const long long w = (n + 4 * RED_THREADS - 1) / (4 * RED_THREADS);
-  return w < 1 ? 1 : w > RED_PARTIALS ? RED_PARTIALS : (int)w;
-}
+// whose workgroups are the first red_wgs(n) of that row (red_split.h).  With more than
+// one, the last to arrive combines the partials, in a fixed tree; results do not depend
+// on how many reductions share a launch.
 __global__ __launch_bounds__(RED_THREADS) void k_mreduce(const MultiRed m) {
   const RedSpec& r = m.r[blockIdx.y];
   const int wgs = red_wgs(r.n);

@@ -4,6 +4,7 @@
 #include <initializer_list>
 
 #include "common.h"
+#include "red_split.h"
 
 namespace ahlp {
 
@@ -405,7 +406,6 @@ void launch_mreduce(hipStream_t st, const MultiRed& m);
 // RED_RATIO2: the ratio test over two pairs, min over i of -a/b (b < 0) and -c/d (d < 0)
 enum RedOp { RED_DOT = 0, RED_MAXABS = 1, RED_RATIO = 2, RED_MUAFF = 3, RED_MAXSUM = 4, RED_MIN = 5,
              RED_RATIO2 = 6 };
-constexpr int RED_PARTIALS = 64;
 
 // ---- static workspace (noalloc.hip)
 // Size of the per-device static array that ahlp_kkt_solve_noalloc works in.
