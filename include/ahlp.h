@@ -419,6 +419,13 @@ ahlp_status_t ahlp_debug_block(ahlp_problem_t p, int32_t i, double* L, double* W
  * (sum l + n0)^2 row-major array (small problems only), before factorization. */
 ahlp_status_t ahlp_debug_schur(ahlp_problem_t p, double* S);
 
+/* Which forms create chose for this problem's blocks: *compressed, 1 if the row
+ * and column passes read a compressed copy of them (0: the dense tiles);
+ * *lists64 and *lists32, the number of blocks whose SYRK walks nonzero lists in
+ * FP64 and in FP32 (the others multiply their dense tiles).  Any pointer may be
+ * NULL.  Does not synchronize. */
+ahlp_status_t ahlp_debug_plan(ahlp_problem_t p, int32_t* compressed, int32_t* lists64, int32_t* lists32);
+
 /* Pivots replaced by the pivot rule in the last factorization (synchronizes). */
 ahlp_status_t ahlp_debug_pivots(ahlp_problem_t p, int32_t* count);
 

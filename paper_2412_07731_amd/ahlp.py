@@ -95,6 +95,8 @@ SIGNATURES = {
                             C.POINTER(C.c_int64), C.POINTER(C.c_int32)], C.c_int),
     "ahlp_debug_block": ([C.c_void_p, C.c_int32, _f64p, _f64p], C.c_int),
     "ahlp_debug_schur": ([C.c_void_p, _f64p], C.c_int),
+    "ahlp_debug_plan": ([C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)],
+                        C.c_int),
     "ahlp_debug_pivots": ([C.c_void_p, C.POINTER(C.c_int32)], C.c_int),
     "ahlp_ceiling_mfma": ([C.c_int32, C.POINTER(C.c_double), C.c_void_p], C.c_int),
     "ahlp_ceiling_hbm_read": ([C.c_void_p, C.c_int64, C.POINTER(C.c_double), C.c_void_p], C.c_int),
@@ -367,6 +369,12 @@ class Problem:
         S = np.zeros((max(dim, 1), max(dim, 1)))
         _check(lib().ahlp_debug_schur(self.h, S.ctypes.data_as(_f64p)))
         return S[:dim, :dim]
+
+    def debug_plan(self):
+        """(compressed passes, blocks on nonzero lists in FP64, in FP32) (ahlp_debug_plan)."""
+        c, a, b = C.c_int32(), C.c_int32(), C.c_int32()
+        _check(lib().ahlp_debug_plan(self.h, C.byref(c), C.byref(a), C.byref(b)))
+        return bool(c.value), a.value, b.value
 
     def pivots(self):
         c = C.c_int32()

@@ -2846,6 +2846,19 @@ ahlp_status_t ahlp_ceiling_tile_chol(int32_t beside_mfma, double* us_per_tile,
   return AHLP_OK;
 }
 
+ahlp_status_t ahlp_debug_plan(ahlp_problem_t p, int32_t* compressed, int32_t* lists64, int32_t* lists32) {
+  g_err.clear();
+  if (!p) return fail(AHLP_EINVAL, "null handle");
+  int32_t* out[2] = {lists64, lists32};
+  if (compressed) *compressed = p->sparse ? 1 : 0;
+  for (int q = 0; q < 2; ++q)
+    if (out[q]) {
+      const auto& v = p->syrk_plan[q].sparse;
+      *out[q] = (int32_t)std::count(v.begin(), v.end(), 1);
+    }
+  return AHLP_OK;
+}
+
 ahlp_status_t ahlp_debug_pivots(ahlp_problem_t p, int32_t* count) {
   if (!p || !count) return fail(AHLP_EINVAL, "null argument");
   CHK(check_info(p, p->timer.st, nullptr));
