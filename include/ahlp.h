@@ -193,7 +193,12 @@ typedef struct {
 void ahlp_ipm_default_opts(ahlp_ipm_opts_t* opts);
 
 /* Packs the problem into library-owned device memory (tile-major blocks; link
- * rows as compressed sparse rows and columns).  The caller may free desc's
+ * rows as compressed sparse rows and columns).  Blocks with few nonzeros are
+ * kept in two further forms where those are the faster ones (a compressed copy
+ * for the row and column passes, nonzero lists for the SYRK): each takes at most
+ * an eighth of the device memory that is free at create beyond what the handle
+ * may allocate later (FP32 factors at first use, tuning), or 64 MB, and is left
+ * out otherwise.  The caller may free desc's
  * arrays on return.  Synchronizes `stream`.  Errors: AHLP_EINVAL for sizes out
  * of range, AHLP_ENUMERIC for non-finite data, AHLP_ENOMEM, AHLP_EHIP. */
 ahlp_status_t ahlp_problem_create(const ahlp_problem_desc_t* desc, hipStream_t stream,

@@ -17,6 +17,7 @@
 
 #include "../../include/ahlp.h"
 #include "common.h"
+#include "copy_room.h"
 #include "kernels.h"
 
 using namespace ahlp;
@@ -1144,8 +1145,15 @@ bool pack_block(const double* __restrict__ A, const BlockInfo& b, double* __rest
 // 10, 40, 60 and 80% nonzeros (0.15, 0.55, 0.82 and 1.05 of the dense bytes):
 // 1.63, 1.97, 2.22 and 2.18 ms against 2.42, 2.38, 2.38 and 2.15 ms; so it is
 // used up to SPARSE_SHARE of them.  It takes at most an eighth of the free
-// memory; without that the dense passes stay.
+// memory (copy_fits); without that the dense passes stay.
 constexpr double SPARSE_SHARE = 0.9;
+
+// Bytes that a handle may allocate after create: the FP32 forms of the blocks and their
+// factors, the copy of q, the tall kernels' scratch while tuning.
+double later_bytes(const ahlp_problem_s* p) {
+  return 4.0 * (double)(p->a_total + p->lb_total + p->linv_total) + 8.0 * (double)p->n_tot +
+         8.0 * (double)tall_scratch_doubles(p->N);
+}
 ahlp_status_t sparse_setup(ahlp_problem_t p, const std::vector<int>& rownz,
                            const std::vector<int>& colnz, const std::vector<int>& ccolnz,
                            hipStream_t st) {
@@ -1191,7 +1199,7 @@ ahlp_status_t sparse_setup(ahlp_problem_t p, const std::vector<int>& rownz,
   if (need > 64e6) {   // (the query takes longer than a small problem's fill)
     size_t mem_free = 0, mem_all = 0;
     HIPCHK(hipMemGetInfo(&mem_free, &mem_all));
-    if (8.0 * need > (double)mem_free) return AHLP_OK;
+    if (!copy_fits(need, (double)mem_free, later_bytes(p))) return AHLP_OK;
   }
   DevMem& M = p->mem;
   SpMat& s = p->sp;
@@ -1345,7 +1353,9 @@ ahlp_status_t syrk_setup(ahlp_problem_t p, const std::vector<unsigned char>& stn
   size_t mem_free = 0, mem_all = 0;
   HIPCHK(hipMemGetInfo(&mem_free, &mem_all));
   unsigned char* base = nullptr;
-  if (8 * bytes > mem_free || p->mem.alloc(&base, (long long)bytes) != AHLP_OK) {
+  // (half as much again for the FP32 values at first use)
+  if (!copy_fits(1.5 * (double)bytes, (double)mem_free, later_bytes(p)) ||
+      p->mem.alloc(&base, (long long)bytes) != AHLP_OK) {
     // no memory for the lists: the dense tiles
     (void)hipGetLastError();
     g_err.clear();

@@ -1579,7 +1579,8 @@ void launch_block_factor_tall(hipStream_t st, const BlockInfo* blk, const int* o
                          st, blk, part, LB, PQ);
   });
 }
-size_t tall_scratch_doubles(int n) { return (size_t)n * 2 * TALL_ND * TE; }
+// (the slots go by blockIdx.y)
+size_t tall_scratch_doubles(int n) { return (size_t)std::min(n, GRID_ROWS) * 2 * TALL_ND * TE; }
 bool block_factor_panel_fits(int rt) { return rt <= 4 * BF_RMAX_MAX; }
 bool block_factor_panel8_fits(int rt) { return rt <= 8 * 5; }
 template void launch_block_factor_panel<double>(hipStream_t, const BlockInfo*, const int*, int, int,
