@@ -1556,7 +1556,11 @@ bool factor_fused_fits(int rt, int mt) { return rt <= 4 * BF_RMAX_MAX && mt <= 2
 // Tall blocks (any height): one launch per panel, the last panel's diagonal
 // factors copied into place by one more, then the Schur contributions.  A
 // block gets enough workgroups for one tile row per wave as long as the launch
-// stays within the two workgroups that fit a CU.
+// stays within the two workgroups that fit a CU; with four a CU, so that the diagonal
+// blocks are factored again for a second round of workgroups, 48, 96, 160 and 256
+// blocks of 645-900 rows took 1318, 2150, 3235 and 4710 us a factorization where they
+// take 1292, 2095, 3090 and 4515 (up to 24 blocks, with a row per wave either way, the
+// same 1000).
 template <typename T>
 void launch_block_factor_tall(hipStream_t st, const BlockInfo* blk, const int* order, int n,
                               int max_mt, int max_rt, int max_kt, T* LB, T* LINV, double* PQ,
@@ -1569,7 +1573,7 @@ void launch_block_factor_tall(hipStream_t st, const BlockInfo* blk, const int* o
     for (int c0 = 0;; c0 += TALL_W) {
       const int rows = max_rt - std::min(c0 + TALL_W, max_mt);
       const int g = c0 >= max_mt ? 1 : std::max(1, std::min((rows + TALL_NW - 1) / TALL_NW,
-                                                             std::max(1, 4 * num_cu / count)));
+                                                             std::max(1, 2 * num_cu / count)));
       hipLaunchKernelGGL(k_tall_panel<T>, dim3(g, count), dim3(64 * TALL_NW), 0, st, blk, part, LB, LINV,
                          bthr, reinterpret_cast<T*>(scratch), info, c0);
       if (c0 >= max_mt) break;
