@@ -137,30 +137,10 @@ struct DevInfo {
   int nonfinite;    // x or z not finite / not positive at factor
 };
 
-// Cross-lane sums on the VALU (DPP moves within a 16-lane row, permlane
-// swaps across rows) instead of LDS-pipe permutes.  Each gives every lane the
-// additions of the xor butterfly x += shfl_xor(x, s) over its strides, in the
-// same order, so the results are bitwise the same.  The controls used here
-// (quad permutations, row mirrors) give every lane a source, so a move needs
-// no old value.
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double v) {
-  union { double d; int i[2]; } u, o;
-  u.d = v;
-  o.i[0] = __builtin_amdgcn_mov_dpp(u.i[0], CTRL, 0xF, 0xF, false);
-  o.i[1] = __builtin_amdgcn_mov_dpp(u.i[1], CTRL, 0xF, 0xF, false);
-  return o.d;
-}
-// strides 1, 2, 4, 8: the sum over the lane's 16-lane row.  After the two
-// quad steps every lane of a quad holds the same value, so the half-row and
-// row mirrors read the same values as the xor-4 and xor-8 partners.
-__device__ __forceinline__ double row_sum16(double x) {
-  x += dpp_mov<0xB1>(x);    // quad_perm [1,0,3,2]: lane ^ 1
-  x += dpp_mov<0x4E>(x);    // quad_perm [2,3,0,1]: lane ^ 2
-  x += dpp_mov<0x141>(x);   // row_half_mirror: the other quad of the half row
-  x += dpp_mov<0x140>(x);   // row_mirror: the other half row
-  return x;
-}
+// Cross-lane sums on the VALU (permlane swaps across 16-lane rows) instead of
+// LDS-pipe permutes.  Each gives every lane the additions of the xor butterfly
+// x += shfl_xor(x, s) over its strides, in the same order, so the results are
+// bitwise the same.
 // x_l + x_(l ^ S) for S = 16 or 32: the swap leaves the two values of each
 // lane pair in its two outputs, whose sum is the same in both lanes
 template <int S>

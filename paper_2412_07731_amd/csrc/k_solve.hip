@@ -618,51 +618,12 @@ __global__ void k_adj_scale(long long n, int mode, const double* __restrict__ zs
     out[i] = mode ? v[i] / zs[i] : zs[i] * v[i];
 }
 
-// dz = (rz - zs dx) / xs
-__global__ void k_dz(long long n, const double* __restrict__ rz, const double* __restrict__ zs,
-                     const double* __restrict__ xs, const double* __restrict__ dx,
-                     double* __restrict__ dz) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    dz[i] = (rz[i] - zs[i] * dx[i]) / xs[i];
-}
-
-// Refinement residual pieces in x-space: ex = rx - g - dz;  ez = rz - zs dx - xs dz.
 // dual residual from a maintained g = A'y:  rd = c - g - z
 __global__ void k_rd(long long n, const double* __restrict__ c, const double* __restrict__ g,
                      const double* __restrict__ z, double* __restrict__ rd) {
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
     rd[i] = c[i] - g[i] - z[i];
-}
-
-__global__ void k_res_x(long long n, const double* __restrict__ rx, const double* __restrict__ rz,
-                        const double* __restrict__ g, const double* __restrict__ dx,
-                        const double* __restrict__ dz, const double* __restrict__ xs,
-                        const double* __restrict__ zs, double* __restrict__ ex,
-                        double* __restrict__ ez) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    ex[i] = rx[i] - g[i] - dz[i];
-    ez[i] = rz[i] - (zs[i] * dx[i] + xs[i] * dz[i]);
-  }
-}
-
-// w = D (a b) / x in padded x-space (a null: w = D / x); the x_0 part is zero.
-__global__ void k_wscaled(const BlockInfo* __restrict__ blk, int N, int n0, long long x0off,
-                          long long d0off, const double* __restrict__ a,
-                          const double* __restrict__ b, const double* __restrict__ xs,
-                          const double* __restrict__ Dp, double* __restrict__ w) {
-  const int i = blockIdx.x;
-  long long xo, po;
-  int n, np;
-  if (i < N) { xo = blk[i].xoff; po = blk[i].dpoff; n = blk[i].n; np = TS * blk[i].nt; }
-  else { xo = x0off; po = d0off; n = 0; np = (n0 + TS - 1) / TS * TS; }
-  for (int c = threadIdx.x; c < np; c += blockDim.x) {
-    double v = 0.0;
-    if (c < n) v = Dp[po + c] * (a ? a[xo + c] * b[xo + c] : 1.0) / xs[xo + c];
-    w[po + c] = v;
-  }
 }
 
 // out = t - smu a + b
@@ -949,12 +910,6 @@ void launch_pad_x(hipStream_t st, const BlockInfo* blk, int N, int n0, long long
                   long long d0off, const double* x, double* xp, const double* scale) {
   hipLaunchKernelGGL(k_pad_x, dim3(N + 1), dim3(256), 0, st, blk, N, n0, x0off, d0off, x, xp, scale);
 }
-void launch_wscaled(hipStream_t st, const BlockInfo* blk, int N, int n0, long long x0off,
-                    long long d0off, const double* a, const double* b, const double* xs,
-                    const double* Dp, double* w) {
-  hipLaunchKernelGGL(k_wscaled, dim3(N + 1), dim3(256), 0, st, blk, N, n0, x0off, d0off, a, b, xs,
-                     Dp, w);
-}
 void launch_combine(hipStream_t st, long long n, const double* t, double smu, const double* a,
                     const double* b, double* out, const double* smu_dev) {
   hipLaunchKernelGGL(k_combine, dim3(grid1d(n)), dim3(256), 0, st, n, t, smu, smu_dev, a, b, out);
@@ -1118,19 +1073,9 @@ void launch_axpys(hipStream_t st, double a, std::initializer_list<Axpy> list) {
   }
   if (most > 0) hipLaunchKernelGGL(k_axpy, dim3(grid1d(most), k), dim3(256), 0, st, a, s);
 }
-void launch_dz(hipStream_t st, long long n, const double* rz, const double* zs, const double* xs,
-               const double* dx, double* dz) {
-  hipLaunchKernelGGL(k_dz, dim3(grid1d(n)), dim3(256), 0, st, n, rz, zs, xs, dx, dz);
-}
 void launch_rd(hipStream_t st, long long n, const double* c, const double* g, const double* z,
                double* rd) {
   hipLaunchKernelGGL(k_rd, dim3(grid1d(n)), dim3(256), 0, st, n, c, g, z, rd);
-}
-void launch_res_x(hipStream_t st, long long n, const double* rx, const double* rz,
-                  const double* g, const double* dx, const double* dz, const double* xs,
-                  const double* zs, double* ex, double* ez) {
-  hipLaunchKernelGGL(k_res_x, dim3(grid1d(n)), dim3(256), 0, st, n, rx, rz, g, dx, dz, xs, zs, ex,
-                     ez);
 }
 void launch_copy(hipStream_t st, long long n, const double* src, double* dst) {
   if (n > 0) hipLaunchKernelGGL(k_copy, dim3(grid1d(n)), dim3(256), 0, st, n, src, dst);

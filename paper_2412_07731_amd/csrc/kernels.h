@@ -47,8 +47,8 @@ void launch_syrk_sp(hipStream_t st, const BlockInfo* blk, const int4* items, int
 void launch_syrk_sp_fill(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
                          const double* A, const SyrkSp& sp, double* val, unsigned short* idx);
 void set_syrk_sp_smem_limits();
-template <typename T>
 // nb: width of the border section (global rows, then x_0)
+template <typename T>
 void launch_link(hipStream_t st, const BlockInfo* blk, const int2* items, int nitems, int nb,
                  const double* A, const double* C, const int* lptr, const int* lcol,
                  const double* lval, const double* Dp, T* LB, double* PQ);
@@ -134,9 +134,8 @@ struct ChainSolveArgs {
 constexpr int SEGRHS_STRIDE = 2 * LMAX + N0MAX;
 
 
-// Tile path (pairs of at most 16 rows, at most 64 linking variables).
-// Block cyclic reduction of T and the border (k_bcr.hip), pairs of <= 16 rows,
-// n0 <= 64.  Tiles are 16x16 column-major, padded.
+// Block cyclic reduction of T and the border (k_bcr.hip, k_bcrn.hip for pairs of over
+// 16 rows), for a border of at most 64.  Tiles are 16x16 column-major, padded.
 struct BcrArgs {
   int P, n0, t0, ng;                              // n0: border width, ng of it global rows
   int tp;                                         // tiles per pair side (1 to 4)
@@ -206,12 +205,7 @@ struct RowsArgs {
   int padded[RV_MAX];           // output in padded v-space (rows >= m_i set to 0) or canonical
   int chain[RV_MAX];
 };
-// w = D (a b) / x (padded x-space; a, b canonical, null a: w = D / x); x_0 part zero
-void launch_wscaled(hipStream_t st, const BlockInfo* blk, int N, int n0, long long x0off,
-                    long long d0off, const double* a, const double* b, const double* xs,
-                    const double* Dp, double* w);
-// out = t - smu * a + b over n values
-// out = t - smu a + b; smu from *smu_dev when that is not null
+// out = t - smu a + b over n values; smu from *smu_dev when that is not null
 void launch_combine(hipStream_t st, long long n, const double* t, double smu, const double* a,
                     const double* b, double* out, const double* smu_dev = nullptr);
 // scal[s_out] = (mu_aff / mu)^3 mu with mu = scal[s_xz] / n, mu_aff = scal[s_muaff] / n;
@@ -269,9 +263,6 @@ void launch_linkrows(hipStream_t st, const BlockInfo* blk, const LinkArgs& la);
 // The row passes take the link and global rows along, in workgroups of their own.
 void launch_rows_multi(hipStream_t st, const BlockInfo* blk, const int2* rowtiles, int nrt,
                        const double* A, const double* C, long long d0off, const RowsArgs& ra, const LinkArgs& la);
-// the dual rows after the blocks (link rows, then global rows):
-// out = base + alpha (F xp [+ F0 x0]); F0 the extended (nl + ng) x n0 coupling,
-// F0L the same or null when its link rows are zero
 
 // Optional fused output of the column pass (mode 2): dz = (rz - zs dx) / xs
 struct DzArgs {
@@ -355,13 +346,8 @@ void launch_axpys(hipStream_t st, double a, std::initializer_list<Axpy> list);
 // the transposed Newton solve into a Newton solve)
 void launch_adj_scale(hipStream_t st, long long n, int mode, const double* zs, const double* v,
                       double* out);
-void launch_dz(hipStream_t st, long long n, const double* rz, const double* zs, const double* xs,
-               const double* dx, double* dz);
 void launch_rd(hipStream_t st, long long n, const double* c, const double* g, const double* z,
                double* rd);
-void launch_res_x(hipStream_t st, long long n, const double* rx, const double* rz,
-                  const double* g, const double* dx, const double* dz, const double* xs,
-                  const double* zs, double* ex, double* ez);
 void launch_copy(hipStream_t st, long long n, const double* src, double* dst);
 // rz = -x z (mode 0) or smu - x z - dxa dza (mode 1); smu from *smu_dev when not null.
 // With bounds (b.ub, mode 1) also the corrector's x right-hand side

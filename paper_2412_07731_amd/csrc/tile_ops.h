@@ -91,52 +91,6 @@ __device__ __forceinline__ d4 mma_xyt(d4 acc, const double* X, const double* Y, 
   }
   return acc;
 }
-// acc += alpha X S Y' with S = diag(-1 where neg has the bit of the inner
-// index, +1 elsewhere)
-template <int LD = TS>
-__device__ __forceinline__ d4 mma_xsyt(d4 acc, const double* X, const double* Y, double alpha,
-                                       unsigned neg) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const double f = ((neg >> (4 * s + (lane >> 4))) & 1u) ? -alpha : alpha;
-    const int o = tix<LD>(lane & 15, 4 * s + (lane >> 4));
-    acc = mfma(f * X[o], Y[o], acc);
-  }
-  return acc;
-}
-// acc += alpha X Y
-template <int LD = TS>
-__device__ __forceinline__ d4 mma_xy(d4 acc, const double* X, const double* Y, double alpha) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-    acc = mfma(alpha * X[tix<LD>(lane & 15, 4 * s + (lane >> 4))],
-               Y[tix<LD>(4 * s + (lane >> 4), lane & 15)], acc);
-  return acc;
-}
-// acc += alpha X' Y
-template <int LD = TS>
-__device__ __forceinline__ d4 mma_txy(d4 acc, const double* X, const double* Y, double alpha) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int o = tix<LD>(4 * s + (lane >> 4), lane & 15);
-    acc = mfma(alpha * X[o], Y[o], acc);
-  }
-  return acc;
-}
-// tile copy between leading dimensions LDD (destination) and LDS_ (source)
-template <int LDD = TS, int LDS_ = TS>
-__device__ __forceinline__ void tile_copy(double* dst, const double* src) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int i = lane & 15, j = 4 * s + (lane >> 4);
-    dst[tix<LDD>(i, j)] = src[tix<LDS_>(i, j)];
-  }
-}
-
 __device__ __forceinline__ void vec_put(double* dst, double y) {
   const int lane = threadIdx.x & 63;
   if (lane < 16) dst[lane] = y;
