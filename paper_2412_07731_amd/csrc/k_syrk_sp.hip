@@ -42,45 +42,33 @@ template <> struct Pair<double> { typedef double type __attribute__((ext_vector_
 template <> struct Pair<float> { typedef float type __attribute__((ext_vector_type(2))); };
 
 // A DPP operand must not have been written by the vector unit in the two wait states
-// before, and the compiler does not look into asm for that: every asm that reads one
+// before, and the compiler does not look into asm for that: an asm that reads one
 // starts with these waits, so that it stands wherever it is scheduled.  (With the waits
-// on the first of a chunk alone, each instruction an asm of its own, the kernel took 5%
-// less: 200 us where it is 209; with a chunk's four entries in one asm 212 us, since its
-// products then wait for all four reads.)
+// on a chunk's first product alone the kernel took 2% less; with two or four entries in
+// one asm 2% to 5% more, since their products then wait for each other's reads.)
 
-// acc + (lane J, then J + 1 of the 16-lane row's a) * x for both columns.  The FP64 form
-// is written out: the compiler broadcasts into a register first.
+// Both columns' acc + (lane J of the 16-lane row's a) * x.  The FP64 form is written
+// out: the compiler broadcasts into a register first.
 template <int J>
-__device__ __forceinline__ void fmac_bcast(double a, const Pair<double>::type* x, double& c0, double& c1) {
+__device__ __forceinline__ void fmac_bcast(double a, const Pair<double>::type& x, double& c0, double& c1) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm("s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %2, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
-      : "+&v"(c0), "+&v"(c1)
-      : "v"(a), "v"(x[0].x), "v"(x[0].y), "v"(x[1].x), "v"(x[1].y), "n"(J), "n"(J + 1));
+      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+      : "+&v"(c0), "+&v"(c1) : "v"(a), "v"(x.x), "v"(x.y), "n"(J));
 #endif
 }
 template <int J>
-__device__ __forceinline__ void fmac_bcast(float a, const Pair<float>::type* x, float& c0, float& c1) {
-  const float a0 = row_bcast<J>(a), a1 = row_bcast<J + 1>(a);
-  c0 = fmaf(a1, x[1].x, fmaf(a0, x[0].x, c0));
-  c1 = fmaf(a1, x[1].y, fmaf(a0, x[0].y, c1));
+__device__ __forceinline__ void fmac_bcast(float a, const Pair<float>::type& x, float& c0, float& c1) {
+  const float aj = row_bcast<J>(a);
+  c0 = fmaf(aj, x.x, c0);
+  c1 = fmaf(aj, x.y, c1);
 }
 
-// xb plus lanes J .. J + 3 of the row's o
+// xb + lane J of the row's o: one DPP add, to which the compiler gives its waits
 template <int J>
-__device__ __forceinline__ void add_bcast(unsigned o, unsigned xb, unsigned (&r)[4]) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm("s_nop 1\n\t"
-      "v_add_u32_dpp %0, %4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_u32_dpp %1, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_u32_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_u32_dpp %3, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
-      : "v"(o), "v"(xb), "n"(J), "n"(J + 1), "n"(J + 2), "n"(J + 3));
-#endif
+__device__ __forceinline__ unsigned add_bcast(unsigned o, unsigned xb) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)o, 0x150 + J, 0xF, 0xF, true) + xb;
 }
 template <typename T>
 using LdsPair = const __attribute__((address_space(3))) typename Pair<T>::type*;
@@ -89,14 +77,16 @@ using LdsPair = const __attribute__((address_space(3))) typename Pair<T>::type*;
 // of X, o: each lane's entry's byte offset of its row, added lane to lane.
 template <int J, typename T>
 __device__ __forceinline__ void sp_chunk(T a, unsigned o, unsigned xb, T& c0, T& c1) {
-  unsigned at[4];
   typename Pair<T>::type x[4];
-  add_bcast<J>(o, xb, at);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) x[u] = *(LdsPair<T>)at[u];
+  x[0] = *(LdsPair<T>)add_bcast<J>(o, xb);
+  x[1] = *(LdsPair<T>)add_bcast<J + 1>(o, xb);
+  x[2] = *(LdsPair<T>)add_bcast<J + 2>(o, xb);
+  x[3] = *(LdsPair<T>)add_bcast<J + 3>(o, xb);
   __builtin_amdgcn_sched_barrier(0);   // all reads before the first product
-  fmac_bcast<J>(a, x, c0, c1);
-  fmac_bcast<J + 2>(a, x + 2, c0, c1);
+  fmac_bcast<J>(a, x[0], c0, c1);
+  fmac_bcast<J + 1>(a, x[1], c0, c1);
+  fmac_bcast<J + 2>(a, x[2], c0, c1);
+  fmac_bcast<J + 3>(a, x[3], c0, c1);
 }
 
 template <typename T>
