@@ -595,15 +595,16 @@ def main():
         # the dominant kernel by device time
         "roofline": {"kernel": dom_name, "bound": "mfma" if fused else "lds",
                      "achieved": dom_tflops, "peak": peak, "unit": "TFLOP/s", "frac": dom_tflops / peak,
-                     "traffic": (measured_traffic("k_factor_fused", "n512")
-                                 if fused and main_prec == FP64 else None),
+                     "traffic": (measured_traffic("k_factor_fused" if fused else "k_syrk_sp", "n512")
+                                 if main_prec == FP64 else None),
                      "flop_per_launch": dom_flop, "avg_launch_ms": dom_ms,
                      "launches_per_solve": nfact / args.steps},
         "rooflines_other": [
             {"kernel": "k_sp_rows (row pass out_k = base_k + A v_k over the compressed blocks, "
                        "1-3 vectors per read, the link rows beside it)",
              "bound": "hbm", "achieved": rows_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-             "frac": rows_gbs / PEAK_HBM_GBS, "traffic": None,
+             "frac": rows_gbs / PEAK_HBM_GBS,
+             "traffic": measured_traffic("k_sp_rows", "n512") if main_prec == FP64 and not fused else None,
              "bytes_per_launch": rows_bytes_avg, "avg_launch_ms": rows_ms,
              "launches_per_solve": n_rows, "timed": "in the extra fully timed solve"}],
     }

@@ -140,10 +140,13 @@ typedef struct {
 
 /* Stage indices of ahlp_ipm_result_t.t_stage_ms / n_stage. */
 enum {
-  AHLP_ST_PREP = 0,       /* D-scaling, link columns (a1)                            */
-  AHLP_ST_SYRK = 1,       /* M_i = A_i D_i A_i' (a2)                                 */
-  AHLP_ST_FACTOR = 2,     /* Cholesky of M_i and W_i = L_i^-1 B_i (a3, a4)            */
-  AHLP_ST_SCHUR = 3,      /* W_i' W_i and assembly of S (a5)                          */
+  AHLP_ST_PREP = 0,       /* D-scaling (a1)                                          */
+  AHLP_ST_SYRK = 1,       /* M_i = A_i D_i A_i' (a2); the link columns (a1) where they */
+                          /* go along in its launch, and in per-block launches        */
+  AHLP_ST_FACTOR = 2,     /* Cholesky of M_i and W_i = L_i^-1 B_i (a3, a4), with      */
+                          /* W_i' W_i; the link columns otherwise; the whole fused    */
+                          /* launch                                                  */
+  AHLP_ST_SCHUR = 3,      /* assembly of S (a5)                                       */
   AHLP_ST_TFACTOR = 4,    /* block-tridiagonal + border factorization of S (a6)       */
   AHLP_ST_SOLVE = 5,      /* solve phase (a7)                                         */
   AHLP_ST_RESID = 6,      /* residuals, reductions, refinement residuals (a8)         */
@@ -164,7 +167,8 @@ typedef struct {
   double t_stage_ms[AHLP_ST_COUNT];   /* summed device time per stage (timing=1)     */
   int32_t n_stage[AHLP_ST_COUNT];     /* number of timed launches per stage         */
   double rows_bytes;      /* algorithmic HBM bytes of the timed row passes          */
-                          /* (AHLP_ST_AROWS): A and C read, vectors read and written */
+                          /* (AHLP_ST_AROWS): A and C read (10 bytes a nonzero where  */
+                          /* they read the compressed copy), vectors read and written */
   int32_t correctors;     /* Gondzio correctors kept over the whole run             */
   double start_bkerr[2];  /* backward errors of the two starting-point solves       */
                           /* after refinement (-1 with opts->start == 1)            */
@@ -253,7 +257,9 @@ ahlp_status_t ahlp_kkt_solve(ahlp_problem_t p, const double* rx, const double* r
  * workspace (solve-phase and Schur-solve vectors, refinement residual and
  * correction, reduction partials and scalar slots) lives in the library's
  * static device array of 32 MiB per GPU (held until the process ends) instead
- * of the handle's.  The call allocates nothing.  Problems whose workspace
+ * of the handle's; for link pairs of over 32 rows the Schur solve's pair vectors
+ * lie in a second set of the handle's, which only this call uses.  The call
+ * allocates nothing.  Problems whose workspace
  * exceeds the array are refused with AHLP_EINVAL (the N = 512 workload, 256 x
  * 512 blocks, needs about 24 MiB).  Every call on one GPU shares that GPU's
  * array and clears it first: calls that overlap on one GPU (other streams,
@@ -307,17 +313,18 @@ ahlp_status_t ahlp_problem_set_bc(ahlp_problem_t p, const double* b, const doubl
 /* How the per-block stages of the factorization (SYRK, link columns, block
  * Cholesky with W_i and the Schur products; the per-block steps of Alg. 2,
  * Sec. 3.2) are launched.  Blocks of uneven size go largest first and the
- * block factor runs in two buckets, by whether the bordered block fits the
- * panel kernel.
+ * block factor runs in up to three buckets, by the kernel that takes the
+ * bordered block (four-wave panel, eight-wave panel, tall; ahlp_autotune).
  * AHLP_LAUNCH_BATCHED (default): one launch per stage over all blocks (the
- * SYRK, the link columns on a second stream beside it, the two factor
- * buckets).
+ * SYRK, then the link columns, or those in the SYRK's launch where both are
+ * small, then the factor buckets, beside each other on two streams if there is
+ * a four-wave one and another).
  * AHLP_LAUNCH_PER_BLOCK: the same kernels, one launch per block and stage, in
  * block order.
- * AHLP_LAUNCH_FUSED: the panel bucket in one persistent launch over a
+ * AHLP_LAUNCH_FUSED: the four-wave panel bucket in one persistent launch over a
  * largest-first block queue, in which each CU's workgroup forms the next
- * block's link columns and SYRK while it factors the previous one; the column
- * bucket, if any, beside it with one launch per stage.
+ * block's link columns and SYRK while it factors the previous one; the other
+ * buckets, if any, beside it with launches per stage.
  * The arithmetic per block is the same in all three, so results are bitwise
  * equal.  Errors: AHLP_EINVAL. */
 enum { AHLP_LAUNCH_BATCHED = 0, AHLP_LAUNCH_PER_BLOCK = 1, AHLP_LAUNCH_FUSED = 2 };

@@ -1255,7 +1255,8 @@ ahlp_status_t sparse_setup(ahlp_problem_t p, const std::vector<int>& rownz,
 // per 64 x 64 item and 0.043 (FP32 0.025) per 16 x 16 x 16 tile product, the
 // other 1.5 per item, 1.75 (0.95) per item and stage and 0.003 (0.0023) per
 // nonzero walked, more than twice that past 16 in a row and stage.  256 blocks of 256 x 512, FP64: 198 us dense; lists 76, 114,
-// 176 and 282 us at 3, 10, 20 and 30% nonzeros.  With fewer items than two per
+// 176 and 282 us at 3, 10, 20 and 30% nonzeros (some 3% more since every product
+// has its own wait states).  With fewer items than two per
 // CU the launch lasts as long as its longest items, and the dense ones are
 // shorter (47 blocks of 110 x 220: 16 us against 24); and a second launch has
 // to be worth its 20 us.

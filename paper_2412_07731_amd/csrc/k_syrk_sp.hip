@@ -12,16 +12,18 @@
 // zero leave the chain's value as it is, so this gives the dense kernel's
 // values bit for bit.
 //
-// What bounds it is the LDS read per nonzero and 128 columns.  Two columns a
-// lane make it a 16-byte read in FP64, which the LDS serves at 234 bytes per
+// What bounds it is the LDS read per nonzero and 128 columns, and a stage's fixed
+// part (clearing and expanding the products between barriers): the LDS is active in
+// 55% of the cycles, the vector unit in 39%, memory at 1.15 TB/s (counters).  Two
+// columns a lane make it a 16-byte read in FP64, which the LDS serves at 234 bytes per
 // clock (8-byte reads: 125); a nonzero's value and k reach all lanes by DPP
 // from the lane of each row of 16 that loaded it, as operands of the
 // multiply-add and of the address sum, so that the vector unit stays below the
-// LDS time.  512 blocks of 256 x 512 at 3.2% nonzeros: 252 us against the dense
-// kernel's 377 us in FP64, 181 against 209 us in FP32, all with the link columns'
-// gather beside them; 200 and 146 us since it has its turn.  (Broadcast by scalar
+// LDS time.  512 blocks of 256 x 512 at 10% nonzeros: 206 us against the dense
+// kernel's 368 us in FP64, 149 against 207 us in FP32 (with the link columns' gather
+// beside it on another stream 252 and 181 us, and 377 and 209 us).  (Broadcast by scalar
 // loads waits on their latency, since those share their counter with the LDS
-// reads: 333 us; one column a lane and a stage of 128: 273 us.)
+// reads: 333 us with the gather beside it; one column a lane and a stage of 128: 273 us.)
 #include "common.h"
 #include "kernels.h"
 #include "tile_chol.h"
@@ -41,11 +43,12 @@ template <typename T> struct Pair;
 template <> struct Pair<double> { typedef double type __attribute__((ext_vector_type(2))); };
 template <> struct Pair<float> { typedef float type __attribute__((ext_vector_type(2))); };
 
-// A DPP operand must not have been written by the vector unit in the two wait states
-// before, and the compiler does not look into asm for that: an asm that reads one
-// starts with these waits, so that it stands wherever it is scheduled.  (With the waits
-// on a chunk's first product alone the kernel took 2% less; with two or four entries in
-// one asm 2% to 5% more, since their products then wait for each other's reads.)
+// A DPP instruction's operands must not have been written by the vector unit in the two
+// wait states before, and the compiler does not look into asm for that: an asm with one
+// starts with these waits, so that it stands wherever it is scheduled, and its products
+// are of both columns, so that no sum follows itself sooner.  (With the waits on a chunk's
+// first product alone the kernel took 2% to 3% less; two or four entries in one asm took
+// 2% to 3% more, since their products then wait for each other's reads.)
 
 // Both columns' acc + (lane J of the 16-lane row's a) * x.  The FP64 form is written
 // out: the compiler broadcasts into a register first.

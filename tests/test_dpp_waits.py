@@ -1,7 +1,8 @@
 """The wait states of hand-written DPP instructions do not rest on the order the
 compiler gives: in the assembly of every kernel, each inline-assembly block that reads
 a DPP operand starts with the two wait states that a vector write before it needs, and
-writes none of its DPP sources."""
+none of its instructions reads what another of the block has written (counting every
+operand, the accumulator of a multiply-add too, as the compiler's own rule does)."""
 import os
 import re
 import subprocess
@@ -35,7 +36,8 @@ def faults(asm):
             if "_dpp" not in s:
                 continue
             ops = [o.strip() for o in s.split(" row_")[0].split(None, 1)[1].split(",")]
-            if regs(ops[1]) & written:
+            read = set().union(*(regs(o) for o in (ops if "fmac" in s else ops[1:])))
+            if read & written:
                 out.append(f"{s} reads what the block wrote")
             written |= regs(ops[0])
     return seen, out
@@ -46,6 +48,8 @@ def test_checker():
     assert faults(ok) == (1, [])
     assert faults(ok.replace("\ts_nop 1\n", ""))[1]
     assert faults(ok.replace("\n\t;;", "\n\tv_add_u32_dpp v9, v3, v8 row_newbcast:1\n\t;;"))[1]
+    assert faults(ok.replace("\n\t;;", "\n\tv_fmac_f64_dpp v[2:3], v[4:5], v[8:9] row_newbcast:2\n\t;;"))[1]
+    assert not faults(ok.replace("\n\t;;", "\n\tv_fmac_f64_dpp v[8:9], v[4:5], v[10:11] row_newbcast:2\n\t;;"))[1]
 
 
 @pytest.mark.parametrize("name", FILES)
