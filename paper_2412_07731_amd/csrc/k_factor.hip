@@ -1557,7 +1557,7 @@ bool factor_fused_fits(int rt, int mt) { return rt <= 4 * BF_RMAX_MAX && mt <= 2
 // factors copied into place by one more, then the Schur contributions.  A
 // block gets enough workgroups for one tile row per wave as long as the launch
 // stays within the two workgroups that fit a CU; with four a CU, so that the diagonal
-// blocks are factored again for a second round of workgroups, 48, 96, 160 and 256
+// blocks are factored again for a second turn of workgroups, 48, 96, 160 and 256
 // blocks of 645-900 rows took 1318, 2150, 3235 and 4710 us a factorization where they
 // take 1292, 2095, 3090 and 4515 (up to 24 blocks, with a row per wave either way, the
 // same 1000).

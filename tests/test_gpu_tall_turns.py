@@ -13,7 +13,7 @@ from tests.test_gpu_parity import T, dev, point  # noqa: E402, F401
 
 
 @pytest.mark.parametrize("N", [48, 140])
-def test_rounds(dev, N):  # noqa: F811
+def test_turns(dev, N):  # noqa: F811
     from paper_2412_07731_amd.ahlp import FP32_REFINE, Problem
     inst = gen.generate(dict(N=N, m=(645, 680), n="2m", l=(1, 9), n0=3, density=0.02), 2)
     print("case", N, flush=True)
